@@ -64,6 +64,9 @@ __device__ __forceinline__ void store8(bf16_t* p, const float (&v)[8])
     *reinterpret_cast<uint4*>(p) = a;
 }
 
+// Number of this workgroup in a one-dimensional grid that lookm_host::wide_grid may have folded into rows.
+__device__ __forceinline__ unsigned wide_block() { return blockIdx.y * gridDim.x + blockIdx.x; }
+
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63); }
 
 // number of set bits of a 64-bit wave mask below this lane
@@ -110,6 +113,15 @@ size_t decode_scratch_bytes(int H, int d);
 size_t decode_partial_bytes(int H, int S, int d);
 int decode_static_scratch_setup();     // once per device: resolves the device address of the static scratch array
 float* decode_static_scratch();        // that address for the current device (null before the set-up)
+
+// `blocks` workgroups of 256 threads in a row, folded into rows of 2^22: a grid of 2^32 threads or more in one dimension is
+// cut down to its low 32 bits without an error.  A batch of prompts folded into the heads gets there.  The last row may
+// hold workgroups past the end; 2^22 is a multiple of eight, so consecutive workgroups stay on consecutive XCDs.
+inline dim3 wide_grid(size_t blocks)
+{
+    constexpr size_t row = (size_t)1 << 22;
+    return blocks <= row ? dim3((unsigned)blocks) : dim3((unsigned)row, (unsigned)((blocks + row - 1) / row));
+}
 
 inline int hip_ok(hipError_t e) { return e == hipSuccess ? LOOKM_OK : LOOKM_ERR_DEVICE; }
 

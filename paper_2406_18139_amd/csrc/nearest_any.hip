@@ -28,7 +28,7 @@ constexpr int NA_WAVES = 4;
 template <typename T>
 __global__ void __launch_bounds__(256) k_rnorm(const T* __restrict__ k, size_t rows, int d, float* __restrict__ rnorm)
 {
-    inverse_norms(k, rows, d, blockIdx.x, rnorm);
+    inverse_norms(k, rows, d, wide_block(), rnorm);
 }
 
 // The best and the second best value and their slots; equal values in the order of their slots.
@@ -60,16 +60,17 @@ k_nearest_any(const T* __restrict__ k, const float* __restrict__ rnorm, const in
     constexpr int SR = 16 * CG;
     __shared__ top_two fold[NA_WAVES][SR];
     __shared__ __attribute__((aligned(1024))) char blocks[NA_WAVES][FRAG_BLOCK * frag_row_bytes<KS>()];
+    const unsigned unit = wide_block();
     int h, t;                                        // XCD-affine by head, as in k_score_any
     if (H >= 8) {
-        const int j = blockIdx.x >> 3;
-        h = (j / n_strips) * 8 + (blockIdx.x & 7);
+        const int j = unit >> 3;
+        h = (j / n_strips) * 8 + (unit & 7);
         t = j % n_strips;
     } else {
-        h = blockIdx.x % H;
-        t = blockIdx.x / H;
+        h = unit % H;
+        t = unit / H;
     }
-    if (h >= H) return;
+    if (h >= H || t >= n_strips) return;
     k += (size_t)h * L * d;
     rnorm += (size_t)h * L;
     kept += (size_t)h * B;
@@ -209,13 +210,13 @@ static int launch_nearest_t(const T* k, const int32_t* kept, const int32_t* evic
     const LaunchCheck check;
     const size_t rows = (size_t)H * L;
     if (!rnorm_ready)
-        hipLaunchKernelGGL(lookm::k_rnorm<T>, dim3((unsigned)((rows + 31) / 32)), dim3(256), 0, st, k, rows, d, rnorm);
+        hipLaunchKernelGGL(lookm::k_rnorm<T>, wide_grid((rows + 31) / 32), dim3(256), 0, st, k, rows, d, rnorm);
     mark(LOOKM_K_RNORM);
     if (mfma) return launch_nearest_mfma(k, kept, evicted, H, L, budget, rnorm, assign, sim, scratch, st);
     lookm::with_frag_shape<T>(d, [&](int rows) { return (long)((Le + rows - 1) / rows) * H; }, [&](auto steps, auto groups) {
         constexpr int KS = decltype(steps)::value, CG = decltype(groups)::value;
         const int strips = (Le + 16 * CG - 1) / (16 * CG);
-        hipLaunchKernelGGL((lookm::k_nearest_any<T, KS, CG>), dim3((unsigned)((H >= 8 ? (H + 7) / 8 * 8 : H) * strips)), dim3(256), 0, st,
+        hipLaunchKernelGGL((lookm::k_nearest_any<T, KS, CG>), wide_grid((size_t)(H >= 8 ? (H + 7) / 8 * 8 : H) * strips), dim3(256), 0, st,
                            k, rnorm, kept, evicted, H, L, d, budget, Le, strips, assign, sim);
     });
     mark(LOOKM_K_NEAREST);

@@ -65,7 +65,7 @@ __device__ __forceinline__ void lse_update(const acc_t (&acc)[2][CG], float scal
 }
 
 // PASS 1: stationary q (query heads), streamed k; writes lse2.  PASS 2: stationary k (key heads), streamed q of each of
-// the `group` query heads in turn; writes scores.  Workgroups from n_units on compute inverse key norms instead.
+// the `group` query heads in turn; writes scores.  Workgroups from n_units on compute the inverse norms of norm_rows keys.
 template <int PASS, typename T, int KS, int CG>
 __global__ void __launch_bounds__(256, 2)
 k_score_any(const T* __restrict__ q, const T* __restrict__ k, int heads, int group, int L, int R0, int d, float scale2,
@@ -76,21 +76,22 @@ k_score_any(const T* __restrict__ q, const T* __restrict__ k, int heads, int gro
     constexpr int SR = 16 * CG;                      // stationary rows
     __shared__ float fold_a[SA_WAVES][SR], fold_b[PASS == 1 ? SA_WAVES : 1][SR];
     __shared__ __attribute__((aligned(1024))) char blocks[SA_WAVES][FRAG_BLOCK * frag_row_bytes<KS>()];
-    if (blockIdx.x >= n_units) {
-        inverse_norms(k, norm_rows, d, blockIdx.x - n_units, rnorm);
+    const unsigned unit = wide_block();
+    if (unit >= n_units) {
+        inverse_norms(k, norm_rows, d, unit - n_units, rnorm);
         return;
     }
     // consecutive workgroups go to consecutive XCDs: with eight or more heads XCD x works through the heads x, x + 8, ...,
     // `together` of them at a time (as many as its L2 holds the streamed rows of), the longest strips of those first
     int h, t;
     if (heads >= 8) {
-        const int j = blockIdx.x >> 3, set = j / (n_strips * together), in_set = j % (n_strips * together);
+        const int j = unit >> 3, set = j / (n_strips * together), in_set = j % (n_strips * together);
         const int n = min(together, (heads + 7) / 8 - set * together);         // heads in this set
-        h = (set * together + in_set % n) * 8 + (blockIdx.x & 7);
+        h = (set * together + in_set % n) * 8 + (unit & 7);
         t = in_set / n;
     } else {
-        h = blockIdx.x % heads;
-        t = blockIdx.x / heads;
+        h = unit % heads;
+        t = unit / heads;
     }
     if (h >= heads) return;
     const int nS = (L + SR - 1) / SR;
@@ -250,8 +251,7 @@ static int launch_scores_any(const T* q, const T* k, int H, int kv_heads, int L,
     const LaunchCheck check;
     const int group = H / kv_heads;
     const float scale2 = lookm::kLog2e / sqrtf((float)d);
-    const size_t norm_rows = (size_t)kv_heads * L;
-    const unsigned norm_blocks = rnorm ? (unsigned)((norm_rows + 31) / 32) : 0u;     // they ride with the first launch
+    const size_t norm_rows = rnorm ? (size_t)kv_heads * L : 0, norm_blocks = (norm_rows + 31) / 32;   // they ride with the first launch
     auto units = [](int heads, int strips) { return (unsigned)((heads >= 8 ? (heads + 7) / 8 * 8 : heads) * strips); };
     const int together = (int)std::min<size_t>(64, std::max<size_t>(1, (size_t)(2 << 20) / ((size_t)L * d * sizeof(T))));
     auto strips = [&](int rows) { return (long)((L - R0 + rows - 1) / rows) * H; };
@@ -260,14 +260,14 @@ static int launch_scores_any(const T* q, const T* k, int H, int kv_heads, int L,
         const int nS = (L + 16 * CG - 1) / (16 * CG);
         if (!lse_in) {
             const int n1 = nS - R0 / (16 * CG);       // strips with a query row that counts (observation window)
-            hipLaunchKernelGGL((lookm::k_score_any<1, T, KS, CG>), dim3(units(H, n1) + norm_blocks), dim3(256), 0, st, q, k, H, group,
+            hipLaunchKernelGGL((lookm::k_score_any<1, T, KS, CG>), wide_grid(units(H, n1) + norm_blocks), dim3(256), 0, st, q, k, H, group,
                                L, R0, d, scale2, (const float*)nullptr, 1.0f, lse, n1, together, units(H, n1), norm_rows, rnorm);
             mark(LOOKM_K_SCORE_LSE);
         }
         // a caller-supplied row log-sum-exp is natural-log: one factor log2(e) brings it to the kernels' base
-        hipLaunchKernelGGL((lookm::k_score_any<2, T, KS, CG>), dim3(units(kv_heads, nS) + (lse_in ? norm_blocks : 0u)), dim3(256), 0,
+        hipLaunchKernelGGL((lookm::k_score_any<2, T, KS, CG>), wide_grid(units(kv_heads, nS) + (lse_in ? norm_blocks : 0)), dim3(256), 0,
                            st, q, k, kv_heads, group, L, R0, d, scale2, lse_in ? lse_in : lse, lse_in ? lookm::kLog2e : 1.0f,
-                           scores, nS, together, units(kv_heads, nS), norm_rows, rnorm);
+                           scores, nS, together, units(kv_heads, nS), lse_in ? norm_rows : 0, rnorm);
         mark(LOOKM_K_SCORE_COLSUM);
     });
     return check.status();

@@ -101,3 +101,22 @@ def test_nearly_equal_cosines_are_decided_by_the_sum_in_the_order_of_the_dims(d,
     kept, ev = (torch.arange(n, 3 * n)[None].int().cuda(), torch.arange(n)[None].int().cuda())
     a, _ = lookm.lookm_nearest(k.cuda(), kept, ev)
     assert (a.cpu().numpy()[0] == want).all()
+
+
+def test_more_heads_than_one_grid_dimension_holds():
+    # 2^24 workgroups of 256 threads are 2^32: a batch of prompts folded into the heads passes that with a workgroup per head
+    H, d = (1 << 24) + 200_001, 8
+    g = torch.Generator(device="cuda").manual_seed(7)
+    x = torch.randn((H, 2, d), generator=g, device="cuda").to(BF)
+    logits = (x[:, 1, None].float() * x.float()).sum(2) / d ** 0.5          # of row 1; row 0 sees key 0 alone
+    want = torch.softmax(logits, 1)
+    want[:, 0] += 1
+    assert (lookm.lookm_scores(x, x) - want).abs().max() < 1e-5
+    k = torch.cat([x, torch.randn((H, 1, d), generator=g, device="cuda").to(BF)], 1)
+    kept = torch.tensor([0, 2], dtype=torch.int32, device="cuda").repeat(H, 1)
+    ev = torch.ones((H, 1), dtype=torch.int32, device="cuda")
+    a, sim = lookm.lookm_nearest(k, kept, ev)
+    cos = torch.nn.functional.cosine_similarity(k[:, 1, None].float(), k[:, ::2].float(), dim=2)
+    assert (sim[:, 0] - cos.max(1).values).abs().max() < 1e-5
+    clear = (cos[:, 0] - cos[:, 1]).abs() > 1e-5
+    assert torch.equal(a[clear, 0].long(), cos.argmax(1)[clear])
