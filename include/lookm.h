@@ -141,6 +141,7 @@ int lookm_compress(const void* q, const void* k, const void* v, const uint8_t* m
  * Eq. 4: scores_out[h, j] = sum over rows i >= j of exp(q_i.k_j/sqrt(d) - lse_i), where lse_i is the
  * log-sum-exp of row i over columns <= i.  Two flash-style passes over Q K^T (row log-sum-exp, then
  * column sums), on the matrix cores with fp32 accumulation (fp32 inputs: fp32 products).
+ *   Attention weights below 2^-126 count as zero for bf16 with d = 128 and are kept, down to 2^-149, for other shapes.
  *   scores_out  device, float [H, L].
  */
 int lookm_scores(const void* q, const void* k, int H, int L, int d, lookm_dtype dt,

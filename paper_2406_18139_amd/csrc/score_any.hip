@@ -64,6 +64,37 @@ __device__ __forceinline__ void lse_update(const acc_t (&acc)[2][CG], float scal
     }
 }
 
+// This thread's share of the sums over FEW keys of one query head, rows thread, thread + 256, ... from each key on: dots in
+// the order of the dims on the vector ALU and exp2f, which gives weights down to 2^-149.
+constexpr int FEW = 4;
+template <typename T>
+__device__ __forceinline__ void weights_of_keys(const T* __restrict__ q, const T* __restrict__ k, const float* __restrict__ lse2,
+                                                const int (&key)[FEW], int R0, int L, int d, float scale2, float lse_scale,
+                                                float (&sum)[FEW])
+{
+    for (int i = max(key[0], R0) + (int)threadIdx.x; i < L; i += 64 * SA_WAVES) {        // key[0] is the lowest
+        float dot[FEW] = {};
+#pragma unroll 2
+        for (int c = 0; c < d; c += 8) {
+            float y[8];
+            load8(q + (size_t)i * d + c, y);
+#pragma unroll
+            for (int n = 0; n < FEW; ++n) {
+                float x[8];
+                load8(k + (size_t)key[n] * d + c, x);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) dot[n] = fmaf(y[e], x[e], dot[n]);
+            }
+        }
+        const float neg = -lse2[i] * lse_scale;
+#pragma unroll
+        for (int n = 0; n < FEW; ++n) {
+            const float p = exp2f(fmaf(dot[n], scale2, neg));
+            sum[n] += (i >= key[n]) ? p : 0.f;
+        }
+    }
+}
+
 // PASS 1: stationary q (query heads), streamed k; writes lse2.  PASS 2: stationary k (key heads), streamed q of each of
 // the `group` query heads in turn; writes scores.  Workgroups from n_units on compute the inverse norms of norm_rows keys.
 template <int PASS, typename T, int KS, int CG>
@@ -218,21 +249,58 @@ k_score_any(const T* __restrict__ q, const T* __restrict__ k, int heads, int gro
         }
     }
     __syncthreads();
-    if (tid < SR && s0 + tid < L) {
-        float sum = 0.f;
-        if (PASS == 1) {
-            float M = -1e30f;
+    const bool mine = lane < SR && s0 + lane < L;    // every wave folds the waves' sums: row s0 + lane
+    float sum = 0.f;
+    if (PASS == 1) {
+        if (wave != 0 || !mine) return;
+        float M = -1e30f;
 #pragma unroll
-            for (int w = 0; w < SA_WAVES; ++w) M = fmaxf(M, fold_b[w][tid]);
+        for (int w = 0; w < SA_WAVES; ++w) M = fmaxf(M, fold_b[PASS == 1 ? w : 0][lane]);
 #pragma unroll
-            for (int w = 0; w < SA_WAVES; ++w) sum = fmaf(fold_a[w][tid], exp2f(fold_b[w][tid] - M), sum);
-            sum = M + log2f(sum);
-        } else {
+        for (int w = 0; w < SA_WAVES; ++w) sum = fmaf(fold_a[w][lane], exp2f(fold_b[PASS == 1 ? w : 0][lane] - M), sum);
+        sum = M + log2f(sum);
+    } else {
+        auto fold = [&]() {
+            float f = 0.f;
 #pragma unroll
-            for (int w = 0; w < SA_WAVES; ++w) sum += fold_a[w][tid];
+            for (int w = 0; w < SA_WAVES; ++w) f += fold_a[w][lane];
+            return f;
+        };
+        if (mine) sum = fold();
+        // The bare exponential instruction gives zero for weights below 2^-126.  `n` of them are below n * 2^-126: a sum above
+        // n * 2^-102 has lost nothing in its 24 bits, a smaller one is worked out again with exp2f, which gives subnormal
+        // weights too, so that keys that hardly any query looks at are still told apart.  (exp2f in the loop above would cost four
+        // instructions more per logit, a second run of that loop eight registers and with them a wave per SIMD.  With every
+        // key that far down, 32 x 2781 x 64 bf16 takes 574 us instead of 60, less than the 786 us of scores on the vector ALU.)
+        const uint64_t few = __ballot(mine && sum < (float)group * (float)L * 0x1p-102f);      // alike in all four waves
+        if (__builtin_expect(few != 0, 0)) {
+            __syncthreads();                         // fold_a has been read
+            for (uint64_t todo = few; todo != 0;) {
+                int r[FEW], key[FEW];
+#pragma unroll
+                for (int n = 0; n < FEW; ++n) {      // fewer left: the last one again
+                    r[n] = (n == 0 || todo != 0) ? __builtin_ctzll(todo) : r[n > 0 ? n - 1 : 0];
+                    key[n] = s0 + r[n];
+                    todo &= todo - 1;
+                }
+                float f[FEW] = {};
+                for (int g = 0; g < group; ++g) {
+                    const size_t row0 = ((size_t)h * group + g) * L;
+                    weights_of_keys(q + row0 * d, k + (size_t)h * L * d, lse2 + row0, key, R0, L, d, scale2, lse_scale, f);
+                }
+#pragma unroll
+                for (int n = 0; n < FEW; ++n) {
+#pragma unroll
+                    for (int off = 1; off < 64; off <<= 1) f[n] += __shfl_xor(f[n], off);
+                    if (lane == 0) fold_a[wave][r[n]] = f[n];
+                }
+            }
+            __syncthreads();
+            if ((few >> lane) & 1) sum = fold();
         }
-        out[(size_t)h * L + s0 + tid] = sum;
+        if (wave != 0 || !mine) return;
     }
+    out[(size_t)h * L + s0 + lane] = sum;
 }
 
 }  // namespace lookm

@@ -76,6 +76,34 @@ def test_infinite_keys_and_nan_queries_stay_where_they_are(d, dtype):
     np.testing.assert_allclose(got.numpy(), p[bad + 1:].sum(0).numpy(), rtol=3e-5)
 
 
+@pytest.mark.parametrize("d,dtype,group,window,own_lse", [(64, F32, 1, 0, False), (64, BF, 1, 0, False), (24, BF, 2, 0, False), (128, F32, 1, 40, False),
+                                                          (8, F32, 1, 0, True), (256, BF, 1, 0, False)])
+def test_weights_below_the_normal_range_are_kept(d, dtype, group, window, own_lse):
+    # The first key takes all the attention; the others' logits lie 60 to 103 below (natural units), their weights around and
+    # far below 2^-126 = e^-87.3, down to the smallest number fp32 has.
+    L = 300
+    q, k = torch.zeros(group, L, d), torch.zeros(1, L, d)
+    q[..., 0] = 8.0 * d ** 0.5
+    k[0, 1:, 0] = -torch.linspace(60, 103, L - 1) / 8
+    q, k = q.to(dtype), k.to(dtype)
+    logits = (q.double() @ k[0].double().t()) / d ** 0.5
+    p = torch.softmax(logits.masked_fill(torch.ones(L, L).triu(1).bool(), -float("inf")), 2)
+    want = p[:, L - window if window else 0:].sum((0, 1))
+    qg, kg = q.cuda(), k.cuda()
+    if own_lse:
+        lse = torch.logsumexp(logits.masked_fill(torch.ones(L, L).triu(1).bool(), -float("inf")), 2).float()
+        got = lookm.lookm_scores_lse(qg, kg, lse.cuda())
+    elif window:
+        got = lookm.lookm_scores_window(qg, kg, window)
+    else:
+        got = lookm.lookm_scores_grouped(qg, kg)
+    got = got.cpu().double()[0]
+    # exponents of up to 150 binades are rounded to 2^-17: 5e-6 of the weight and once more for the log-sum-exp; a subnormal
+    # weight is rounded to 2^-149, and its sum over the rows with it
+    assert ((got - want).abs() <= 2e-5 * want + group * L * 2.0 ** -149).all()
+    assert (want < 2.0 ** -126).sum() > 50 and got[1:].unique().numel() > 250
+
+
 @pytest.mark.parametrize("d,dtype", [(64, BF), (80, BF), (256, BF), (24, F32), (128, F32)])
 def test_nearly_equal_cosines_are_decided_by_the_sum_in_the_order_of_the_dims(d, dtype):
     # Evicted keys that read the same backwards, and for each a conserved key and its mirror image: equal dots and norms in
