@@ -148,3 +148,38 @@ def test_more_heads_than_one_grid_dimension_holds():
     assert (sim[:, 0] - cos.max(1).values).abs().max() < 1e-5
     clear = (cos[:, 0] - cos[:, 1]).abs() > 1e-5
     assert torch.equal(a[clear, 0].long(), cos.argmax(1)[clear])
+
+
+@pytest.mark.parametrize("d,dtype,n,padding", [(64, BF, 150, 40), (80, BF, 60, 700), (256, BF, 40, 3), (24, F32, 150, 0), (128, F32, 90, 300),
+                                               (32, BF, 1200, 0)])
+def test_more_than_two_nearly_equal_cosines(d, dtype, n, padding):
+    # Evicted keys that are the same read backwards and with their halves swapped.  For each, a conserved key in its four
+    # arrangements - equal dots and norms in exact arithmetic - and one of them twice: five candidates apart by roundings.
+    g = torch.Generator().manual_seed(d + n)
+    quarter = torch.randn(n, d // 4, generator=g)
+    a = torch.cat([quarter, quarter.flip(1)], 1)
+    e = torch.cat([a, a], 1).to(dtype)
+    c = (e.float() + 0.3 * torch.randn(n, d, generator=g)).to(dtype)
+    swap = lambda x: torch.cat([x[:, d // 2:], x[:, :d // 2]], 1)
+    arranged = [c, c.flip(1), swap(c), swap(c.flip(1))]
+    twice = torch.stack(arranged)[torch.randint(0, 4, (n,), generator=g), torch.arange(n)]
+    other = torch.randn(padding, d, generator=g).to(dtype)         # conserved keys of no interest, one of them NaN
+    if padding:
+        other[padding // 2, 1] = float("nan")
+    k = torch.cat([e, *arranged, twice, other])[None].contiguous()
+    perm = torch.randperm(5 * n + padding, generator=g)
+    k[0, n:] = k[0, n:][perm]
+    kf = k[0].double().numpy()
+    dot = np.zeros((n, 5 * n + padding), np.float32)
+    for i in range(d):                              # fused multiply-adds: one rounding to fp32 per dim
+        dot = (kf[:n, None, i] * kf[None, n:, i] + dot.astype(np.float64)).astype(np.float32)
+    val = dot * (1 / np.sqrt((kf[n:] ** 2).sum(-1))).astype(np.float32)
+    want = np.where(np.isnan(val), -np.inf, val).argmax(1)       # the lowest slot of the largest value
+    kept, ev = (torch.arange(n, 6 * n + padding)[None].int().cuda(), torch.arange(n)[None].int().cuda())
+    got, _ = lookm.lookm_nearest(k.cuda(), kept, ev)
+    assert (got.cpu().numpy()[0] == want).all()
+    # every conserved key a copy of the same one, and an evicted key of zeros among the others: the lowest slot
+    k[0, n:] = c[0]
+    k[0, 1] = 0
+    got, _ = lookm.lookm_nearest(k.cuda(), kept, ev)
+    assert (got == 0).all()
