@@ -105,8 +105,10 @@ const char* lookm_status_string(int status);
 int lookm_protected_count(const uint8_t* mask_host, int L, int recent_window);
 
 /*
- * Bytes of device scratch that lookm_compress (and each stage call) needs for these sizes;
- * 0 on invalid sizes.  The workspace must be 256-byte aligned.
+ * Bytes of device scratch for lookm_compress (and each stage call) at these sizes; 0 on invalid sizes.  The workspace
+ * must be 256-byte aligned.  For bf16 with d = 128 a part of it only buys speed: a smaller workspace is accepted as long as
+ * it holds the partial sums of chunks of max(8, T / 6144) tiles (T: 64-row tiles of the causal half, all heads).  The
+ * score sums are then added in longer chunks and may differ in their last bits.
  */
 size_t lookm_workspace_bytes(int H, int L, int d, int budget, lookm_dtype dt);
 
@@ -126,7 +128,7 @@ size_t lookm_workspace_bytes(int H, int L, int d, int budget, lookm_dtype dt);
  *                  bf16, d = 128) the second score pass runs only over the keys that compete in the selection -
  *                  image tokens before the recent window - which is faster; the cache comes out bit for bit the same.
  *   status_out     device, int32 [1]: LOOKM_OK or LOOKM_ERR_BUDGET_BELOW_PROTECTED. Must not be NULL.
- *   workspace      device scratch of at least lookm_workspace_bytes(H, L, d, budget, dt) bytes.
+ *   workspace      device scratch of lookm_workspace_bytes(H, L, d, budget, dt) bytes (see there for smaller ones).
  */
 int lookm_compress(const void* q, const void* k, const void* v, const uint8_t* modality_mask,
                    int H, int L, int d, lookm_dtype dt,

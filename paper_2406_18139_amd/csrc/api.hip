@@ -14,7 +14,7 @@ constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-    size_t lse, scores, evicted, assign, sim, rnorm, plan, member_pos, member_w, lists, partials, total;
+    size_t lse, scores, evicted, assign, sim, rnorm, plan, member_pos, member_w, lists, partials, total, least;    // total: what lookm_workspace_bytes gives; least: what is accepted
 };
 
 // Hq query heads, H key / value heads (Hq = H without grouped query heads): only the row log-sum-exp and the score
@@ -36,9 +36,12 @@ Layout make_layout(int Hq, int H, int L, int d, int dt, int budget)
     w.lists = o;      o += align_up(lookm_host::score_list_ints(L) * sizeof(int32_t));   // competing / protected keys
     // the score partials and the matching partials are never live at the same time: one slice serves both
     w.partials = o;
-    o += align_up(std::max(lookm_host::scores_scratch_floats(Hq, L, d, (lookm_dtype)dt) * sizeof(float),
-                           lookm_host::nearest_scratch_bytes(H, L, d, (lookm_dtype)dt, budget)));
-    w.total = o;
+    auto end = [&](bool least) {
+        return o + align_up(std::max(lookm_host::scores_scratch_floats(Hq, L, d, (lookm_dtype)dt, least) * sizeof(float),
+                                     lookm_host::nearest_scratch_bytes(H, L, d, (lookm_dtype)dt, budget)));
+    };
+    w.total = end(false);
+    w.least = end(true);
     return w;
 }
 
@@ -63,7 +66,7 @@ int check_budget(int L, int budget, int M)
 int check_workspace(const void* ws, size_t bytes, int Hq, int H, int L, int d, int dt, int budget)
 {
     if (ws == nullptr || (reinterpret_cast<uintptr_t>(ws) % kAlign) != 0) return LOOKM_ERR_WORKSPACE;
-    if (bytes < make_layout(Hq, H, L, d, dt, budget).total) return LOOKM_ERR_WORKSPACE;
+    if (bytes < make_layout(Hq, H, L, d, dt, budget).least) return LOOKM_ERR_WORKSPACE;
     return LOOKM_OK;
 }
 
@@ -286,8 +289,8 @@ static int scores_impl(const void* q, const void* k, const float* row_lse, int H
     const Layout w = make_layout(H, kv_heads, L, d, (int)dt, 0);
     if ((rc = lookm_host::ensure_device_ready()) != LOOKM_OK) return rc;
     return lookm_host::launch_scores(q, k, H, kv_heads, L, d, dt, window ? L - window : 0, at<float>(workspace, w.lse),
-                                     row_lse, scores_out, nullptr, at<float>(workspace, w.partials), nullptr, 0, nullptr,
-                                     (hipStream_t)hip_stream);
+                                     row_lse, scores_out, nullptr, at<float>(workspace, w.partials),
+                                     (workspace_bytes - w.partials) / sizeof(float), nullptr, 0, nullptr, (hipStream_t)hip_stream);
 }
 
 int lookm_scores(const void* q, const void* k, int H, int L, int d, lookm_dtype dt, float* scores_out,
@@ -437,6 +440,7 @@ int enqueue_job(const lookm_job& j, hipStream_t st)
     int rc = lookm_host::launch_scores(j.q, j.k, Hq, H, L, d, dt, j.score_window ? L - j.score_window : 0,
                                        at<float>(workspace, w.lse), j.row_lse, scores,
                                        match ? rnorm : nullptr, at<float>(workspace, w.partials),
+                                       (j.workspace_bytes - w.partials) / sizeof(float),
                                        competing_only ? j.modality_mask : nullptr, j.recent_window,
                                        competing_only ? at<int32_t>(workspace, w.lists) : nullptr, st);
     if (rc != LOOKM_OK) return rc;

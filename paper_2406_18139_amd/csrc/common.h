@@ -92,10 +92,11 @@ namespace lookm_host {
 // entries of `scores` left unwritten (other shapes compute every score regardless).  lists: device scratch of
 // score_list_ints(L) ints.
 int launch_scores(const void* q, const void* k, int H, int kv_heads, int L, int d, lookm_dtype dt, int first_row,
-                  float* lse, const float* lse_in, float* scores, float* rnorm, float* scratch, const uint8_t* mask, int M,
-                  int32_t* lists, hipStream_t st);
+                  float* lse, const float* lse_in, float* scores, float* rnorm, float* scratch, size_t scratch_floats,
+                  const uint8_t* mask, int M, int32_t* lists, hipStream_t st);
 inline size_t score_list_ints(int L) { return (size_t)2 * L + 64; }
-size_t scores_scratch_floats(int H, int L, int d, lookm_dtype dt);
+// floats of scratch that the score passes like to have, or the least that they run with
+size_t scores_scratch_floats(int H, int L, int d, lookm_dtype dt, bool least);
 int launch_select(const float* scores, const uint8_t* mask, int H, int L, int budget, int M, int rule, int32_t* kept,
                   int32_t* evicted, int32_t* status, hipStream_t st);
 // rnorm_ready: rnorm already holds the inverse key norms (written by launch_scores)

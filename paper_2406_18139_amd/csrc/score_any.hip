@@ -308,9 +308,9 @@ k_score_any(const T* __restrict__ q, const T* __restrict__ k, int heads, int gro
 namespace lookm_host {
 
 int launch_scores_mfma(const void* q, const void* k, int H, int kv_heads, int L, int d, int R0, float* lse,
-                       const float* lse_in, float* scores, float* rnorm, float* scratch, const uint8_t* mask, int M,
-                       int32_t* lists, hipStream_t st);
-size_t scores_mfma_scratch_floats(int H, int L);
+                       const float* lse_in, float* scores, float* rnorm, float* scratch, size_t scratch_floats,
+                       const uint8_t* mask, int M, int32_t* lists, hipStream_t st);
+size_t scores_mfma_scratch_floats(int H, int L, bool least);
 
 template <typename T>
 static int launch_scores_any(const T* q, const T* k, int H, int kv_heads, int L, int d, int R0, float* lse,
@@ -341,19 +341,19 @@ static int launch_scores_any(const T* q, const T* k, int H, int kv_heads, int L,
     return check.status();
 }
 
-size_t scores_scratch_floats(int H, int L, int d, lookm_dtype dt)
+size_t scores_scratch_floats(int H, int L, int d, lookm_dtype dt, bool least)
 {
-    return (dt == LOOKM_BF16 && d == 128) ? scores_mfma_scratch_floats(H, L) : 0;
+    return (dt == LOOKM_BF16 && d == 128) ? scores_mfma_scratch_floats(H, L, least) : 0;
 }
 
 int launch_scores(const void* q, const void* k, int H, int kv_heads, int L, int d, lookm_dtype dt, int first_row,
-                  float* lse, const float* lse_in, float* scores, float* rnorm, float* scratch, const uint8_t* mask, int M,
-                  int32_t* lists, hipStream_t st)
+                  float* lse, const float* lse_in, float* scores, float* rnorm, float* scratch, size_t scratch_floats,
+                  const uint8_t* mask, int M, int32_t* lists, hipStream_t st)
 {
     const int R0 = first_row;
     if (dt == LOOKM_BF16) {
         if (d == 128)
-            return launch_scores_mfma(q, k, H, kv_heads, L, d, R0, lse, lse_in, scores, rnorm, scratch, mask, M, lists, st);
+            return launch_scores_mfma(q, k, H, kv_heads, L, d, R0, lse, lse_in, scores, rnorm, scratch, scratch_floats, mask, M, lists, st);
         return launch_scores_any((const lookm::bf16_t*)q, (const lookm::bf16_t*)k, H, kv_heads, L, d, R0, lse, lse_in, scores,
                                  rnorm, st);
     }

@@ -748,13 +748,29 @@ namespace lookm_host {
 //    47 K   (40 x 5904)                                    419   391   383   361   373   361   379   393
 //   158 K   (32 x 12644)                                  1377  1245  1194  1147  1139  1124  1126  1131
 //   264 K   (8 x 32768)                                   2551  2166  2012  1916  1884  1850  1843  1831
+//    1.06 M (32 x 32768)                    C = 40: 7239   67: 7212   100: 7227   172: 7252
+//    4.23 M (128 x 32768)                                133: 28570   256: 28900
 // The best length grows like the square root of the total.
-static int chunk_tiles(int H, int L)
+static long all_tiles(int H, int L)
 {
     long total = 0;
     const int nS = (L + lookm::BS - 1) / lookm::BS;
     for (int t = 0; t < nS; ++t) total += (L - t * lookm::BS + lookm::BX - 1) / lookm::BX;
-    return std::max(1, (int)std::ceil(0.065 * std::sqrt((double)total * H)));
+    return total * H;
+}
+static int chunk_tiles(int H, int L) { return std::max(1, (int)std::ceil(0.065 * std::sqrt((double)all_tiles(H, L)))); }
+// The chunk length whose partials every workspace holds: a smaller workspace than lookm_workspace_bytes gives is accepted
+// down to this, so that the sizes that a program has kept, or taken from its longest prompt, stay good for short chunks too.
+static int roomy_chunk_tiles(int H, int L)
+{
+    return (int)std::min(256l, std::max(8l, (all_tiles(H, L) + 6143) / 6144));
+}
+
+// floats of the chunk partials: two arrays [H][chunks][strips][256]
+static size_t partial_floats(int H, int L, int C)
+{
+    const int nS = (L + lookm::BS - 1) / lookm::BS, G = (L + C * lookm::BX - 1) / (C * lookm::BX);
+    return (size_t)2 * H * G * nS * lookm::BS;
 }
 
 static int total_chunks(int pass, int L, int C, int R0)
@@ -773,25 +789,24 @@ static unsigned score_grid(int H, int U)
     return 8u * (unsigned)((U + xph - 1) / xph);
 }
 
-// floats of scratch for the chunk partials: two arrays [H][chunks][strips][256]
-size_t scores_mfma_scratch_floats(int H, int L)
+size_t scores_mfma_scratch_floats(int H, int L, bool least)
 {
-    const int C = chunk_tiles(H, L), CT = C * lookm::BX;
-    const int nS = (L + lookm::BS - 1) / lookm::BS, G = (L + CT - 1) / CT;
-    return (size_t)2 * H * G * nS * lookm::BS;
+    const size_t floor = partial_floats(H, L, roomy_chunk_tiles(H, L));
+    return least ? floor : std::max(floor, partial_floats(H, L, chunk_tiles(H, L)));
 }
 
 // mask / M / lists: when given (the caller does not want the scores of the protected keys), pass 2 runs over the
 // competing keys only; lists: device, 2 * L + LIST_HEAD ints
 int launch_scores_mfma(const void* q, const void* k, int H, int kv_heads, int L, int d, int R0, float* lse,
-                       const float* lse_in, float* scores, float* rnorm, float* scratch, const uint8_t* mask, int M,
-                       int32_t* lists, hipStream_t st)
+                       const float* lse_in, float* scores, float* rnorm, float* scratch, size_t scratch_floats,
+                       const uint8_t* mask, int M, int32_t* lists, hipStream_t st)
 {
     if (d != lookm::SD) return LOOKM_ERR_UNSUPPORTED;
     const LaunchCheck check;
     const int group = H / kv_heads;
     const int nS = (L + lookm::BS - 1) / lookm::BS;
-    const int C = chunk_tiles(H, L);
+    int C = chunk_tiles(H, L);
+    while (partial_floats(H, L, C) > scratch_floats) ++C;      // (ends: roomy_chunk_tiles' partials fit)
     const int G = (L + C * lookm::BX - 1) / (C * lookm::BX);
     // Pass 2 keeps the full problem's chunk length also under a window (its partial arrays keep their layout).
     // Pass 1 under a window runs only the last strips, each over all keys: shorter chunks give the chip enough

@@ -131,6 +131,29 @@ def test_batch_validates_every_job_before_any_launch():
     assert run([fake_job(d=100), fake_job()]) == lookm.ERR_UNSUPPORTED and bad.value == 0
 
 
+def test_workspaces_of_a_longer_prompt_and_of_kept_sizes_are_accepted():
+    import ctypes
+    bad = ctypes.c_int(-1)
+
+    def accepted(H, n, budget, nbytes):
+        # every job is looked at before anything is launched: the second one is refused, so nothing is
+        jobs = (lookm.Job * 2)(fake_job(H=H, L=n, d=128, dt=lookm.BF16, budget=budget, workspace_bytes=nbytes), fake_job(q=None))
+        rc = lookm.lib().lookm_compress_batch(jobs, 2, ctypes.byref(bad), None)
+        assert (rc, bad.value) in ((lookm.ERR_INVALID_ARG, 1), (lookm.ERR_WORKSPACE, 0))
+        return rc == lookm.ERR_INVALID_ARG
+
+    # sizes that lookm_workspace_bytes gave before chunks became shorter, of programs that have kept them; one byte less is refused
+    kept = {(8, 700, 200): 278016, (32, 700, 160): 1095424, (8, 1482, 400): 675328, (32, 2896, 1000): 7579648,
+            (40, 5904, 2775): 30754304, (32, 12644, 2276): 50375424, (8, 32768, 4256): 33680640, (32, 32768, 4000): 92549376}
+    for (H, n, budget), nbytes in kept.items():
+        assert accepted(H, n, budget, nbytes) and not accepted(H, n, budget, nbytes - 1)
+        assert accepted(H, n, budget, lookm.workspace_bytes(H, n, 128, budget, lookm.BF16))
+    # one workspace for all prompts of up to `longest` tokens
+    for H, longest in ((8, 900), (8, 3000), (32, 400), (32, 1500), (32, 6000), (40, 2000), (40, 6000)):
+        nbytes = lookm.workspace_bytes(H, longest, 128, longest // 4, lookm.BF16)
+        assert all(accepted(H, n, n // 4, nbytes) for n in range(32, longest + 1))
+
+
 def test_two_stream_batch_and_workspace_offsets_validate_on_the_host():
     L = lookm.lib()
     bad = ctypes.c_int(-1)

@@ -109,6 +109,26 @@ def test_scores_from_a_supplied_row_lse(H, L, d, dtype):
     assert (np.abs(own - s) / ref).max() < 1e-5       # both routes agree
 
 
+@pytest.mark.parametrize("H,L,nbytes", [(8, 700, 278016), (32, 700, 1095424), (8, 1482, 675328), (32, 2896, 7579648)])
+@pytest.mark.parametrize("window", [0, 300])
+def test_compression_in_the_smallest_workspace(H, L, nbytes, window):
+    # a smaller workspace than lookm_workspace_bytes gives: longer chunks, nothing written past its end
+    d, B = 128, {(8, 700): 200, (32, 700): 160, (8, 1482): 400, (32, 2896): 1000}[H, L]
+    q, k = rand_qk(H, L, d, torch.bfloat16, seed=L + H)
+    qg, kg, mask = q.cuda(), k.cuda(), torch.ones(L, dtype=torch.uint8, device="cuda")
+    run = lambda ws: lookm.lookm_compress(qg, kg, kg, mask, B, 16, "averaged", want_scores=True, workspace=ws, score_window=window)
+    full = run(None)
+    ws = torch.full((nbytes + 256 + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    start = -ws.data_ptr() % 256
+    small = run(ws[start:start + nbytes])
+    assert (ws[start + nbytes:] == 0xA5).all()
+    # the same fp32 sums in another order: a few last bits in the log-sum-exp and in the column sum, 1.7e-6 measured
+    np.testing.assert_allclose(small.scores.cpu().numpy(), full.scores.cpu().numpy(), rtol=1e-5)
+    assert (small.kept_idx == full.kept_idx).float().mean() > 0.999      # two scores within that may trade places
+    again = run(ws[start:start + nbytes])
+    assert torch.equal(again.scores, small.scores) and torch.equal(again.k_out, small.k_out)
+
+
 @pytest.mark.parametrize("H,L,d,dtype,windows", [
     (2, 700, 128, torch.bfloat16, (1, 63, 64, 65, 300, 699, 700)),      # matrix cores: inside one tile, across chunks
     (2, 3000, 128, torch.bfloat16, (17, 256, 1000, 2999)),
