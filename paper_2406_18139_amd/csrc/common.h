@@ -67,6 +67,16 @@ __device__ __forceinline__ void store8(bf16_t* p, const float (&v)[8])
 // Number of this workgroup in a one-dimensional grid that lookm_host::wide_grid may have folded into rows.
 __device__ __forceinline__ unsigned wide_block() { return blockIdx.y * gridDim.x + blockIdx.x; }
 
+// Zero that the compiler knows nothing about.  In an index of the reads where the lanes of a wave hand values to each other
+// through LDS: the hardware executes a wave's LDS operations in order, and the compiler then has to keep those reads and
+// every write around them in order, since they may touch the same place.
+__device__ __forceinline__ int unknown_zero()
+{
+    int zero = 0;
+    asm volatile("" : "+v"(zero));
+    return zero;
+}
+
 __device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63); }
 
 // number of set bits of a 64-bit wave mask below this lane

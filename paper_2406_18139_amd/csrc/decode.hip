@@ -192,13 +192,14 @@ k_decode_merge(const float* __restrict__ part, const float2* __restrict__ part_m
     }
 #pragma unroll
     for (int off = 1; off < 64; off <<= 1) den += __shfl_xor(den, off);
-    __builtin_amdgcn_wave_barrier();                                        // the wave reads what its own lanes wrote
+    __builtin_amdgcn_wave_barrier();
+    const float* weight = wgt[wave] + unknown_zero();                       // the wave reads what its own lanes wrote
     float num = 0.f;
 #pragma unroll
     for (int i = 0; i < AHEAD; ++i)
-        if (slice + i * NSL < nsplit) num = fmaf(a[i], wgt[wave][slice + i * NSL], num);
+        if (slice + i * NSL < nsplit) num = fmaf(a[i], weight[slice + i * NSL], num);
 #pragma unroll 8
-    for (int s = slice + AHEAD * NSL; s < nsplit; s += NSL) num = fmaf(p[(size_t)s * d], wgt[wave][s], num);
+    for (int s = slice + AHEAD * NSL; s < nsplit; s += NSL) num = fmaf(p[(size_t)s * d], weight[s], num);
     red[slice][tid % DC_DIMS] = num;
     __syncthreads();
     if (slice == 0 && c < d) {

@@ -252,10 +252,11 @@ k_nearest_mfma(const bf16_t* __restrict__ k, const float* __restrict__ rnorm, co
                     rows[cb][hd][i] = *reinterpret_cast<const uint4*>(k + (size_t)pos * ND + hd * 64 + (lane & 7) * 8);
             }
         bf16_t* mine = turn[wave];
+        const bf16_t* theirs = mine + unknown_zero();
 #pragma unroll
         for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
-            for (int hd = 0; hd < 2; ++hd) {             // (LDS operations of a wave are executed in order)
+            for (int hd = 0; hd < 2; ++hd) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const int r = 8 * i + (lane >> 3);
@@ -263,7 +264,7 @@ k_nearest_mfma(const bf16_t* __restrict__ k, const float* __restrict__ rnorm, co
                 }
 #pragma unroll
                 for (int ks = 0; ks < 4; ++ks)
-                    sf[cb][4 * hd + ks] = __builtin_bit_cast(nbf16x8, *reinterpret_cast<const uint4*>(&mine[n * 64 + ((2 * ks + half) ^ (n & 7)) * 8]));
+                    sf[cb][4 * hd + ks] = __builtin_bit_cast(nbf16x8, *reinterpret_cast<const uint4*>(&theirs[n * 64 + ((2 * ks + half) ^ (n & 7)) * 8]));
             }
     }
     LOOKM_LOAD_TILE(xs0);

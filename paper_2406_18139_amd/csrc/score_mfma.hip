@@ -340,14 +340,15 @@ k_score_mfma(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, int H, 
                 rows[cg][i] = *reinterpret_cast<const uint4*>(S + (size_t)min((unsigned)row, (unsigned)(L - 1)) * SD + c16 * 8);
             }
         bf16_t* mine = turn[wave];
+        const bf16_t* theirs = mine + unknown_zero();
 #pragma unroll
-        for (int cg = 0; cg < 4; ++cg) {                 // (LDS operations of a wave are executed in order)
+        for (int cg = 0; cg < 4; ++cg) {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 *reinterpret_cast<uint4*>(&mine[(4 * i + q4) * XROW + (c16 ^ ((4 * i + q4) & 7)) * 8]) = rows[cg][i];
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks)
-                sf[cg][ks] = as_bf16x8(*reinterpret_cast<const uint4*>(&mine[c16 * XROW + ((4 * ks + q4) ^ (c16 & 7)) * 8]));
+                sf[cg][ks] = as_bf16x8(*reinterpret_cast<const uint4*>(&theirs[c16 * XROW + ((4 * ks + q4) ^ (c16 & 7)) * 8]));
         }
     }
 
