@@ -163,14 +163,25 @@ k_nearest_any(const T* __restrict__ k, const float* __restrict__ rnorm, const in
         fold_s(wave * 4 + q4)[16 * cg + c16] = s1[cg];
     }
     if (tid < SR) again[tid] = 0;
-    __syncthreads();
-    const bool mine = lane < SR && e0 + lane < Le;   // every wave folds the sixteen lanes: evicted key e0 + lane
-    const int at = mine ? lane : 0;
-    top_two found{-INFINITY, -INFINITY, -INFINITY, 0x7fffffff, 0x7fffffff};
-#pragma unroll
-    for (int j = 0; j < LANES; ++j) found.take(fold_v(j, 0)[at], fold_s(j)[at], fold_v(j, 1)[at]);
+    // every wave folds the sixteen lanes of evicted key e0 + lane; a strip of fewer than 64 keys shares them out to the lanes
+    const bool mine = lane < SR && e0 + lane < Le;
+    const int at = min(lane % SR, Le - 1 - e0);
     const int e_row = evicted[e0 + at];
     const float e_rn = rnorm[e_row];
+    __syncthreads();
+    top_two found{-INFINITY, -INFINITY, -INFINITY, 0x7fffffff, 0x7fffffff};
+#pragma unroll
+    for (int i = 0; i < LANES; i += 64 / SR) {
+        const int j = i + lane / SR;
+        found.take(fold_v(j, 0)[at], fold_s(j)[at], fold_v(j, 1)[at]);
+    }
+#pragma unroll
+    for (int step = SR; step < 64; step <<= 1) {
+        const top_two o{__shfl_xor(found.v1, step), __shfl_xor(found.v2, step), __shfl_xor(found.rest, step),
+                        __shfl_xor(found.s1, step), __shfl_xor(found.s2, step)};
+        found.take(o.v1, o.s1, o.rest);
+        found.take(o.v2, o.s2, -INFINITY);
+    }
     float v = found.v1;
     int s = found.s1;
     // A sum of d products in any order, roundings to nearest or towards zero, is off by at most d 2^-23 |e| |c|, the chain of fused

@@ -74,7 +74,7 @@ __device__ __forceinline__ void weights_of_keys(const T* __restrict__ q, const T
 {
     for (int i = max(key[0], R0) + (int)threadIdx.x; i < L; i += 64 * SA_WAVES) {        // key[0] is the lowest
         float dot[FEW] = {};
-#pragma unroll 2
+#pragma unroll sizeof(T) == 2 ? 2 : 1      // (fp32: two steps of four keys take more scalar registers than there are)
         for (int c = 0; c < d; c += 8) {
             float y[8];
             load8(q + (size_t)i * d + c, y);
