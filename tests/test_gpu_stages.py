@@ -23,7 +23,7 @@ def rand_qk(H, L, d, dtype, seed, scale=1.0):
     (2, 256, 128, torch.bfloat16),      # exactly one strip
     (1, 1, 128, torch.bfloat16),        # single token
     (2, 65, 128, torch.bfloat16),
-    (2, 333, 64, torch.bfloat16),       # portable path, bf16
+    (2, 333, 64, torch.bfloat16),       # other widths, bf16
     (2, 256, 64, torch.float32),        # the tiny configuration's shape
     (1, 130, 8, torch.float32),
     (1, 97, 256, torch.float32),
@@ -132,7 +132,7 @@ def test_compression_in_the_smallest_workspace(H, L, nbytes, window):
 @pytest.mark.parametrize("H,L,d,dtype,windows", [
     (2, 700, 128, torch.bfloat16, (1, 63, 64, 65, 300, 699, 700)),      # matrix cores: inside one tile, across chunks
     (2, 3000, 128, torch.bfloat16, (17, 256, 1000, 2999)),
-    (1, 333, 64, torch.bfloat16, (5, 200)),                             # portable kernels
+    (1, 333, 64, torch.bfloat16, (5, 200)),                             # other widths
     (2, 256, 64, torch.float32, (16, 255)),
 ])
 def test_window_scores_match_oracle(H, L, d, dtype, windows):
@@ -152,7 +152,7 @@ def test_window_scores_match_oracle(H, L, d, dtype, windows):
 @pytest.mark.parametrize("H,kvh,L,d,dtype", [
     (8, 2, 700, 128, torch.bfloat16),       # matrix cores, groups of four
     (6, 3, 1500, 128, torch.bfloat16),
-    (4, 1, 300, 64, torch.bfloat16),        # portable kernels, one key head for all query heads
+    (4, 1, 300, 64, torch.bfloat16),        # other widths, one key head for all query heads
     (4, 2, 256, 64, torch.float32),
 ])
 def test_grouped_scores_match_oracle(H, kvh, L, d, dtype):
@@ -279,7 +279,7 @@ def split(L, B, seed):
     (1, 300, 1, 128, torch.bfloat16),      # one conserved key
     (1, 300, 299, 128, torch.bfloat16),    # one evicted key
     (1, 32768, 32000, 128, torch.bfloat16),  # the longest prompt the library takes, nearly all of it conserved: nine chunks of 112 blocks
-    (2, 500, 130, 64, torch.bfloat16),     # portable path
+    (2, 500, 130, 64, torch.bfloat16),     # other widths
     (2, 256, 154, 64, torch.float32),
     (1, 100, 30, 8, torch.float32),
 ])
