@@ -35,6 +35,8 @@ static_assert(BX == 64, "the lse staging of pass 2 is done by wave 0, one row pe
 constexpr int XROW = 128;       // LDS row = 256 B, unpadded; the 16-byte chunk c of row r sits at chunk c ^ (r & 7),
                                // so 16-byte reads of 8 consecutive rows at the same c hit all 32 banks once
 
+typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
+
 __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast(bf16x8, v); }
 
 // Epilogues of a finished block: acc[rg][cg], rg = which 16 of the block's 32 streamed rows, cg = which 16 of the
@@ -330,14 +332,18 @@ k_score_mfma(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, int H, 
         }
     bf16x8 sf[4][4];
     {
-        uint4 rows[4][4];
+        // (Pass 1: a wave wholly past the end has zeros.  Under an observation window the last strip is all there is: a window of
+        // 64 in 12644 tokens, where two waves of four lie past the end, 40.1 -> 38.2 us.)
+        u32x4 rows[4][4];
 #pragma unroll
         for (int cg = 0; cg < 4; ++cg)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
+                rows[cg][i] = u32x4{0, 0, 0, 0};
+                if (PASS == 1 && w0 >= L) continue;
                 int row = w0 + 16 * cg + 4 * i + q4;     // rows past the end repeat the last one: nothing reads their results
                 if (sparse) row = clist[min(row, max(NC, 1) - 1)];
-                rows[cg][i] = *reinterpret_cast<const uint4*>(S + (size_t)min((unsigned)row, (unsigned)(L - 1)) * SD + c16 * 8);
+                rows[cg][i] = *reinterpret_cast<const u32x4*>(S + (size_t)min((unsigned)row, (unsigned)(L - 1)) * SD + c16 * 8);
             }
         bf16_t* mine = turn[wave];
         const bf16_t* theirs = mine + unknown_zero();
@@ -345,7 +351,7 @@ k_score_mfma(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, int H, 
         for (int cg = 0; cg < 4; ++cg) {
 #pragma unroll
             for (int i = 0; i < 4; ++i)
-                *reinterpret_cast<uint4*>(&mine[(4 * i + q4) * XROW + (c16 ^ ((4 * i + q4) & 7)) * 8]) = rows[cg][i];
+                *reinterpret_cast<u32x4*>(&mine[(4 * i + q4) * XROW + (c16 ^ ((4 * i + q4) & 7)) * 8]) = rows[cg][i];
 #pragma unroll
             for (int ks = 0; ks < 4; ++ks)
                 sf[cg][ks] = as_bf16x8(*reinterpret_cast<const uint4*>(&theirs[c16 * XROW + ((4 * ks + q4) ^ (c16 & 7)) * 8]));
