@@ -129,8 +129,9 @@ __device__ __forceinline__ void inverse_norms(const T* __restrict__ k, size_t ro
 // Calls f(steps, groups) with integral constants: the steps of a fragment that hold d dims, and how many groups of 16
 // stationary rows a wave keeps in registers next to them: as many as 64 registers hold (at most 4 groups, 2 for fp32,
 // whose matrix instructions take eight times as long per LDS byte) - or a single group where such strips would leave
-// most of the chip idle: strips(rows per strip) workgroups, fewer than one per compute unit.  (A 256-token fp32 prompt
-// of 2 x 64: score passes and matching 21 us with two groups, 16 us with one; 1483 tokens of 16 x 128, 750
+// most of the chip idle: strips(rows per strip), fewer than one per compute unit.  The score passes count the strips of
+// the query heads for both: with grouped heads pass 2 has fewer workgroups than that, each with several heads to go
+// through (32 query heads on 8 key heads x 700 x 64 bf16: 88 for 256 compute units; not tuned).  (A 256-token fp32 prompt of 2 x 64: score passes and matching 21 us with two groups, 16 us with one; 1483 tokens of 16 x 128, 750
 // workgroups: 163 us with two groups, 168 us with one, and a tenth of the LDS traffic more per flop than that shows.)
 template <typename T, typename Strips, typename F>
 inline void with_frag_shape(int d, Strips&& strips, F&& f)

@@ -14,10 +14,10 @@
 // enough workgroups, and nothing is written but the result.
 //
 // What bounds it: fp32 - the fp32 matrix instruction (64 flop per cycle and SIMD, and the vector ALU stands still
-// meanwhile: the co-execution counter reads zero); bf16 - the vector ALU, busy 85 % of the time with an exponential
-// and its two companions per logit.  Both passes over 16 heads x 1483 x 128 fp32: 129 us (74 TFLOP/s; on the vector
-// ALU, with 64 x 64 tiles in LDS: 685 us); over 32 x 2781 x 64 bf16: 67 us (790 us); over 2 x 256 x 64 fp32: 10 us
-// (64 us).
+// meanwhile: the co-execution counter reads zero; the matrix pipe is busy 62 % of the time); bf16 - the vector ALU, busy
+// 86 % of the time in pass 1 and 77 % in pass 2 with an exponential and its two companions per logit.  Both passes over
+// 16 heads x 1483 x 128 fp32: 128 us (74 TFLOP/s; on the vector ALU, with 64 x 64 tiles in LDS: 685 us); over
+// 32 x 2781 x 64 bf16: 66 us (790 us); over 2 x 256 x 64 fp32: 10 us (64 us).
 #include "frag.h"
 
 #include <algorithm>

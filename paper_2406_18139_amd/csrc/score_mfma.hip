@@ -747,13 +747,13 @@ namespace lookm_host {
 // so, only partly hidden by the two others of the compute unit) and the fold's time; long ones leave a few rounds of
 // workgroups and an uneven last one.  Both passes with their folds, event-free kernel times in us:
 //   total tiles (heads x length)      C =  1     2     3     4     6     8    12    16    20    24    40
-//      184  (8 x 700)                     26    28    31    33    39    45    53    53
+//      168  (8 x 700)                     26    28    31    33    39    45    53    53
 //      672  (8 x 1482)                    39    34    34    35    40    45    56    67
-//     2496  (8 x 2896)                    82    61    54    50    51    56    59    69
-//    10 K   (32 x 2896)                                    118   115   118   115   116   132   140   171
+//     2304  (8 x 2896)                    82    61    54    50    51    56    59    69
+//     9.2 K (32 x 2896)                                    118   115   118   115   116   132   140   171
 //    20 K   (8 x 8871)                   504   290   250   227   210   199   197   197
-//    47 K   (40 x 5904)                                    419   391   383   361   373   361   379   393
-//   158 K   (32 x 12644)                                  1377  1245  1194  1147  1139  1124  1126  1131
+//    45 K   (40 x 5904)                                    419   391   383   361   373   361   379   393
+//   160 K   (32 x 12644)                                  1377  1245  1194  1147  1139  1124  1126  1131
 //   264 K   (8 x 32768)                                   2551  2166  2012  1916  1884  1850  1843  1831
 //    1.06 M (32 x 32768)                    C = 40: 7239   67: 7212   100: 7227   172: 7252
 //    4.23 M (128 x 32768)                                133: 28570   256: 28900
