@@ -42,12 +42,28 @@ __device__ __forceinline__ bf16x8 as_bf16x8(uint4 v) { return __builtin_bit_cast
 // Epilogues of a finished block: acc[rg][cg], rg = which 16 of the block's 32 streamed rows, cg = which 16 of the
 // wave's 64 stationary rows.  Entry i of acc[rg][cg] is streamed row xq + 16*rg + i (xq = block start + 4q) against
 // this lane's stationary row of group cg, whose position is sP[cg].
+
+// A block on the diagonal: logits outside the causal region become -inf (weight 0), in place and ahead of the one epilogue
+// that every block runs - with an epilogue of its own for masked blocks the running values met on two paths, a register
+// copy for each of them in every block.
+template <int PASS>
+__device__ __forceinline__ void mask_block(f32x4 (&acc)[2][4], int xq, const int (&sP)[4])
+{
+#pragma unroll
+    for (int cg = 0; cg < 4; ++cg)
+#pragma unroll
+        for (int rg = 0; rg < 2; ++rg)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int x = xq + 16 * rg + i;
+                if (PASS == 1 ? x > sP[cg] : x < sP[cg]) acc[rg][cg][i] = -INFINITY;
+            }
+}
+
 //   PASS 2: running sums of 2^(c*(s - b_i)) over the query rows of the lane's four keys, b_i = lse2_i / c; the
 //           accumulators arrive with -b_i already in them (the MFMA chain starts from it instead of from zero),
 //           so no per-row value has to be held in registers here.
-template <bool MASK>
-__device__ __forceinline__ void colsum_block_epilogue(const f32x4 (&acc)[2][4], float scale2, int xq, const int (&sP)[4],
-                                                      float (&run)[4])
+__device__ __forceinline__ void colsum_block_epilogue(const f32x4 (&acc)[2][4], float scale2, float (&run)[4])
 {
 #pragma unroll
     for (int cg = 0; cg < 4; ++cg) {
@@ -56,12 +72,13 @@ __device__ __forceinline__ void colsum_block_epilogue(const f32x4 (&acc)[2][4], 
         for (int rg = 0; rg < 2; ++rg)
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                float p = __builtin_amdgcn_exp2f(acc[rg][cg][i] * scale2);
-                if (MASK && (xq + 16 * rg + i < sP[cg])) p = 0.f;   // query before the key
+                const float p = __builtin_amdgcn_exp2f(acc[rg][cg][i] * scale2);
                 sum = (rg == 0 && i == 0) ? p : sum + p;
             }
         run[cg] += sum;
     }
+#pragma unroll
+    for (int cg = 0; cg < 4; ++cg) asm volatile("" : "+v"(run[cg]));   // here, not sunk behind the next block's MFMAs
 }
 
 // Pass 1, a finished block (32 streamed keys against the lane's four query rows).
@@ -70,33 +87,23 @@ __device__ __forceinline__ void colsum_block_epilogue(const f32x4 (&acc)[2][4], 
 // binades above the reference) is the block maximum taken and the running sum rescaled.  The result is the same up
 // to rounding - a float sum keeps its relative precision at any magnitude below 2^64 - and the common case saves
 // the maximum over the block.  One wave-uniform test covers the whole block (a branch on a vector result drains the
-// wave's vector pipeline); the refresh is valid for a row that did not overflow as well.
-__device__ __forceinline__ void lse_refresh(const f32x4& lo, const f32x4& hi, float scale2, float& m, float& l)
+// wave's vector pipeline); the refresh is valid for a row that did not overflow as well.  A NaN needs no refresh: it
+// reaches the running sum either way.
+__device__ __forceinline__ void lse_refresh(const f32x4& lo, const f32x4& hi, float scale2, float& m, float& l, float& sum)
 {
     const float bm = fmaxf(fmaxf(fmaxf(fmaxf(lo[0], lo[1]), lo[2]), fmaxf(fmaxf(lo[3], hi[0]), hi[1])), fmaxf(hi[2], hi[3]));
     const float mn = fmaxf(m, bm * scale2);
-    float sum = 0.f;
+    sum = 0.f;
 #pragma unroll
     for (int i = 0; i < 4; ++i) sum += __builtin_amdgcn_exp2f(fmaf(lo[i], scale2, -mn));
 #pragma unroll
     for (int i = 0; i < 4; ++i) sum += __builtin_amdgcn_exp2f(fmaf(hi[i], scale2, -mn));
-    l = fmaf(l, __builtin_amdgcn_exp2f(m - mn), sum);
+    l *= __builtin_amdgcn_exp2f(m - mn);
     m = mn;
 }
 
-template <bool MASK>
-__device__ __forceinline__ void lse_block_epilogue(f32x4 (&acc)[2][4], float scale2, int xq, const int (&sP)[4],
-                                                   float (&m)[4], float (&l)[4])
+__device__ __forceinline__ void lse_block_epilogue(const f32x4 (&acc)[2][4], float scale2, float (&m)[4], float (&l)[4])
 {
-    if (MASK) {
-#pragma unroll
-        for (int cg = 0; cg < 4; ++cg)
-#pragma unroll
-            for (int rg = 0; rg < 2; ++rg)
-#pragma unroll
-                for (int i = 0; i < 4; ++i)
-                    if (xq + 16 * rg + i > sP[cg]) acc[rg][cg][i] = -INFINITY;   // key after the query
-    }
     float sum[4];
 #pragma unroll
     for (int cg = 0; cg < 4; ++cg) {
@@ -108,14 +115,13 @@ __device__ __forceinline__ void lse_block_epilogue(f32x4 (&acc)[2][4], float sca
                 sum[cg] = (rg == 0 && i == 0) ? p : sum[cg] + p;   // (0 + x is an addition the compiler may not drop)
             }
     }
-    const bool over = !(sum[0] <= 1.8e19f) || !(sum[1] <= 1.8e19f) || !(sum[2] <= 1.8e19f) || !(sum[3] <= 1.8e19f);
-    if (__builtin_expect(__any(over), 0)) {     // also true for NaN; wave-uniform
+    const float top = fmaxf(fmaxf(fmaxf(sum[0], sum[1]), sum[2]), sum[3]);
+    if (__builtin_expect(__any(top > 1.8e19f), 0)) {     // wave-uniform
 #pragma unroll
-        for (int cg = 0; cg < 4; ++cg) lse_refresh(acc[0][cg], acc[1][cg], scale2, m[cg], l[cg]);
-    } else {
-#pragma unroll
-        for (int cg = 0; cg < 4; ++cg) l[cg] += sum[cg];
+        for (int cg = 0; cg < 4; ++cg) lse_refresh(acc[0][cg], acc[1][cg], scale2, m[cg], l[cg], sum[cg]);
     }
+#pragma unroll
+    for (int cg = 0; cg < 4; ++cg) l[cg] += sum[cg];
 }
 
 // ---- work decomposition -------------------------------------------------------------------------------
@@ -332,19 +338,26 @@ k_score_mfma(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, int H, 
         }
     bf16x8 sf[4][4];
     {
-        // (Pass 1: a wave wholly past the end has zeros.  Under an observation window the last strip is all there is: a window of
-        // 64 in 12644 tokens, where two waves of four lie past the end, 40.1 -> 38.2 us.)
+        // Pass 1: a wave wholly past the end has zeros - a buffer of no bytes, which needs no memory.  (Under an observation
+        // window the last strip is all there is: a window of 64 in 12644 tokens, where two waves of four lie past the end,
+        // 40.1 -> 38.2 us.)
+        const auto srsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(S), 0, (PASS == 1 && w0 >= L) ? 0 : L * (SD * 2), 0x00020000);
         u32x4 rows[4][4];
+        auto load_rows = [&](auto&& offset) {     // offset(r): scalar and per-lane byte offset of row r (+ q4) of the wave
 #pragma unroll
-        for (int cg = 0; cg < 4; ++cg)
+            for (int cg = 0; cg < 4; ++cg)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                rows[cg][i] = u32x4{0, 0, 0, 0};
-                if (PASS == 1 && w0 >= L) continue;
-                int row = w0 + 16 * cg + 4 * i + q4;     // rows past the end repeat the last one: nothing reads their results
-                if (sparse) row = clist[min(row, max(NC, 1) - 1)];
-                rows[cg][i] = *reinterpret_cast<const u32x4*>(S + (size_t)min((unsigned)row, (unsigned)(L - 1)) * SD + c16 * 8);
-            }
+                for (int i = 0; i < 4; ++i) {
+                    const int2 o = offset(16 * cg + 4 * i);
+                    rows[cg][i] = __builtin_bit_cast(u32x4, __builtin_amdgcn_raw_buffer_load_b128(srsrc, o.y, o.x, 0));
+                }
+        };
+        if (sparse)                               // rows past the end of the list repeat its last one: nothing reads their results
+            load_rows([&](int r) { return make_int2(0, (int)min((unsigned)clist[min(w0 + r + q4, max(NC, 1) - 1)], (unsigned)(L - 1)) * (SD * 2) + c16 * 16); });
+        else if (s0 + BS <= L)                    // a whole strip: no arithmetic per row
+            load_rows([&](int r) { return make_int2((w0 + r) * (SD * 2), lane * 16); });
+        else                                      // rows past the end repeat the last one
+            load_rows([&](int r) { return make_int2(0, min(w0 + r + q4, L - 1) * (SD * 2) + c16 * 16); });
         bf16_t* mine = turn[wave];
         const bf16_t* theirs = mine + unknown_zero();
 #pragma unroll
@@ -360,51 +373,54 @@ k_score_mfma(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, int H, 
 
     const int n_it = idle ? 0 : (x_end - x_begin + BX - 1) / BX;
 
-    // Staging goes from global memory straight into LDS (global_load_lds_dwordx4): the 64 lanes of a wave
+    // Staging goes from global memory straight into LDS (buffer_load_dwordx4 lds): the 64 lanes of a wave
     // fill 1 KB = 4 consecutive LDS rows, lane l landing at chunk l%16 of row l/16, so the swizzle is applied
     // on the global side: the lane fetches chunk (l%16) ^ (row & 7) of its row.  Rows past the end re-read the
-    // last row (their contribution is masked out or weighted by 2^-inf).  No staging registers, no LDS stores.
+    // last row (their contribution is masked out or weighted by 2^-inf).  No staging registers, no LDS stores, and with
+    // a buffer descriptor no address arithmetic: a lane's offset inside a tile never changes, the rest is scalar.
+    // (32 heads x 12644, with one epilogue per block instead of a masked and a plain one, and in pass 2 the blocks written
+    // out instead of a loop over the two, in which a fragment read waited for the loads of the next tile: pass 1
+    // 599 -> 591 us, pass 2 530 -> 513 us, bit-identical; pass 2's vector instructions per block 119 -> 108.)
     constexpr int NLD = BX / 16;   // 1 KB pieces per wave and tile
     float stage_l = 0.f;
-    // byte offset of this lane's 16 bytes inside a tile: row (wave*4 + ld_sub) of the first 1 KB piece, swizzled chunk
+    // byte offset of this lane's 16 bytes inside a tile: row (wave*4 + lane/16) of the first 1 KB piece, swizzled chunk
     // (the 16 rows between two pieces do not change row & 7)
-    // (pass 1 works it out again for every tile - six instructions - instead of holding it: with its registers all
-    // taken the compiler otherwise parks it in scratch memory and waits for the reload at the top of every tile)
-    auto lane_offset = [&]() {
-        int t = lane;
-        if (PASS == 1) {   // the lane number afresh (two instructions), so that no register has to hold it meanwhile
-            t = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
-            asm volatile("" : "+v"(t));
-        }
-        const int sub = t >> 4, pos = t & 15;
-        return (uint32_t)((wave * 4 + sub) * (SD * 2) + ((pos ^ ((wave * 4 + sub) & 7)) * 16));
+    // The lane number afresh (two instructions), where values derived from it are needed once in a while: no register has
+    // to hold them meanwhile.  With the registers all taken the compiler otherwise parks them in scratch memory, and every
+    // reload waits for the tile loads in flight.
+    auto lane_again = [&]() {
+        int t = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        asm volatile("" : "+v"(t));
+        return t;
     };
-    const char* Xb = reinterpret_cast<const char*>(X);
+    const auto xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<bf16_t*>(X), 0, L * (SD * 2), 0x00020000);
+    auto lane_offset = [&](int t) {
+        const int row = wave * 4 + (t >> 4);
+        return row * (SD * 2) + ((t & 15) ^ (row & 7)) * 16;
+    };
+    const int lane_off = lane_offset(lane);
     auto load_tile = [&](int x0, bf16_t* xsb) {
-        const uint32_t lane_off = lane_offset();
         if (x0 + BX <= L) {          // scalar test: a whole tile inside the tensor needs no clamping
-            const uint32_t o = (uint32_t)x0 * (SD * 2) + lane_off;
+            const int o = (PASS == 1) ? lane_offset(lane_again()) : lane_off;
 #pragma unroll
             for (int i = 0; i < NLD; ++i)
-                __builtin_amdgcn_global_load_lds(
-                    (const __attribute__((address_space(1))) void*)(Xb + (o + (uint32_t)i * 16 * SD * 2)),
-                    (__attribute__((address_space(3))) void*)&xsb[(i * 4 + wave) * 4 * XROW], 16, 0, 0);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    xrsrc, (__attribute__((address_space(3))) void*)&xsb[(i * 4 + wave) * 4 * XROW], 16, o,
+                    x0 * (SD * 2) + i * 16 * SD * 2, 0, 0);
         } else {                     // the tensor's last tile: rows past the end re-read the last row
-            const int lane_row = (int)(lane_off >> 8), lane_chunk = (int)(lane_off & 255);   // SD * 2 = 256 bytes per row
+            const int o = lane_offset(lane_again()), row = o >> 8, chunk = o & 255;   // SD * 2 = 256 bytes per row
 #pragma unroll
-            for (int i = 0; i < NLD; ++i) {
-                const uint32_t o = (uint32_t)min(x0 + i * 16 + lane_row, L - 1) * (SD * 2) + lane_chunk;
-                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(Xb + o),
-                                                 (__attribute__((address_space(3))) void*)&xsb[(i * 4 + wave) * 4 * XROW],
-                                                 16, 0, 0);
-            }
+            for (int i = 0; i < NLD; ++i)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    xrsrc, (__attribute__((address_space(3))) void*)&xsb[(i * 4 + wave) * 4 * XROW], 16,
+                    min(x0 + i * 16 + row, L - 1) * (SD * 2) + chunk, 0, 0, 0);
         }
         // Pass 2 also needs lse2 of the tile's rows: wave 0 (threads 0 .. BX-1, a scalar test) loads one value per
         // lane here, unconditionally (rows outside the tensor read its last row), and store_tile puts it into LDS at
         // the end of the previous tile.  Nothing may touch the loaded value before that: a use right after the load
         // would make the wave wait for everything it has just issued, the tile's rows included - hence the empty asm
         // in store_tile, which keeps the compiler from moving the arithmetic up here.
-        if (PASS == 2 && wave == 0) stage_l = lse_h[min(x0 + tid, L - 1)];
+        if (PASS == 2 && wave == 0) stage_l = lse_h[min(x0 + lane_again(), L - 1)];
     };
     // x0: first row of the tile that was loaded.  Value stored: -lse2_i / c (the start of the MFMA chains of pass 2);
     // rows outside [R0, L) get -inf and contribute nothing.
@@ -412,7 +428,8 @@ k_score_mfma(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, int H, 
         if (PASS == 2 && wave == 0) {
             float v = stage_l;
             asm volatile("" : "+v"(v));
-            xlb[tid] = (x0 + tid < L && x0 + tid >= R0) ? -v * lse_scale : -INFINITY;
+            const int t = lane_again();
+            xlb[t] = (x0 + t < L && x0 + t >= R0) ? -v * lse_scale : -INFINITY;
         }
     };
 
@@ -492,25 +509,17 @@ k_score_mfma(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, int H, 
         fetch_group(tile_rows, rb, 0);
         fetch_group(tile_rows, rb, 1);
     };
-    // pass 1 (its epilogue keeps twice the state of pass 2's and needs registers to work in): the fragments of the
-    // first two MFMA steps before the epilogue, those of the last two - needed after sixteen MFMAs - after it
-    auto fetch_early = [&](const bf16_t* tile_rows, int rb) {
+    // pass 2: what the MFMA chains of a block start from, -lse2_i / c of the lane's streamed rows, fetched with the fragments
+    f32x4 init[2];
+    auto fetch_init = [&](const float* tile_l, int rb) {
 #pragma unroll
-        for (int rg = 0; rg < 2; ++rg) {
-            const bf16_t* ap = &tile_rows[(rb * 32 + 16 * rg + c16) * XROW];
-            a[rg][0] = as_bf16x8(*reinterpret_cast<const uint4*>(ap + frag_off[0]));
-            a[rg][1] = as_bf16x8(*reinterpret_cast<const uint4*>(ap + frag_off[1]));
-        }
+        for (int rg = 0; rg < 2; ++rg)
+            init[rg] = __builtin_bit_cast(f32x4, *reinterpret_cast<const float4*>(&tile_l[rb * 32 + 16 * rg + 4 * q4]));
     };
-    auto fetch_late = [&](const bf16_t* tile_rows, int rb) {
-#pragma unroll
-        for (int rg = 0; rg < 2; ++rg) {
-            const bf16_t* ap = &tile_rows[(rb * 32 + 16 * rg + c16) * XROW];
-            a[rg][2] = as_bf16x8(*reinterpret_cast<const uint4*>(ap + frag_off[0] + 64));
-            a[rg][3] = as_bf16x8(*reinterpret_cast<const uint4*>(ap + frag_off[1] + 64));
-        }
-    };
-    if (n_it > 0) fetch(xs0, 0);
+    if (n_it > 0) {
+        fetch(xs0, 0);
+        if (PASS == 2) fetch_init(xl0, 0);
+    }
 
     // One tile, with its LDS buffer known at compile time.  Tiles that touch the diagonal evaluate the causal
     // condition per element in their epilogues; tiles known to lie entirely inside the causal region run the same
@@ -531,14 +540,13 @@ k_score_mfma(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, int H, 
 
         // End of the tile's LDS reads: wait for the next tile's loads, meet the other waves, and fetch the next
         // tile's first fragments - before the epilogue of this tile's second block, which hides their latency.
-        // (pass 1 fetches only the first row group here and the second after the epilogue: see below)
-        auto finish_tile = [&](bool all_fragments) {
+        auto finish_tile = [&]() {
             if (it + 1 < n_it) store_tile(nxt_l, x0 + BX);
             __builtin_amdgcn_s_waitcnt(0x0F70);   // vmcnt(0): the next tile's direct-to-LDS loads have landed
             __syncthreads();
             // unconditional: after the last tile this reads an old tile and the values are never used
-            if (all_fragments) fetch(nxt, 0);
-            else fetch_early(nxt, 0);
+            fetch(nxt, 0);
+            if (PASS == 2) fetch_init(nxt_l, 0);
         };
         if (!skip) {
             // Two blocks of 32 streamed rows; the fragments of block 0 are in `a` already (fetched by the previous
@@ -547,89 +555,45 @@ k_score_mfma(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, int H, 
             // epilogue.  The scheduling barriers keep the compiler from undoing the order, and from holding more
             // than one block's values at a time: the kernel has to stay within 168 VGPRs.
             f32x4 acc[2][4];
-            // the MFMA chains of a block start from zero in pass 1 and from -lse2_i / c of the lane's streamed rows
-            // (two 16-byte LDS reads; every chain's first MFMA takes them as its C operand) in pass 2
-            auto multiply = [&](int rb) {
-                if (PASS == 1) {
-                    // step by step over all eight tiles, so that a tile's next MFMA is eight instructions away; the
-                    // fragments of the last step were asked for after the previous epilogue and land meanwhile
-                    const f32x4 zero = {0.f, 0.f, 0.f, 0.f};   // an inline constant of the instruction, no registers
+            // the MFMA chains of a block start from zero in pass 1 and from -lse2_i / c of the lane's streamed rows in pass 2;
+            // step by step over all eight tiles, so that a tile's next MFMA is eight instructions away
+            auto multiply = [&]() {
+                const f32x4 zero = {0.f, 0.f, 0.f, 0.f};   // an inline constant of the instruction, no registers
+#pragma unroll
+                for (int ks = 0; ks < 4; ++ks)
 #pragma unroll
                     for (int cg = 0; cg < 4; ++cg)
 #pragma unroll
                         for (int rg = 0; rg < 2; ++rg)
-                            acc[rg][cg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rg][0], sf[cg][0], zero, 0, 0, 0);
-#pragma unroll
-                    for (int ks = 1; ks < 4; ++ks)
-#pragma unroll
-                        for (int cg = 0; cg < 4; ++cg)
-#pragma unroll
-                            for (int rg = 0; rg < 2; ++rg)
-                                acc[rg][cg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rg][ks], sf[cg][ks], acc[rg][cg], 0, 0, 0);
-                } else {
-#pragma unroll
-                    for (int rg = 0; rg < 2; ++rg) {
-                        const float4 v = *reinterpret_cast<const float4*>(&cur_l[rb * 32 + 16 * rg + 4 * q4]);
-                        const f32x4 init = {v.x, v.y, v.z, v.w};
-#pragma unroll
-                        for (int cg = 0; cg < 4; ++cg)
-                            acc[rg][cg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rg][0], sf[cg][0], init, 0, 0, 0);
-                    }
-#pragma unroll
-                    for (int ks = 1; ks < 4; ++ks)
-#pragma unroll
-                        for (int cg = 0; cg < 4; ++cg)
-#pragma unroll
-                            for (int rg = 0; rg < 2; ++rg)
-                                acc[rg][cg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rg][ks], sf[cg][ks], acc[rg][cg], 0, 0, 0);
-                }
+                            acc[rg][cg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                a[rg][ks], sf[cg][ks], ks > 0 ? acc[rg][cg] : PASS == 1 ? zero : init[rg], 0, 0, 0);
             };
             auto epilogue = [&](int rb) {
-                const int xq = x0 + rb * 32 + 4 * q4;   // streamed index of entry i of acc[rg][.]: xq + 16*rg + i
-                if (mask) {      // a scalar branch; both sides leave the prefetched fragments alone
-                    const int sP[4] = {stationary_pos(0), stationary_pos(1), stationary_pos(2), stationary_pos(3)};
-                    if (PASS == 1) lse_block_epilogue<true>(acc, scale2, xq, sP, m, l);
-                    else colsum_block_epilogue<true>(acc, scale2, xq, sP, run);
-                } else {
-                    const int sP[4] = {0, 0, 0, 0};
-                    if (PASS == 1) lse_block_epilogue<false>(acc, scale2, xq, sP, m, l);
-                    else colsum_block_epilogue<false>(acc, scale2, xq, sP, run);
+                if (mask) {      // a scalar branch
+                    const int t = lane_again();
+                    int sP[4];
+#pragma unroll
+                    for (int cg = 0; cg < 4; ++cg) sP[cg] = sparse ? spos[cg * 256 + wave * 64 + t] : w0 + 16 * cg + (t & 15);
+                    mask_block<PASS>(acc, x0 + rb * 32 + 4 * (t >> 4), sP);   // streamed index of entry i of acc[rg][.]: + 16*rg + i
                 }
+                if (PASS == 1) lse_block_epilogue(acc, scale2, m, l);
+                else colsum_block_epilogue(acc, scale2, run);
             };
-            // The two blocks as a loop: unrolled, neither pass fits into 168 VGPRs.  Pass 1, whose epilogue keeps
-            // twice the state of pass 2's, holds only HALF of the next block's fragments (row group 0) during the
-            // epilogue and asks for the other half after it.
-            if (PASS == 1) {
-                multiply(0);
-                __builtin_amdgcn_sched_barrier(0);
-                fetch_early(cur, 1);
-                __builtin_amdgcn_sched_barrier(0);
-                epilogue(0);
-                __builtin_amdgcn_sched_barrier(0);
-                fetch_late(cur, 1);
-                __builtin_amdgcn_sched_barrier(0);
-                multiply(1);
-                __builtin_amdgcn_sched_barrier(0);
-                finish_tile(false);
-                __builtin_amdgcn_sched_barrier(0);
-                epilogue(1);
-                __builtin_amdgcn_sched_barrier(0);
-                fetch_late(nxt, 0);
-                __builtin_amdgcn_sched_barrier(0);
-            } else {
-#pragma unroll 1
-                for (int rb = 0; rb < BX / 32; ++rb) {
-                    multiply(rb);
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (rb == 0) fetch(cur, 1);
-                    else finish_tile(true);
-                    __builtin_amdgcn_sched_barrier(0);
-                    epilogue(rb);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
+            multiply();
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(cur, 1);
+            if (PASS == 2) fetch_init(cur_l, 1);
+            __builtin_amdgcn_sched_barrier(0);
+            epilogue(0);
+            __builtin_amdgcn_sched_barrier(0);
+            multiply();
+            __builtin_amdgcn_sched_barrier(0);
+            finish_tile();
+            __builtin_amdgcn_sched_barrier(0);
+            epilogue(1);
+            __builtin_amdgcn_sched_barrier(0);
         } else {
-            finish_tile(true);
+            finish_tile();
         }
     };
     for (int it = 0; it < n_it; it += 2) {
@@ -647,23 +611,17 @@ k_score_mfma(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, int H, 
         if (PASS == 1) {
             float mm = m[cg], ll = l[cg];
 #pragma unroll
-            for (int step = 16; step <= 32; step <<= 1) {
-                const bool upper = (lane & step) != 0;
+            for (int step = 16; step <= 32; step <<= 1) {     // (only the lower lane of a pair is read from here on)
                 const float mo = __shfl_xor(mm, step), lo = __shfl_xor(ll, step);
                 const float M = fmaxf(mm, mo);
-                const float la = upper ? lo : ll, ma = upper ? mo : mm;   // the lower lane's values first
-                const float lb = upper ? ll : lo, mb = upper ? mm : mo;
-                ll = la * __builtin_amdgcn_exp2f(ma - M) + lb * __builtin_amdgcn_exp2f(mb - M);
+                ll = ll * __builtin_amdgcn_exp2f(mm - M) + lo * __builtin_amdgcn_exp2f(mo - M);
                 mm = M;
             }
             if (q4 == 0) { pa[r] = mm; pb[r] = ll; }
         } else {
             float v = run[cg];
 #pragma unroll
-            for (int step = 16; step <= 32; step <<= 1) {
-                const float other = __shfl_xor(v, step);
-                v = (lane & step) ? other + v : v + other;
-            }
+            for (int step = 16; step <= 32; step <<= 1) v += __shfl_xor(v, step);
             if (q4 == 0) pa[r] = v;
         }
     }
