@@ -14,10 +14,14 @@
 // enough workgroups, and nothing is written but the result.
 //
 // What bounds it: fp32 - the fp32 matrix instruction (64 flop per cycle and SIMD, and the vector ALU stands still
-// meanwhile: the co-execution counter reads zero; the matrix pipe is busy 62 % of the time); bf16 - the vector ALU, busy
-// 86 % of the time in pass 1 and 77 % in pass 2 with an exponential and its two companions per logit.  Both passes over
-// 16 heads x 1483 x 128 fp32: 128 us (74 TFLOP/s; on the vector ALU, with 64 x 64 tiles in LDS: 685 us); over
-// 32 x 2781 x 64 bf16: 66 us (790 us); over 2 x 256 x 64 fp32: 10 us (64 us).
+// meanwhile: the co-execution counter reads zero; the matrix pipe is busy 68 % of the time a compute unit has work, the
+// longest strips run alone for the last fifth); bf16 - the vector ALU, busy 83 % of the time in pass 1 and 77 % in pass 2
+// with an exponential and its two companions per logit.  Both passes over 16 heads x 1483 x 128 fp32: 105 us
+// (on the vector ALU, with 64 x 64 tiles in LDS: 685 us); over 32 x 2781 x 64 bf16: 55 us (790 us); over
+// 2 x 256 x 64 fp32: 10 us (64 us).  Stationary rows through LDS, blocks through a buffer descriptor, log-sum-exps
+// straight to LDS, the first block of a wave without a sum against a reference that it has not got: 121 and 62 us before.
+// (Tried: every other 32 workgroups of an XCD in the opposite order, so that long strips meet short ones: 2 us slower;
+// fp32 blocks of 16 rows, three workgroups a compute unit instead of two: pass 1 52 -> 56 us, all strips start at once.)
 #include "frag.h"
 
 #include <algorithm>
@@ -28,12 +32,12 @@ namespace lookm {
 constexpr int SA_WAVES = 4;
 
 // sum over a block of 32 streamed keys against the reference of each row; a row whose sum overflows gets a new
-// reference (see score_mfma.hip)
+// reference, and a NaN reaches the sum either way (see score_mfma.hip)
 template <int CG>
-__device__ __forceinline__ void lse_update(const acc_t (&acc)[2][CG], float scale2, float (&m)[CG], float (&l)[CG])
+__device__ __forceinline__ void lse_update(const acc_t (&acc)[2][CG], float scale2, float (&m)[CG], float (&l)[CG], bool first)
 {
-    float sum[CG];
-    bool over = false;
+    float sum[CG], top = INFINITY;
+    if (!first)             // (scalar; a wave's first block has no reference yet)
 #pragma unroll
     for (int cg = 0; cg < CG; ++cg) {
 #pragma unroll
@@ -43,25 +47,24 @@ __device__ __forceinline__ void lse_update(const acc_t (&acc)[2][CG], float scal
                 const float p = __builtin_amdgcn_exp2f(fmaf(acc[rg][cg][i], scale2, -m[cg]));
                 sum[cg] = (rg == 0 && i == 0) ? p : sum[cg] + p;
             }
-        over = over || !(sum[cg] <= 1.8e19f);
+        top = (cg == 0) ? sum[cg] : fmaxf(top, sum[cg]);
     }
-    if (__builtin_expect(__any(over), 0)) {
+    if (__builtin_expect(__any(top > 1.8e19f), 0)) {
 #pragma unroll
         for (int cg = 0; cg < CG; ++cg) {
             float bm = acc[0][cg][0];
 #pragma unroll
             for (int i = 1; i < 8; ++i) bm = fmaxf(bm, acc[i >> 2][cg][i & 3]);
             const float mn = fmaxf(m[cg], bm * scale2);
-            float s = 0.f;
+            sum[cg] = 0.f;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) s += __builtin_amdgcn_exp2f(fmaf(acc[i >> 2][cg][i & 3], scale2, -mn));
-            l[cg] = fmaf(l[cg], __builtin_amdgcn_exp2f(m[cg] - mn), s);
+            for (int i = 0; i < 8; ++i) sum[cg] += __builtin_amdgcn_exp2f(fmaf(acc[i >> 2][cg][i & 3], scale2, -mn));
+            l[cg] *= __builtin_amdgcn_exp2f(m[cg] - mn);
             m[cg] = mn;
         }
-    } else {
-#pragma unroll
-        for (int cg = 0; cg < CG; ++cg) l[cg] += sum[cg];
     }
+#pragma unroll
+    for (int cg = 0; cg < CG; ++cg) l[cg] += sum[cg];
 }
 
 // This thread's share of the sums over FEW keys of one query head, rows thread, thread + 256, ... from each key on: dots in
@@ -107,6 +110,7 @@ k_score_any(const T* __restrict__ q, const T* __restrict__ k, int heads, int gro
     constexpr int SR = 16 * CG;                      // stationary rows
     __shared__ float fold_a[SA_WAVES][SR], fold_b[PASS == 1 ? SA_WAVES : 1][SR];
     __shared__ __attribute__((aligned(1024))) char blocks[SA_WAVES][FRAG_BLOCK * frag_row_bytes<KS>()];
+    __shared__ __attribute__((aligned(256))) float refs[PASS == 2 ? SA_WAVES : 1][64];
     const unsigned unit = wide_block();
     if (unit >= n_units) {
         inverse_norms(k, norm_rows, d, unit - n_units, rnorm);
@@ -131,10 +135,23 @@ k_score_any(const T* __restrict__ q, const T* __restrict__ k, int heads, int gro
     char* block = blocks[wave];                     // this wave's streamed block
 
     const T* S = (PASS == 1) ? q + (size_t)h * L * d : k + (size_t)h * L * d;
+    int off[frag_row_kinds<KS>()];
+    frag_row_offsets<T, KS>(d, lane, off);
+    // Stationary rows: every wave needs all of them, so each loads a quarter of the strip - into the buffers that the
+    // streamed blocks take afterwards - and reads all of it.  (Fragments straight from global memory touch sixteen cache
+    // lines for 1 KB: 3 us of a compute unit's L1 for its 128 KB.)
     frag_t sf[CG][KS];
+    {
+        constexpr int RB = frag_row_bytes<KS>(), PART = (RB == 64) ? 16 : (CG == 4) ? 16 : 8;     // rows a wave loads: 1 KB at least, whole swizzle patterns
+        const auto srsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(S), 0, L * d * (int)sizeof(T), 0x00020000);
+        if (wave * PART < SR)
+            frag_load_rows<T, KS, PART>(srsrc, d, &blocks[0][0] + wave * PART * RB, lane, off, min(s0 + wave * PART, L - 1), L - min(s0 + wave * PART, L - 1));
+        frag_wait_loads();
+        __syncthreads();
 #pragma unroll
-    for (int cg = 0; cg < CG; ++cg)
-        frag_stationary<T, KS>(S + (size_t)min(s0 + 16 * cg + c16, L - 1) * d, q4, d, sf[cg]);
+        for (int cg = 0; cg < CG; ++cg) frag_read<T, KS>(&blocks[0][0], cg, c16, q4, d, sf[cg]);
+        __syncthreads();
+    }
 
     float m[CG], l[CG];                              // pass 1: reference and sum per stationary row; pass 2: l only
 #pragma unroll
@@ -147,14 +164,15 @@ k_score_any(const T* __restrict__ q, const T* __restrict__ k, int heads, int gro
     for (int g = 0; g < n_heads; ++g) {
         const T* X = (PASS == 1) ? k + (size_t)(h / group) * L * d : q + ((size_t)h * group + g) * L * d;
         const float* lse_h = lse2 + ((size_t)h * group + g) * L;        // pass 2
+        const auto xrsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(X), 0, L * d * (int)sizeof(T), 0x00020000);
         frag_t a[2][KS];
-        float ref[2];                                                  // pass 2: log-sum-exp of streamed row c16
         auto fetch = [&](int b) {
-            const uint32_t row_bytes = (uint32_t)(d * sizeof(T));
-            if (PASS == 2)
-#pragma unroll
-                for (int rg = 0; rg < 2; ++rg) ref[rg] = lse_h[min(b * 32 + 16 * rg + c16, L - 1)];
-            frag_load_block<T, KS>(X, d, block, lane, [&](int, int r) { return (uint32_t)min(b * 32 + r, L - 1) * row_bytes; });
+            if (PASS == 2) {                                           // log-sum-exp of the block's rows (and of 32 more)
+                const int row = (b * 32 + 64 <= L) ? b * 32 + lane : min(b * 32 + lane, L - 1);
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(lse_h + row),
+                                                 (__attribute__((address_space(3))) void*)refs[PASS == 2 ? wave : 0], 4, 0, 0);
+            }
+            frag_load_rows<T, KS, FRAG_BLOCK>(xrsrc, d, block, lane, off, b * 32, L - b * 32);
         };
         if (b0 < b_end) fetch(b0);
         for (int b = b0; b < b_end; b += SA_WAVES) {
@@ -162,14 +180,15 @@ k_score_any(const T* __restrict__ q, const T* __restrict__ k, int heads, int gro
             asm volatile("" ::: "memory");
 #pragma unroll
             for (int rg = 0; rg < 2; ++rg) frag_read<T, KS>(block, rg, c16, q4, d, a[rg]);
-            float neg[2][4];
+            float neg[2][4];                         // pass 2: -log-sum-exp of the lane's eight streamed rows
             if (PASS == 2)
 #pragma unroll
                 for (int rg = 0; rg < 2; ++rg) {
-                    const int row = b * 32 + 16 * rg + c16;
-                    const float v = (row < L) ? -ref[rg] * lse_scale : -INFINITY;      // (past the end: row L-1 again, weight 0)
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) neg[rg][i] = __shfl(v, 4 * q4 + i);
+                    const float4 v = *reinterpret_cast<const float4*>(&refs[PASS == 2 ? wave : 0][16 * rg + 4 * q4]);
+                    neg[rg][0] = -v.x * lse_scale;
+                    neg[rg][1] = -v.y * lse_scale;
+                    neg[rg][2] = -v.z * lse_scale;
+                    neg[rg][3] = -v.w * lse_scale;
                 }
             // the block is in registers: the next one's rows may take its place in LDS
             __builtin_amdgcn_s_waitcnt(0xC07F);      // lgkmcnt(0): the fragments have arrived
@@ -200,28 +219,37 @@ k_score_any(const T* __restrict__ q, const T* __restrict__ k, int heads, int gro
                             for (int i = 0; i < 4; ++i)
                                 if (xq + 16 * rg + i > s0 + 16 * cg + c16) acc[rg][cg][i] = -INFINITY;   // key after the query
                 }
-                lse_update<CG>(acc, scale2, m, l);
+                lse_update<CG>(acc, scale2, m, l, b == b0);
             } else {
-                // masked: terms of rows before the key, and before the observation window, are not added at all (as -inf
-                // in the exponent they would still meet the row's log-sum-exp, which may be infinite or NaN)
-                auto add = [&](auto masked) {
+                // masked: terms of rows before the key, before the observation window and past the end are not added at all (as
+                // -inf in the exponent they would still meet the row's log-sum-exp, which may be infinite or NaN)
+                const bool masked = b * 32 < max(s0 + SR - 1, R0) || b * 32 + 32 > L;       // scalar
+                float p[2][CG][4];
 #pragma unroll
-                    for (int cg = 0; cg < CG; ++cg) {
-                        const int first = max(s0 + 16 * cg + c16, R0);
-                        float sum = 0.f;
+                for (int cg = 0; cg < CG; ++cg)
+#pragma unroll
+                    for (int rg = 0; rg < 2; ++rg)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) p[rg][cg][i] = __builtin_amdgcn_exp2f(fmaf(acc[rg][cg][i], scale2, neg[rg][i]));
+                if (masked)
+#pragma unroll
+                    for (int cg = 0; cg < CG; ++cg)
 #pragma unroll
                         for (int rg = 0; rg < 2; ++rg)
 #pragma unroll
                             for (int i = 0; i < 4; ++i) {
-                                float p = __builtin_amdgcn_exp2f(fmaf(acc[rg][cg][i], scale2, neg[rg][i]));
-                                if (masked.value && xq + 16 * rg + i < first) p = 0.f;
-                                sum = (rg == 0 && i == 0) ? p : sum + p;
+                                const int x = xq + 16 * rg + i;
+                                if (x < max(s0 + 16 * cg + c16, R0) || x >= L) p[rg][cg][i] = 0.f;
                             }
-                        l[cg] += sum;
-                    }
-                };
-                if (b * 32 < max(s0 + SR - 1, R0)) add(std::true_type{});
-                else add(std::false_type{});
+#pragma unroll
+                for (int cg = 0; cg < CG; ++cg) {
+                    float sum = 0.f;
+#pragma unroll
+                    for (int rg = 0; rg < 2; ++rg)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) sum = (rg == 0 && i == 0) ? p[rg][cg][i] : sum + p[rg][cg][i];
+                    l[cg] += sum;
+                }
             }
         }
     }
@@ -230,17 +258,14 @@ k_score_any(const T* __restrict__ q, const T* __restrict__ k, int heads, int gro
 #pragma unroll
     for (int cg = 0; cg < CG; ++cg) {
 #pragma unroll
-        for (int step = 16; step <= 32; step <<= 1) {
-            const bool upper = (lane & step) != 0;
+        for (int step = 16; step <= 32; step <<= 1) {          // (only the lower lane of a pair is read from here on)
             const float lo = __shfl_xor(l[cg], step);
             if (PASS == 1) {
                 const float mo = __shfl_xor(m[cg], step), M = fmaxf(m[cg], mo);
-                const float la = upper ? lo : l[cg], ma = upper ? mo : m[cg];
-                const float lb = upper ? l[cg] : lo, mb = upper ? m[cg] : mo;
-                l[cg] = la * __builtin_amdgcn_exp2f(ma - M) + lb * __builtin_amdgcn_exp2f(mb - M);
+                l[cg] = l[cg] * __builtin_amdgcn_exp2f(m[cg] - M) + lo * __builtin_amdgcn_exp2f(mo - M);
                 m[cg] = M;
             } else {
-                l[cg] = upper ? lo + l[cg] : l[cg] + lo;
+                l[cg] += lo;
             }
         }
         if (q4 == 0) {

@@ -41,6 +41,23 @@ def test_scores_and_matching_at_every_head_width(H, L, d, dtype):
     assert sum(parity.check_nearest(kf[h], kept[h], ev[h], a[h], sim[h]) for h in heads) == 0   # rows in the tie band
 
 
+@pytest.mark.parametrize("H", [1, 16])                  # strips of 16 rows; of 64 and 32 rows
+@pytest.mark.parametrize("d,dtype", [(16, BF), (64, BF), (96, BF), (256, BF), (8, F32), (64, F32), (128, F32), (200, F32)])
+def test_scores_of_prompts_that_end_inside_a_strip(H, d, dtype):
+    """Prompts around the pieces that a strip's rows and a block's rows are loaded in (4 to 16 rows a wave): rows past the end
+    repeat the last one.  fp32 logits are off by at most sqrt(d) 2^-24 |q||k| / sqrt(d), twice that in an exponential (3e-5)."""
+    extra = 270 if H > 1 else 0
+    for L in [extra + n for n in (1, 2, 7, 8, 9, 15, 17, 31, 32, 33, 63, 64, 65, 97)]:
+        g = torch.Generator().manual_seed(1000 * d + L)
+        q, k = torch.randn(H, L, d, generator=g).to(dtype), torch.randn(H, L, d, generator=g).to(dtype)
+        got = lookm.lookm_scores(q.cuda(), k.cuda()).cpu().numpy().astype(np.float64)
+        heads = [0, H - 1]
+        np.testing.assert_allclose(got[heads], oracle.scores(q[heads].contiguous(), k[heads].contiguous()), rtol=3e-5, err_msg=str(L))
+        lse = torch.from_numpy(oracle.row_lse(q, k)).float().cuda()
+        own = lookm.lookm_scores_lse(q.cuda(), k.cuda(), lse).cpu().numpy()
+        np.testing.assert_allclose(own, got, rtol=3e-5, err_msg=str(L))
+
+
 @pytest.mark.parametrize("H,kvh,L,d,dtype,window", [(6, 2, 150, 80, BF, 45), (16, 8, 700, 64, BF, 333), (8, 2, 210, 40, F32, 1)])
 def test_grouped_heads_windows_and_supplied_lse(H, kvh, L, d, dtype, window):
     g = torch.Generator().manual_seed(d)
