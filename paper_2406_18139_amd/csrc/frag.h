@@ -7,7 +7,7 @@
 // stored in, the same one for both operands).  Products of bf16 pairs are exact and fp32 ones are fused
 // multiply-adds; both accumulate in fp32.
 //
-// Stationary rows are read once, straight into registers.  Streamed rows pass through LDS: lanes of equal q hold
+// All rows pass through LDS on their way to registers: lanes of equal q hold
 // different rows, so a fragment read from global memory touches 16 cache lines for 1 KB and runs at a quarter of the
 // L1 rate (measured: scores of 32 heads x 2781 x 64 bf16, 44 us a pass; with 32 stationary rows per wave instead of
 // 64, i.e. twice the loads, 66 us).  A wave copies its block of 32 rows with coalesced direct-to-LDS loads into a
@@ -56,13 +56,13 @@ __device__ __forceinline__ int frag_swizzle(int chunk, int r)
     return frag_row_bytes<KS>() >= 128 ? chunk ^ (r & 7) : chunk ^ ((r >> 1) & 3);
 }
 
-// Copies a block of 32 rows to LDS: 1 KB per instruction, lane l of instruction n filling the 16 bytes number 64n + l.
+// Copies ROWS rows to LDS: 1 KB per instruction, lane l of instruction n filling the 16 bytes number 64n + l.
 // row_of(r) gives the byte offset of the block's row r from `base` (below 2^32).  The chunks of a padded row that lie
 // past the end of the head width repeat its first one; frag_read puts zeros there.
-template <typename T, int KS, typename RowOf>
+template <typename T, int KS, int ROWS, typename RowOf>
 __device__ __forceinline__ void frag_load_block(const T* __restrict__ base, int d, void* lds, int lane, RowOf&& row_of)
 {
-    constexpr int RB = frag_row_bytes<KS>(), CH = RB / 16, NI = FRAG_BLOCK * RB / 1024;
+    constexpr int RB = frag_row_bytes<KS>(), CH = RB / 16, NI = ROWS * RB / 1024;
     const char* b = reinterpret_cast<const char*>(base);
     const int chunks = d * (int)sizeof(T) / 16;
 #pragma unroll
@@ -127,16 +127,8 @@ __device__ __forceinline__ void frag_read(const void* lds, int rg, int c16, int 
             if ((ks * 4 + q4) * frag<T>::WIDTH >= d) a[ks] = typename frag<T>::type{};
     }
 }
-template <typename T, int KS>
-__device__ __forceinline__ void frag_stationary(const T* __restrict__ row, int q4, int d, typename frag<T>::type (&b)[KS])
-{
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-        const int at = (ks * 4 + q4) * frag<T>::WIDTH;
-        b[ks] = *reinterpret_cast<const typename frag<T>::type*>(row + (at < d ? at : 0));
-        if (at >= d) b[ks] = typename frag<T>::type{};
-    }
-}
+// Rows of a strip of 16 * CG stationary rows that a wave loads: a quarter, but 1 KB at least and whole patterns of the swizzle.
+template <int KS, int CG> constexpr int frag_strip_part() { return (frag_row_bytes<KS>() == 64 || CG == 4) ? 16 : 8; }
 // Everything a wave has asked for has arrived: direct-to-LDS loads are not tracked by the compiler.
 __device__ __forceinline__ void frag_wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }     // vmcnt(0)
 

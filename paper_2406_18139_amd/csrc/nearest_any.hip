@@ -89,19 +89,29 @@ k_nearest_any(const T* __restrict__ k, const float* __restrict__ rnorm, const in
 
     const int n_blocks = (B + 31) / 32;
     char* block = blocks[wave];                      // this wave's conserved rows
-    frag_t sf[CG][KS];
-#pragma unroll
-    for (int cg = 0; cg < CG; ++cg)
-        frag_stationary<T, KS>(k + (size_t)evicted[min(e0 + 16 * cg + c16, Le - 1)] * d, q4, d, sf[cg]);
-
     // lane r % 32 holds the position of row r of the block that is fetched next, and the inverse norm of the one in flight
     int pos_next = kept[min(wave * 32 + (lane & 31), B - 1)];
+    // Evicted rows: every wave needs all of the strip, loads a quarter into the block buffers and reads all of it.
+    frag_t sf[CG][KS];
+    {
+        constexpr int RB = frag_row_bytes<KS>(), PART = frag_strip_part<KS, CG>();
+        if (wave * PART < SR) {
+            const int mine = evicted[min(e0 + wave * PART + (lane & (PART - 1)), Le - 1)];
+            frag_load_block<T, KS, PART>(k, d, &blocks[0][0] + wave * PART * RB, lane,
+                                         [&](int, int r) { return (uint32_t)__shfl(mine, r) * (uint32_t)(d * sizeof(T)); });
+        }
+        frag_wait_loads();
+        __syncthreads();
+#pragma unroll
+        for (int cg = 0; cg < CG; ++cg) frag_read<T, KS>(&blocks[0][0], cg, c16, q4, d, sf[cg]);
+        __syncthreads();
+    }
     float rn = 0.f;
     auto fetch = [&](int b) {
         rn = rnorm[pos_next];
         if (b * 32 + (lane & 31) >= B) rn = __builtin_nanf("");      // past the end: every comparison with a NaN fails
         const uint32_t row_bytes = (uint32_t)(d * sizeof(T));
-        frag_load_block<T, KS>(k, d, block, lane, [&](int, int r) { return (uint32_t)__shfl(pos_next, r) * row_bytes; });
+        frag_load_block<T, KS, FRAG_BLOCK>(k, d, block, lane, [&](int, int r) { return (uint32_t)__shfl(pos_next, r) * row_bytes; });
         pos_next = kept[min((b + NA_WAVES) * 32 + (lane & 31), B - 1)];
     };
     float v1[CG], v2[CG];

@@ -142,7 +142,7 @@ k_score_any(const T* __restrict__ q, const T* __restrict__ k, int heads, int gro
     // lines for 1 KB: 3 us of a compute unit's L1 for its 128 KB.)
     frag_t sf[CG][KS];
     {
-        constexpr int RB = frag_row_bytes<KS>(), PART = (RB == 64) ? 16 : (CG == 4) ? 16 : 8;     // rows a wave loads: 1 KB at least, whole swizzle patterns
+        constexpr int RB = frag_row_bytes<KS>(), PART = frag_strip_part<KS, CG>();
         const auto srsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(S), 0, L * d * (int)sizeof(T), 0x00020000);
         if (wave * PART < SR)
             frag_load_rows<T, KS, PART>(srsrc, d, &blocks[0][0] + wave * PART * RB, lane, off, min(s0 + wave * PART, L - 1), L - min(s0 + wave * PART, L - 1));
