@@ -5,18 +5,17 @@
 // window with the highest accumulated score.  Eq. 5's "add max(A_s) to text scores" only serves to
 // rank every text token above every image token, so it is realised as a class, not as a float add.
 // The k_img-th largest score is found by an MSB-first radix select over the monotone integer image
-// of the float bits, re-based to the head's own range (a 12-bit LDS histogram; the few keys that share
-// the threshold's digit are then ranked against each other directly, or, if they are many, by two more
-// digits of 12 and 8 bits); equal scores are resolved towards the lower position by an ordered prefix
+// of the float bits, re-based to the head's own range (an LDS histogram over a digit of 10 to 12 bits; the few keys that
+// share the threshold's digit are then ranked against each other directly, or, if they are many, by further
+// digits); equal scores are resolved towards the lower position by an ordered prefix
 // count.  Kept and evicted index lists come out ascending.
 // Supports L <= 32 * 1024 (32 positions per thread).
 #include "common.h"
 
+#include <type_traits>
+
 namespace lookm {
 
-constexpr int SEL_THREADS = 1024;
-constexpr int SEL_WAVES = SEL_THREADS / 64;
-constexpr int SEL_BINS = 4096;    // 12-bit digits
 constexpr int SEL_CAND = 4096;    // capacity of the LDS candidate list
 constexpr int SEL_FAST = 128;     // up to this many candidates are ranked all against all
 
@@ -28,8 +27,9 @@ __device__ __forceinline__ uint32_t score_key(float s)
     return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
 
-// exclusive prefix sum over the workgroup's 16 waves of one wave-uniform int, and the total.  One barrier;
-// `wtot` is a 16-entry LDS array that nothing else touches (every scan of the kernel has its own).
+// exclusive prefix sum over the workgroup's WAVES waves of one wave-uniform int, and the total.  One barrier;
+// `wtot` is an LDS array that nothing else touches (every scan of the kernel has its own).
+template <int WAVES>
 __device__ __forceinline__ int wave_scan_excl(int wave_value, int* wtot, int& total)
 {
     const int wave = threadIdx.x >> 6;
@@ -37,7 +37,7 @@ __device__ __forceinline__ int wave_scan_excl(int wave_value, int* wtot, int& to
     __syncthreads();
     int before = 0, tot = 0;
 #pragma unroll
-    for (int w = 0; w < SEL_WAVES; ++w) {
+    for (int w = 0; w < WAVES; ++w) {
         const int c = wtot[w];
         before += (w < wave) ? c : 0;
         tot += c;
@@ -50,11 +50,14 @@ __device__ __forceinline__ int wave_scan_excl(int wave_value, int* wtot, int& to
 // positions seg + i*64 + l, i < IPT, so global reads and writes are coalesced.  Keys and classes are
 // read once and stay in registers for the radix passes and the compaction; ordered counts are ballots
 // inside the wave plus one 16-entry scan across waves.
-template <int IPT>
+template <int IPT, int SEL_THREADS>
 __global__ void __launch_bounds__(SEL_THREADS)
 k_select(const float* __restrict__ scores, const uint8_t* __restrict__ mask, int L, int B, int M, int rule,
          int32_t* __restrict__ kept, int32_t* __restrict__ evicted, int32_t* __restrict__ status)
 {
+    constexpr int SEL_WAVES = SEL_THREADS / 64;
+    constexpr int DIGIT = (SEL_THREADS == 1024) ? 12 : (SEL_THREADS == 512) ? 11 : 10, SEL_BINS = 1 << DIGIT;    // four bins a thread
+    static_assert(SEL_BINS == 4 * SEL_THREADS, "");
     __shared__ int hist[SEL_BINS];
     __shared__ uint32_t cand[SEL_CAND];     // keys that share the threshold's top 12 bits
     __shared__ int wtot[8][SEL_WAVES];      // one row per workgroup-wide scan
@@ -121,7 +124,7 @@ k_select(const float* __restrict__ scores, const uint8_t* __restrict__ mask, int
     if (lane == 0) { wmin[wave] = kmin; wmax[wave] = kmax; wtmin[wave] = tmin; wtmax[wave] = tmax; }
 
     int ntext;   // text tokens before the window; |T u R| = ntext + M
-    wave_scan_excl(ntext_wave, wtot[0], ntext);
+    wave_scan_excl<SEL_WAVES>(ntext_wave, wtot[0], ntext);
     const int nprot = ntext + M;
     // Eq. 8 has N = B - M places before the window.  If they hold every text token, text and window are sure and
     // the image tokens compete for the rest; if not, the default rule reports an error, while the literal rule
@@ -165,7 +168,7 @@ k_select(const float* __restrict__ scores, const uint8_t* __restrict__ mask, int
         int kk = k_img;
         int scan_row = 1;
         // finds the bin (counting from the top) where the running count first reaches kk; every thread
-        // owns SEL_BINS / SEL_THREADS consecutive bins in descending order.  Two barriers.
+        // owns up to four consecutive bins in descending order.  Two barriers.
         auto find_bin = [&](int nbins) {
             const int per = (nbins + SEL_THREADS - 1) / SEL_THREADS;   // 4 or 1
             int c[4] = {0, 0, 0, 0}, sum = 0;
@@ -181,7 +184,7 @@ k_select(const float* __restrict__ scores, const uint8_t* __restrict__ mask, int
                 if (lane >= off) incl += v;
             }
             int tot;
-            int cum = wave_scan_excl(__shfl(incl, 63), wtot[scan_row++], tot) + incl - sum;   // count in bins above mine
+            int cum = wave_scan_excl<SEL_WAVES>(__shfl(incl, 63), wtot[scan_row++], tot) + incl - sum;   // count in bins above mine
             for (int i = 0; i < per; ++i) {
                 if (cum < kk && cum + c[i] >= kk) { sh_bin = nbins - 1 - (tid * per + i); sh_k = kk - cum; }
                 cum += c[i];
@@ -193,7 +196,7 @@ k_select(const float* __restrict__ scores, const uint8_t* __restrict__ mask, int
 
 #pragma unroll
         for (int i = 0; i < IPT; ++i)
-            if ((evic_m >> i) & 1u) atomicAdd(&hist[key[i] >> 20], 1);   // hist was cleared before the first barrier
+            if ((evic_m >> i) & 1u) atomicAdd(&hist[key[i] >> (32 - DIGIT)], 1);   // hist was cleared before the first barrier
         __syncthreads();
         const uint32_t d0 = find_bin(SEL_BINS);
         const int n_cand = hist[d0];
@@ -201,7 +204,7 @@ k_select(const float* __restrict__ scores, const uint8_t* __restrict__ mask, int
         if (listed) {
 #pragma unroll
             for (int i = 0; i < IPT; ++i)
-                if (((evic_m >> i) & 1u) && (key[i] >> 20) == d0) cand[atomicAdd(&sh_ncand, 1)] = key[i];
+                if (((evic_m >> i) & 1u) && (key[i] >> (32 - DIGIT)) == d0) cand[atomicAdd(&sh_ncand, 1)] = key[i];
         }
         __syncthreads();
         if (n_cand <= SEL_FAST) {
@@ -220,33 +223,27 @@ k_select(const float* __restrict__ scores, const uint8_t* __restrict__ mask, int
             thr = sh_thr;
             need_eq = sh_k;
         } else {
-            // many keys share the first digit: two more digits of 12 and 8 bits, over the LDS list, or over the
-            // registers when even the list is too small
-            for (int i = tid; i < SEL_BINS; i += SEL_THREADS) hist[i] = 0;
-            __syncthreads();
-            if (listed) {
-                for (int c = tid; c < n_cand; c += SEL_THREADS) atomicAdd(&hist[(cand[c] >> 8) & 0xfffu], 1);
-            } else {
+            // many keys share the first digit: further digits, over the LDS list, or over the registers when even the list
+            // is too small
+            thr = d0;
 #pragma unroll
-                for (int i = 0; i < IPT; ++i)
-                    if (((evic_m >> i) & 1u) && (key[i] >> 20) == d0) atomicAdd(&hist[(key[i] >> 8) & 0xfffu], 1);
-            }
-            __syncthreads();
-            const uint32_t d1 = find_bin(SEL_BINS);
-            const uint32_t top24 = (d0 << 12) | d1;
-            if (tid < 256) hist[tid] = 0;
-            __syncthreads();
-            if (listed) {
-                for (int c = tid; c < n_cand; c += SEL_THREADS)
-                    if ((cand[c] >> 8) == top24) atomicAdd(&hist[cand[c] & 0xffu], 1);
-            } else {
+            for (int done = DIGIT; done < 32; done += DIGIT) {
+                const int width = min(DIGIT, 32 - done), shift = 32 - done - width;
+                for (int i = tid; i < 1 << width; i += SEL_THREADS) hist[i] = 0;
+                __syncthreads();
+                auto count = [&](uint32_t x) {
+                    if ((x >> (32 - done)) == thr) atomicAdd(&hist[(x >> shift) & ((1u << width) - 1u)], 1);
+                };
+                if (listed) {
+                    for (int c = tid; c < n_cand; c += SEL_THREADS) count(cand[c]);
+                } else {
 #pragma unroll
-                for (int i = 0; i < IPT; ++i)
-                    if (((evic_m >> i) & 1u) && (key[i] >> 8) == top24) atomicAdd(&hist[key[i] & 0xffu], 1);
+                    for (int i = 0; i < IPT; ++i)
+                        if ((evic_m >> i) & 1u) count(key[i]);
+                }
+                __syncthreads();
+                thr = (thr << width) | find_bin(1 << width);
             }
-            __syncthreads();
-            const uint32_t d2 = find_bin(256);
-            thr = (top24 << 8) | d2;
             need_eq = kk;
         }
     }
@@ -303,18 +300,25 @@ int launch_select(const float* scores, const uint8_t* mask, int H, int L, int bu
                   int32_t* evicted, int32_t* status, hipStream_t st)
 {
     const LaunchCheck check;
-    const int per_thread = (L + lookm::SEL_THREADS - 1) / lookm::SEL_THREADS;
-    dim3 grid(H), block(lookm::SEL_THREADS);
-    if (per_thread <= 4)
-        hipLaunchKernelGGL(lookm::k_select<4>, grid, block, 0, st, scores, mask, L, budget, M, rule, kept, evicted, status);
-    else if (per_thread <= 8)
-        hipLaunchKernelGGL(lookm::k_select<8>, grid, block, 0, st, scores, mask, L, budget, M, rule, kept, evicted, status);
-    else if (per_thread <= 16)
-        hipLaunchKernelGGL(lookm::k_select<16>, grid, block, 0, st, scores, mask, L, budget, M, rule, kept, evicted, status);
-    else if (per_thread <= 32)
-        hipLaunchKernelGGL(lookm::k_select<32>, grid, block, 0, st, scores, mask, L, budget, M, rule, kept, evicted, status);
+    auto go = [&](auto ipt, auto threads) {
+        hipLaunchKernelGGL((lookm::k_select<decltype(ipt)::value, decltype(threads)::value>), dim3(H), dim3(decltype(threads)::value), 0, st,
+                           scores, mask, L, budget, M, rule, kept, evicted, status);
+    };
+#define LOOKM_SELECT(ipt, threads) go(std::integral_constant<int, ipt>{}, std::integral_constant<int, threads>{})
+    // Barriers and scans across sixteen waves cost more than a short prompt's positions.  32 heads, us with 1024 / 512 / 256
+    // threads: 256 positions 5.5 / 4.3 / 4.2, 512 5.5 / 4.5 / 4.5, 1024 5.7 / 5.0 / 5.2, 2048 6.4 / 5.8 / 6.7,
+    // 2800 7.2 / 7.6 / 9.9 (back-to-back calls; four positions a thread at least, as before, 6.5, 6.6, 6.7, 7.0).
+    if (L <= 256) LOOKM_SELECT(1, 256);
+    else if (L <= 512) LOOKM_SELECT(1, 512);
+    else if (L <= 1024) LOOKM_SELECT(2, 512);
+    else if (L <= 2048) LOOKM_SELECT(4, 512);
+    else if (L <= 4096) LOOKM_SELECT(4, 1024);
+    else if (L <= 8192) LOOKM_SELECT(8, 1024);
+    else if (L <= 16384) LOOKM_SELECT(16, 1024);
+    else if (L <= 32768) LOOKM_SELECT(32, 1024);
     else
         return LOOKM_ERR_UNSUPPORTED;
+#undef LOOKM_SELECT
     mark(LOOKM_K_SELECT);
     return check.status();
 }

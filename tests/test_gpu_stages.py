@@ -486,3 +486,31 @@ def test_mfma_probe_reports_a_plausible_rate():
     for mode in (0, 1, 2):        # constant / random operands with 32x32x16, random operands with 16x16x32
         t = lookm.lookm_probe_mfma(mode, 3, iters=256, reps=6)
         assert 250.0 < t < 2600.0, (mode, t)
+
+
+@pytest.mark.parametrize("L", [1, 64, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025, 2047, 2048, 2049])
+@pytest.mark.parametrize("what", ["spread", "equal", "crowded"])
+def test_selection_at_the_edges_of_its_workgroup_sizes(L, what):
+    """256, 512 and 1024 threads, digits of 10, 11 and 12 bits: distinct scores, all equal, and most of them within a few ulp of
+    each other next to a far larger one (more digits).  Exact, ties to the lower position."""
+    g = torch.Generator().manual_seed(L)
+    s = torch.rand(2, L, generator=g) + 0.5
+    if what == "equal":
+        s.fill_(0.75)
+    if what == "crowded":
+        s = 1.0 + torch.randint(0, 40, (2, L), generator=g).float() * 2.0 ** -23
+        s[:, 0] = 1e30
+    mask = (torch.rand(L, generator=g) < 0.8).to(torch.uint8)
+    M = min(5, L)
+    protected = lookm.protected_count(mask, M)
+    for B in {protected, L, protected + (L - protected) // 3, max(protected, L - 1)}:
+        if B < 1:
+            continue
+        kept, ev = lookm.lookm_select(s.cuda(), mask.cuda(), B, M)
+        for h in range(2):
+            rank = torch.where((mask == 0) | (torch.arange(L) >= L - M), float("inf"), s[h].double())
+            want = torch.sort(torch.sort(-rank, stable=True)[1][:B])[0]
+            assert torch.equal(kept[h].cpu().long(), want)
+            rest = torch.ones(L, dtype=torch.bool)
+            rest[want] = False
+            assert torch.equal(ev[h].cpu().long(), torch.nonzero(rest)[:, 0])
