@@ -488,6 +488,32 @@ def test_mfma_probe_reports_a_plausible_rate():
         assert 250.0 < t < 2600.0, (mode, t)
 
 
+@pytest.mark.parametrize("d,dtype", [(64, torch.float32), (40, torch.bfloat16), (128, torch.bfloat16), (200, torch.float32)])
+@pytest.mark.parametrize("B,Le", [(1, 1), (3, 63), (7, 64), (9, 65), (33, 257), (154, 102), (12, 1023), (70, 1024), (500, 1000)])
+def test_merge_without_a_sort(d, dtype, B, Le):
+    """Short lists are merged by waves that collect their slots' members themselves; many heads, or one entry more than
+    1024, go through the sort: the same heads on both paths, bit for bit (both add the members in ascending position)."""
+    L, lanes = B + Le, 8 if d <= 64 else 16 if d <= 128 else 32
+    many = 4096 * 64 // (B * lanes) + 1                     # heads that take the sort
+    g = torch.Generator().manual_seed(B + Le + d)
+    k, v = torch.randn(3, L, d, generator=g).to(dtype).cuda(), torch.randn(3, L, d, generator=g).to(dtype).cuda()
+    perm = torch.stack([torch.randperm(L, generator=g) for _ in range(3)])
+    kept, ev = perm[:, :B].sort(1)[0].int().cuda(), perm[:, B:].sort(1)[0].int().cuda()
+    u = torch.rand(3, Le, generator=g)
+    assign = torch.stack([(u[0] * B).long(), torch.full((Le,), B - 1), (u[2] ** 4 * B).long()]).int().cuda()   # even, one set, uneven
+    sim = torch.rand(3, Le, generator=g).cuda()
+    args = (k, v, kept, ev, assign, sim)
+    sorted_args = [x.repeat((-(-many // 3),) + (1,) * (x.dim() - 1)).contiguous() for x in args] if many * L * d < 1 << 27 else None
+    for mode in ("averaged", "pivotal", "weighted"):
+        ko, vo = lookm.lookm_merge(*args, mode)
+        if sorted_args:
+            ks, vs = lookm.lookm_merge(*sorted_args, mode)
+            assert torch.equal(ks[-3:], ko) and torch.equal(vs[-3:], vo)
+        for h in range(3):
+            ref = oracle.merge(k[h].float().cpu().numpy(), *(x[h].cpu().numpy() for x in (kept, ev, assign, sim)), mode)
+            assert np.abs(ko[h].float().cpu().numpy() - ref).max() < (2e-2 if dtype == torch.bfloat16 else 1e-4)
+
+
 @pytest.mark.parametrize("L", [1, 64, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025, 2047, 2048, 2049])
 @pytest.mark.parametrize("what", ["spread", "equal", "crowded"])
 def test_selection_at_the_edges_of_its_workgroup_sizes(L, what):
