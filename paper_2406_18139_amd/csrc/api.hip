@@ -14,7 +14,7 @@ constexpr size_t kAlign = 256;
 inline size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 struct Layout {
-    size_t lse, scores, evicted, assign, sim, rnorm, plan, member_pos, member_w, lists, partials, total, least;    // total: what lookm_workspace_bytes gives; least: what is accepted
+    size_t lse, scores, evicted, assign, sim, rnorm, first, member_pos, member_w, lists, partials, total, least;    // total: what lookm_workspace_bytes gives; least: what is accepted
 };
 
 // Hq query heads, H key / value heads (Hq = H without grouped query heads): only the row log-sum-exp and the score
@@ -30,7 +30,7 @@ Layout make_layout(int Hq, int H, int L, int d, int dt, int budget)
     w.assign = o;  o += align_up(HE * sizeof(int32_t));
     w.sim = o;     o += align_up(HE * sizeof(float));
     w.rnorm = o;   o += align_up(HL * sizeof(float));
-    w.plan = o;    o += align_up((size_t)H * budget * 4 * sizeof(int32_t));   // merge plan, one int4 per slot
+    w.first = o;   o += align_up((size_t)H * budget * 4 * sizeof(int32_t));   // where a slot's members begin; budget + 1 a head are in use
     w.member_pos = o; o += align_up(HE * sizeof(int32_t));
     w.member_w = o;   o += align_up(HE * sizeof(float));
     w.lists = o;      o += align_up(lookm_host::score_list_ints(L) * sizeof(int32_t));   // competing / protected keys
@@ -391,7 +391,7 @@ int lookm_merge(const void* k, const void* v, const int32_t* kept_idx, const int
     const Layout w = make_layout(H, H, L, d, (int)dt, budget);
     if ((rc = lookm_host::ensure_device_ready()) != LOOKM_OK) return rc;
     return lookm_host::launch_merge(k, v, kept_idx, evicted_idx, assign, sim, H, L, d, dt, budget, (int)merge_mode,
-                                    at<int32_t>(workspace, w.plan), at<int32_t>(workspace, w.member_pos),
+                                    at<int32_t>(workspace, w.first), at<int32_t>(workspace, w.member_pos),
                                     at<float>(workspace, w.member_w), k_out, v_out, (hipStream_t)hip_stream);
 }
 
@@ -455,7 +455,7 @@ int enqueue_job(const lookm_job& j, hipStream_t st)
         if (rc != LOOKM_OK) return rc;
     }
     return lookm_host::launch_merge(j.k, j.v, j.kept_idx, evicted, assign, sim, H, L, d, dt, budget, (int)j.merge_mode,
-                                    at<int32_t>(workspace, w.plan), at<int32_t>(workspace, w.member_pos),
+                                    at<int32_t>(workspace, w.first), at<int32_t>(workspace, w.member_pos),
                                     at<float>(workspace, w.member_w), j.k_out, j.v_out, st);
 }
 }  // namespace

@@ -44,6 +44,35 @@ __device__ __forceinline__ void load8(const bf16_t* p, float (&o)[8])
     o[4] = __uint_as_float(a.z << 16); o[5] = __uint_as_float(a.z & 0xffff0000u);
     o[6] = __uint_as_float(a.w << 16); o[7] = __uint_as_float(a.w & 0xffff0000u);
 }
+// Eight elements as they were loaded: a bf16 row chunk stays in four registers until it is used, so that many of them can be in
+// flight per lane and still leave room for other waves.
+template <typename T> struct raw8;
+template <> struct raw8<bf16_t> {
+    uint4 a;
+    __device__ __forceinline__ void load(const bf16_t* p) { a = *reinterpret_cast<const uint4*>(p); }
+    __device__ __forceinline__ void get(float (&o)[8]) const
+    {
+        const uint32_t w[4] = {a.x, a.y, a.z, a.w};
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            o[2 * i] = __uint_as_float(w[i] << 16);
+            o[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
+        }
+    }
+};
+template <> struct raw8<float> {
+    float4 a, b;
+    __device__ __forceinline__ void load(const float* p)
+    {
+        a = *reinterpret_cast<const float4*>(p);
+        b = *reinterpret_cast<const float4*>(p + 4);
+    }
+    __device__ __forceinline__ void get(float (&o)[8]) const
+    {
+        o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w; o[4] = b.x; o[5] = b.y; o[6] = b.z; o[7] = b.w;
+    }
+};
+
 // 1 / sqrt(sum of squares), 0 for a zero key: binary64 square root and division, one rounding to fp32 at the end
 __device__ __forceinline__ float inverse_norm(double sum_of_squares)
 {
@@ -115,7 +144,7 @@ int launch_nearest(const void* k, const int32_t* kept, const int32_t* evicted, i
                    hipStream_t st);
 size_t nearest_scratch_bytes(int H, int L, int d, lookm_dtype dt, int budget);
 int launch_merge(const void* k, const void* v, const int32_t* kept, const int32_t* evicted, const int32_t* assign,
-                 const float* sim, int H, int L, int d, lookm_dtype dt, int budget, int mode, int32_t* plan_words,
+                 const float* sim, int H, int L, int d, lookm_dtype dt, int budget, int mode, int32_t* first,
                  int32_t* member_pos, float* member_w, void* k_out, void* v_out, hipStream_t st);
 
 int launch_decode(const void* q, const void* k, const void* v, int H, int rows, int S, int d, lookm_dtype dt, void* out,

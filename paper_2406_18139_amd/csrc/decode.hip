@@ -23,35 +23,6 @@ constexpr int DC_ROWS = 4;          // rows per lane group and step (the NaN tes
 constexpr int DC_MAX_SPLIT = 256;
 constexpr int DC_DIMS = 32;         // output dims per workgroup of the merge
 
-// Eight elements as they were loaded: a bf16 row chunk stays in four registers until it is multiplied, so that the eight
-// chunks in flight per lane leave room for six workgroups on a compute unit.
-template <typename T> struct raw8;
-template <> struct raw8<bf16_t> {
-    uint4 a;
-    __device__ __forceinline__ void load(const bf16_t* p) { a = *reinterpret_cast<const uint4*>(p); }
-    __device__ __forceinline__ void get(float (&o)[8]) const
-    {
-        const uint32_t w[4] = {a.x, a.y, a.z, a.w};
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            o[2 * i] = __uint_as_float(w[i] << 16);
-            o[2 * i + 1] = __uint_as_float(w[i] & 0xffff0000u);
-        }
-    }
-};
-template <> struct raw8<float> {
-    float4 a, b;
-    __device__ __forceinline__ void load(const float* p)
-    {
-        a = *reinterpret_cast<const float4*>(p);
-        b = *reinterpret_cast<const float4*>(p + 4);
-    }
-    __device__ __forceinline__ void get(float (&o)[8]) const
-    {
-        o[0] = a.x; o[1] = a.y; o[2] = a.z; o[3] = a.w; o[4] = b.x; o[5] = b.y; o[6] = b.z; o[7] = b.w;
-    }
-};
-
 // sum over the G lanes of a group (groups aligned to G lanes).  Up to sixteen lanes by data-parallel moves of the vector
 // ALU: exchanges of neighbours and pairs, then mirrors of half rows and rows, which are exchanges too once the lanes that
 // trade places hold equal sums.

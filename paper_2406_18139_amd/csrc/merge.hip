@@ -2,9 +2,9 @@
 //
 // k_bucket groups the evicted tokens of a head by the conserved slot they were matched to (the
 // paper's one-to-many similarity sets k_sim), as a stable counting sort so that every set lists its
-// members' positions (with their matching cosines) in ascending position.  k_merge then GATHERS: one
-// lane group per conserved slot reads its own row and its members' rows and writes one compact output
-// row - no scatter, no float atomics, fixed summation order, coalesced 16-byte accesses along the head
+// members' positions (with their matching cosines) in ascending position.  k_merge then GATHERS: a workgroup
+// reads the rows of some consecutive conserved slots and those of all their members and writes the compact output
+// rows - no scatter, no float atomics, fixed summation order, coalesced 16-byte accesses along the head
 // dimension.  Keys and values use the same sets and (for weighted merging) the same cosine weights.
 #include "common.h"
 
@@ -36,20 +36,15 @@ __device__ __forceinline__ uint64_t match_key(int key, bool valid, int nbits)
 // into start offsets in slot-major, wave-minor order, which makes the fill stable across waves; inside a wave
 // the list is taken 64 entries at a time and lanes with equal slots are ranked by lane.
 //
-// It also writes the segment's part of the merge plan: its slots ordered by the size of their similarity
-// set, largest first, one int4 {slot, first member, set size n, position of the conserved token} per entry.
-// k_merge hands consecutive plan entries to the lane groups of a wave, so groups that run in lockstep have
-// sets of (nearly) equal size, and the longest sets start first.  Sizes are classed as min(n, 63); the order
-// inside a class is arbitrary (it only decides which lane group handles which slot, not any result).
+// It also writes where every slot's members begin, first[0 .. B] for a head, first[B] = Le.
 template <int IPT>
 __global__ void __launch_bounds__(BK_THREADS)
 k_bucket(const int32_t* __restrict__ assign, const int32_t* __restrict__ evicted, const float* __restrict__ sim,
-         const int32_t* __restrict__ kept, int Le, int B, int S, int nbits, int4* __restrict__ plan,
-         int32_t* __restrict__ member_pos, float* __restrict__ member_w)
+         int Le, int B, int S, int nbits, int32_t* __restrict__ first, int32_t* __restrict__ member_pos,
+         float* __restrict__ member_w)
 {
     extern __shared__ int lds[];   // cnt [BK_WAVES][ns] ints, then own [BK_WAVES][64 * IPT] 16-bit entry numbers
     __shared__ int wsum[BK_WAVES], wbelow[BK_WAVES];
-    __shared__ int cls[64];
     const int h = blockIdx.y, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int lo = blockIdx.x * S, ns = min(B, lo + S) - lo;   // this workgroup's slots [lo, lo + ns)
     if (ns <= 0) return;
@@ -58,8 +53,7 @@ k_bucket(const int32_t* __restrict__ assign, const int32_t* __restrict__ evicted
     assign += (size_t)h * Le;
     evicted += (size_t)h * Le;
     sim += (size_t)h * Le;
-    kept += (size_t)h * B + lo;
-    plan += (size_t)h * B + lo;
+    first += (size_t)h * (B + 1);
     member_pos += (size_t)h * Le;
     member_w += (size_t)h * Le;
 
@@ -68,7 +62,6 @@ k_bucket(const int32_t* __restrict__ assign, const int32_t* __restrict__ evicted
 #pragma unroll
     for (int i = 0; i < IPT; ++i) a[i] = assign[min(seg + i * 64 + lane, Le - 1)];   // clamped: masked below
     for (int i = tid; i < BK_WAVES * ns; i += BK_THREADS) cnt[i] = 0;
-    if (tid < 64) cls[tid] = 0;
     __syncthreads();
     int below_wave = 0, n_own = 0;
 #pragma unroll
@@ -86,7 +79,7 @@ k_bucket(const int32_t* __restrict__ assign, const int32_t* __restrict__ evicted
         n_own += __popcll(mb);
     }
     // the wave's first two rows of own entries: their slot, position and cosine are fetched now and arrive while
-    // the offsets and the plan are being worked out
+    // the offsets are being worked out
     int pre_key[2], pre_pos[2];
     float pre_w[2];
 #pragma unroll
@@ -113,53 +106,20 @@ k_bucket(const int32_t* __restrict__ assign, const int32_t* __restrict__ evicted
     }
     if (lane == 63) wsum[wave] = incl;
     __syncthreads();
-    int run = incl - local, total = 0;
+    int run = incl - local;
 #pragma unroll
     for (int w = 0; w < BK_WAVES; ++w) {
         run += wbelow[w] + ((w < wave) ? wsum[w] : 0);   // members of lower segments, then of lower slots
-        total += wbelow[w] + wsum[w];
     }
-    for (int s = a0; s < a1; ++s)
+    if (tid == 0 && lo + ns == B) first[B] = Le;
+    for (int s = a0; s < a1; ++s) {
+        first[lo + s] = run;
 #pragma unroll
         for (int w = 0; w < BK_WAVES; ++w) {
             const int c = cnt[w * ns + s];
             cnt[w * ns + s] = run;
             run += c;
         }
-    __syncthreads();
-
-    // the merge plan of this segment; row 0 of cnt holds every slot's first member, `total` ends the last set
-    for (int j = 0; j < per; ++j) {
-        const int s = tid * per + j;
-        const bool valid = s < ns;
-        const int n = valid ? ((s + 1 < ns) ? cnt[s + 1] : total) - cnt[s] : 0;
-        const int c = 63 - min(n, 63);
-        const uint64_t peers = match_key(c, valid, 6);
-        if (valid && mask_rank(peers) == 0) atomicAdd(&cls[c], __popcll(peers));
-    }
-    __syncthreads();
-    if (wave == 0) {
-        const int v = cls[lane];
-        int in2 = v;
-        for (int off = 1; off < 64; off <<= 1) {
-            const int u = __shfl_up(in2, off);
-            if (lane >= off) in2 += u;
-        }
-        cls[lane] = in2 - v;
-    }
-    __syncthreads();
-    for (int j = 0; j < per; ++j) {
-        const int s = tid * per + j;
-        const bool valid = s < ns;
-        const int s0 = valid ? cnt[s] : 0;
-        const int n = valid ? ((s + 1 < ns) ? cnt[s + 1] : total) - s0 : 0;
-        const int c = 63 - min(n, 63);
-        const uint64_t peers = match_key(c, valid, 6);
-        const int leader = valid ? __ffsll((unsigned long long)peers) - 1 : lane;
-        int base = 0;
-        if (valid && lane == leader) base = atomicAdd(&cls[c], __popcll(peers));
-        base = __shfl(base, leader);
-        if (valid) plan[base + mask_rank(peers)] = make_int4(lo + s, s0, n, kept[s]);
     }
     __syncthreads();
 
@@ -202,116 +162,145 @@ k_bucket(const int32_t* __restrict__ assign, const int32_t* __restrict__ evicted
     }
 }
 
-// The rows of one conserved slot by a lane group, eight dims a lane: its own row at `pos` and those of its n members - from
-// number o0 on, position(t) and cosine(t) - in ascending position.  The members are fetched NB at a time (the 2*NB row
-// loads are independent), so the gather keeps many loads in flight per lane group instead of one dependent chain per
-// member; their positions and weights one batch ahead, so that a long set costs one memory round trip per batch (the
-// rows) instead of two dependent ones.  A short last batch repeats the set's last member with weight zero.
-template <typename T, int NT, int NB, typename Position, typename Cosine>
-__device__ __forceinline__ void merge_slot(const T* const (&x)[NT], T* const (&out)[NT], int d, int pos, int o0, int n, int mode, Position&& position, Cosine&& cosine)
+// The merged row of a conserved token: its own row, its n members' weighted sum.
+template <typename T>
+__device__ __forceinline__ void merged_row(const raw8<T>& own, const float (&sum)[8], int n, int mode, T* __restrict__ out)
 {
-    float xc[NT][8];
-#pragma unroll
-    for (int s = 0; s < NT; ++s) load8(x[s] + (size_t)pos * d, xc[s]);
+    float x[8];
+    own.get(x);
     if (n > 0) {
-        float acc[NT][8];
+        const float inv = 1.0f / (float)(n + 1);
+        if (mode == LOOKM_MERGE_PIVOTAL)             // Eq. 11: (x_c + 1/2 sum (x_e + x_c)) / (n + 1)
 #pragma unroll
-        for (int s = 0; s < NT; ++s)
+            for (int i = 0; i < 8; ++i) x[i] = (x[i] + 0.5f * fmaf((float)n, x[i], sum[i])) * inv;
+        else                                         // Eq. 10 / Eq. 12: (x_c + sum w_e x_e) / (n + 1)
 #pragma unroll
-            for (int i = 0; i < 8; ++i) acc[s][i] = 0.f;
+            for (int i = 0; i < 8; ++i) x[i] = (x[i] + sum[i]) * inv;
+    }
+    store8(out, x);
+}
+
+// G lanes per row, each lane 8 consecutive head dims of the key row and of the value row (both use the same set, the
+// same weights and the same index reads).  A workgroup takes 256 / G consecutive slots, whose members are one stretch of the
+// sorted lists, and its lane groups share out the MEMBERS evenly, whatever slots they belong to: set sizes are very uneven
+// (half the slots have no member, some hundreds), and a lane group per slot spends as many memory latencies on the
+// largest set of the chip as that has batches.  A group adds up its members in ascending order; where a slot ends inside
+// its stretch the sum goes to LDS, a slot that several groups hold a part of is put together there in the order of
+// the groups.  Members are fetched NB at a time (2 * NB row loads in flight per lane), their positions and weights a
+// batch ahead; a short last batch repeats the last member and does not add it.  Bound by HBM: 32 heads x 12644, 2276
+// conserved, 248 MB 53 -> 41 us; 40 x 5904, 3139 conserved 54 -> 39; 32 x 2896 18 -> 14, against a lane group per slot in the
+// order of the set sizes, eight members of fp32 in flight (two workgroups a compute unit instead of four, and a plan of the
+// slots by size to be made: sort 18.3 -> 16.3).  NB = 2: 43 us (12644) and 39.7 (5904), 6: 41.4 and 41.7, 8: 43.0 and 48.3.
+template <typename T, int NB>
+__global__ void __launch_bounds__(256)
+k_merge(const T* __restrict__ k, const T* __restrict__ v, const int32_t* __restrict__ kept, const int32_t* __restrict__ first,
+        const int32_t* __restrict__ member_pos, const float* __restrict__ member_w, int L, int d, int B, int Le, int mode, int lg_G,
+        T* __restrict__ k_out, T* __restrict__ v_out)
+{
+    __shared__ int begin[257];                                              // of the slots' members; one more: the end
+    __shared__ __attribute__((aligned(16))) float slot_sum[2][256 * 8];     // sums of slots that begin inside a group's stretch
+    __shared__ __attribute__((aligned(16))) float head_sum[2][256 * 8];     // .. and of the end of one that began before
+    // heads vary fastest over the grid
+    const int h = blockIdx.x, tid = threadIdx.x, G = 1 << lg_G, NG = 256 >> lg_G, grp = tid >> lg_G, s0 = (int)blockIdx.y * NG;
+    const int c0 = (tid & (G - 1)) * 8, cc = (c0 < d) ? c0 : 0, slot = min(s0 + grp, B - 1);
+    const int pos = kept[(size_t)h * B + slot];
+    for (int i = tid; i <= NG; i += 256) begin[i] = (mode == LOOKM_MERGE_NONE) ? 0 : first[(size_t)h * (B + 1) + min(s0 + i, B)];
+    k += (size_t)h * L * d + cc;
+    v += (size_t)h * L * d + cc;
+    raw8<T> own_k, own_v;
+    own_k.load(k + (size_t)pos * d);
+    own_v.load(v + (size_t)pos * d);
+    __syncthreads();
+    const int m0 = begin[0], M = begin[NG] - m0, per = (M + NG - 1) >> (8 - lg_G);      // members of a group
+    const int t_end = min(m0 + (grp + 1) * per, m0 + M);
+    int t = m0 + grp * per;
+    if (t < t_end) {
+        member_pos += (size_t)h * Le;
+        member_w += (size_t)h * Le;
         const bool weighted = (mode == LOOKM_MERGE_WEIGHTED);
-        const int o1 = o0 + n;
+        int c = 0;                                                          // the slot that member t belongs to
+        for (int step = NG >> 1; step > 0; step >>= 1) c += (begin[c + step] <= t) ? step : 0;
+        bool head = begin[c] < t;
+        int c_end = begin[c + 1];
+        float ak[8], av[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) ak[i] = av[i] = 0.f;
+        auto flush = [&]() {
+            float* to_k = head ? &head_sum[0][tid * 8] : &slot_sum[0][((c << lg_G) + (tid & (G - 1))) * 8];
+            float* to_v = to_k + 256 * 8;
+            store8(to_k, ak);
+            store8(to_v, av);
+            head = false;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) ak[i] = av[i] = 0.f;
+        };
         int p[NB];
         float w[NB];
-        auto fetch_members = [&](int t) {
+        auto fetch_members = [&](int from) {
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
-                const int tt = min(t + j, o1 - 1);
-                p[j] = position(tt);
-                w[j] = (t + j < o1) ? (weighted ? cosine(tt) : 1.0f) : 0.0f;
+                const int tt = min(from + j, t_end - 1);
+                p[j] = member_pos[tt];
+                w[j] = weighted ? member_w[tt] : 1.0f;
             }
         };
-        fetch_members(o0);
-        for (int t = o0; t < o1; t += NB) {          // ascending position
-            float xe[NT][NB][8];
+        fetch_members(t);
+        for (; t < t_end; t += NB) {
+            raw8<T> xk[NB], xv[NB];
 #pragma unroll
-            for (int j = 0; j < NB; ++j)
-#pragma unroll
-                for (int s = 0; s < NT; ++s) load8(x[s] + (size_t)p[j] * d, xe[s][j]);
+            for (int j = 0; j < NB; ++j) {
+                xk[j].load(k + (size_t)p[j] * d);
+                xv[j].load(v + (size_t)p[j] * d);
+            }
             float wc[NB];
 #pragma unroll
             for (int j = 0; j < NB; ++j) wc[j] = w[j];
-            if (t + NB < o1) fetch_members(t + NB);  // in flight together with this batch's rows
+            if (t + NB < t_end) fetch_members(t + NB);
 #pragma unroll
-            for (int j = 0; j < NB; ++j)
+            for (int j = 0; j < NB; ++j) {
+                if (t + j < t_end) {
+                    if (t + j == c_end) {
+                        flush();
+                        do { c_end = begin[++c + 1]; } while (c_end <= t + j);          // (slots without members)
+                    }
+                    float e[8];
+                    xk[j].get(e);
 #pragma unroll
-                for (int s = 0; s < NT; ++s)
+                    for (int i = 0; i < 8; ++i) ak[i] = fmaf(e[i], wc[j], ak[i]);
+                    xv[j].get(e);
 #pragma unroll
-                    for (int i = 0; i < 8; ++i) acc[s][i] = fmaf(xe[s][j][i], wc[j], acc[s][i]);
+                    for (int i = 0; i < 8; ++i) av[i] = fmaf(e[i], wc[j], av[i]);
+                }
+            }
         }
-        const float inv = 1.0f / (float)(n + 1);
+        flush();
+    }
+    __syncthreads();
+    if (s0 + grp >= B || c0 >= d) return;
+    const int n = begin[grp + 1] - begin[grp];       // L_sim: size of this slot's similarity set
+    float sk[8], sv[8];
+    if (n > 0) {
+        load8(&slot_sum[0][tid * 8], sk);
+        load8(&slot_sum[1][tid * 8], sv);
+        const int g_first = (begin[grp] - m0) / per, g_last = (begin[grp + 1] - 1 - m0) / per;
+        for (int g = g_first + 1; g <= g_last; ++g) {
+            float e[8];
+            load8(&head_sum[0][((g << lg_G) + (tid & (G - 1))) * 8], e);
 #pragma unroll
-        for (int s = 0; s < NT; ++s) {
-            if (mode == LOOKM_MERGE_PIVOTAL)         // Eq. 11: (x_c + 1/2 sum (x_e + x_c)) / (n + 1)
+            for (int i = 0; i < 8; ++i) sk[i] += e[i];
+            load8(&head_sum[1][((g << lg_G) + (tid & (G - 1))) * 8], e);
 #pragma unroll
-                for (int i = 0; i < 8; ++i) xc[s][i] = (xc[s][i] + 0.5f * fmaf((float)n, xc[s][i], acc[s][i])) * inv;
-            else                                     // Eq. 10 / Eq. 12: (x_c + sum w_e x_e) / (n + 1)
-#pragma unroll
-                for (int i = 0; i < 8; ++i) xc[s][i] = (xc[s][i] + acc[s][i]) * inv;
+            for (int i = 0; i < 8; ++i) sv[i] += e[i];
         }
     }
-#pragma unroll
-    for (int s = 0; s < NT; ++s) store8(out[s], xc[s]);
+    const size_t out_off = ((size_t)h * B + slot) * d + c0;
+    merged_row(own_k, sk, n, mode, k_out + out_off);
+    merged_row(own_v, sv, n, mode, v_out + out_off);
 }
 
-// G lanes per conserved slot, each lane 8 consecutive head dims of the key row and of the value row (both use
-// the same set, the same weights and the same index reads).  The head's merge plan is NS segments of S entries,
-// each ordered by set size; consecutive workgroups take the next 256/G entries of consecutive segments, so the
-// big sets of every segment are started early.
-template <typename T, int NT, int NB>   // NT = 2: one lane group does the key row and the value row; 1: blockIdx.z picks
-__global__ void __launch_bounds__(256)
-k_merge(const T* __restrict__ k, const T* __restrict__ v, const int32_t* __restrict__ kept,
-        const int4* __restrict__ plan, const int32_t* __restrict__ member_pos,
-        const float* __restrict__ member_w, int L, int d, int B, int Le, int mode, int G, int S, int NS,
-        T* __restrict__ k_out, T* __restrict__ v_out)
-{
-    // heads vary fastest over the grid: the workgroups with the largest sets of every head are dispatched first
-    const int h = blockIdx.x;
-    const int g = (int)blockIdx.y % NS, in_seg = ((int)blockIdx.y / NS) * (256 / G) + (int)threadIdx.x / G;
-    const int idx = g * S + in_seg;
-    const int c0 = ((int)threadIdx.x % G) * 8;
-    if (in_seg >= S || idx >= B || c0 >= d) return;
-    int slot = idx, o0 = 0, n = 0, pos;
-    if (mode != LOOKM_MERGE_NONE) {
-        const int4 pl = plan[(size_t)h * B + idx];
-        slot = pl.x;
-        o0 = pl.y;
-        n = pl.z;                                    // L_sim: size of this slot's similarity set
-        pos = pl.w;
-    } else {
-        pos = kept[(size_t)h * B + slot];
-    }
-    const T* x[NT];
-    T* out[NT];
-    const size_t in_off = (size_t)h * L * d + c0, out_off = ((size_t)h * B + slot) * d + c0;
-    if (NT == 2) {
-        x[0] = k + in_off;
-        x[NT - 1] = v + in_off;
-        out[0] = k_out + out_off;
-        out[NT - 1] = v_out + out_off;
-    } else {
-        x[0] = (blockIdx.z ? v : k) + in_off;
-        out[0] = (blockIdx.z ? v_out : k_out) + out_off;
-    }
-
-    member_pos += (size_t)h * Le;
-    member_w += (size_t)h * Le;
-    merge_slot<T, NT, NB>(x, out, d, pos, o0, n, mode, [&](int t) { return member_pos[t]; }, [&](int t) { return member_w[t]; });
-}
-
-// The same without sort and plan, for short lists: a wave looks after 64 / G consecutive slots, goes through the head's whole
+// The same without the sort, for short lists: a wave looks after 64 / G consecutive slots, goes through the head's whole
 // assignment list by itself, collects the few entries of its slots, in order, and sorts those in LDS.  All of it is a chain of
-// memory latencies; this one is a kernel and four barriers shorter (2 heads x 256 x 64 fp32, the whole layer: 27.0 -> 23.7 us).
+// memory latencies; this one is a kernel and four barriers shorter (2 heads x 256 x 64 fp32, the whole layer: 27.0 -> 23.5 us).
 constexpr int DIRECT_MAX = 1024;
 template <typename T, int NB>
 __global__ void __launch_bounds__(256)
@@ -374,24 +363,45 @@ k_merge_direct(const T* __restrict__ k, const T* __restrict__ v, const int32_t* 
     }
     __syncthreads();
     if (s0 + g >= B || c0 >= d) return;
-    const size_t in_off = (size_t)h * L * d + c0, out_off = ((size_t)h * B + slot) * d + c0;
-    const T* const x[2] = {k + in_off, v + in_off};
-    T* const out[2] = {k_out + out_off, v_out + out_off};
-    const int o0 = first[wave][g];
-    merge_slot<T, 2, NB>(x, out, d, pos, o0, first[wave][g + 1] - o0, mode, [&](int t) { return member_pos[wave][t]; },
-                         [&](int t) { return member_w[wave][t]; });
+    k += (size_t)h * L * d + c0;
+    v += (size_t)h * L * d + c0;
+    raw8<T> own_k, own_v;
+    own_k.load(k + (size_t)pos * d);
+    own_v.load(v + (size_t)pos * d);
+    float sk[8], sv[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) sk[i] = sv[i] = 0.f;
+    const int t0 = first[wave][g], t1 = first[wave][g + 1];
+    for (int t = t0; t < t1; t += NB) {                 // ascending position; a short last batch repeats the last member
+        raw8<T> xk[NB], xv[NB];
+        float w[NB];
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            const int tt = min(t + j, t1 - 1), p = member_pos[wave][tt];
+            xk[j].load(k + (size_t)p * d);
+            xv[j].load(v + (size_t)p * d);
+            w[j] = (mode == LOOKM_MERGE_WEIGHTED) ? member_w[wave][tt] : 1.0f;
+        }
+#pragma unroll
+        for (int j = 0; j < NB; ++j)
+            if (t + j < t1) {
+                float e[8];
+                xk[j].get(e);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) sk[i] = fmaf(e[i], w[j], sk[i]);
+                xv[j].get(e);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) sv[i] = fmaf(e[i], w[j], sv[i]);
+            }
+    }
+    const size_t out_off = ((size_t)h * B + slot) * d + c0;
+    merged_row(own_k, sk, t1 - t0, mode, k_out + out_off);
+    merged_row(own_v, sv, t1 - t0, mode, v_out + out_off);
 }
 
 }  // namespace lookm
 
 namespace lookm_host {
-
-#ifndef LOOKM_MERGE_NT
-#define LOOKM_MERGE_NT 2
-#endif
-#ifndef LOOKM_MERGE_NB
-#define LOOKM_MERGE_NB 8
-#endif
 
 // Segments per head: enough workgroups to cover the chip's 256 compute units, and no more than
 // BK_MAX_SEG slots in one segment.
@@ -406,53 +416,51 @@ static void bucket_segments(int H, int B, int& S, int& NS)
     NS = (B + S - 1) / S;
 }
 
-// lanes per conserved slot
+// log2 of the lanes per row
 static int merge_lanes(int d)
 {
-    int G = 1;
-    while (G * 8 < d) G <<= 1;
-    return G;
+    int lg = 0;
+    while ((8 << lg) < d) ++lg;
+    return lg;
 }
 
 template <typename T>
-static void launch_merge_t(const T* k, const T* v, const int32_t* kept, const int4* plan,
-                           const int32_t* member_pos, const float* member_w, int H, int L, int d, int B, int mode,
-                           int S, int NS, T* k_out, T* v_out, hipStream_t st)
+static void launch_merge_t(const T* k, const T* v, const int32_t* kept, const int32_t* first, const int32_t* member_pos,
+                           const float* member_w, int H, int L, int d, int B, int mode, T* k_out, T* v_out, hipStream_t st)
 {
-    const int G = merge_lanes(d), spb = 256 / G;
-    constexpr int NT = LOOKM_MERGE_NT, NB = LOOKM_MERGE_NB;
-    dim3 grid(H, NS * ((S + spb - 1) / spb), 3 - NT);
-    hipLaunchKernelGGL((lookm::k_merge<T, NT, NB>), grid, dim3(256), 0, st, k, v, kept, plan, member_pos, member_w, L, d, B,
-                       L - B, mode, G, S, NS, k_out, v_out);
+    const int lg_G = merge_lanes(d), slots = 256 >> lg_G;
+    hipLaunchKernelGGL((lookm::k_merge<T, 4>), dim3(H, (B + slots - 1) / slots), dim3(256), 0, st, k, v, kept, first, member_pos,
+                       member_w, L, d, B, L - B, mode, lg_G, k_out, v_out);
 }
 
 template <int IPT>
-static int launch_bucket(const int32_t* assign, const int32_t* evicted, const float* sim, const int32_t* kept,
-                         int H, int Le, int B, int S, int NS, int4* plan, int32_t* member_pos, float* member_w,
-                         hipStream_t st)
+static int launch_bucket(const int32_t* assign, const int32_t* evicted, const float* sim, int H, int Le, int B, int S, int NS,
+                         int32_t* first, int32_t* member_pos, float* member_w, hipStream_t st)
 {
     const size_t lds = (size_t)lookm::BK_WAVES * (S * sizeof(int) + 64 * IPT * sizeof(unsigned short));
     int nbits = 1;
     while ((1 << nbits) < S) ++nbits;
-    hipLaunchKernelGGL(lookm::k_bucket<IPT>, dim3(NS, H), dim3(lookm::BK_THREADS), lds, st, assign, evicted, sim, kept,
-                       Le, B, S, nbits, plan, member_pos, member_w);
+    hipLaunchKernelGGL(lookm::k_bucket<IPT>, dim3(NS, H), dim3(lookm::BK_THREADS), lds, st, assign, evicted, sim,
+                       Le, B, S, nbits, first, member_pos, member_w);
     return LOOKM_OK;
 }
 
 int launch_merge(const void* k, const void* v, const int32_t* kept, const int32_t* evicted, const int32_t* assign,
-                 const float* sim, int H, int L, int d, lookm_dtype dt, int budget, int mode, int32_t* plan_words,
+                 const float* sim, int H, int L, int d, lookm_dtype dt, int budget, int mode, int32_t* first,
                  int32_t* member_pos, float* member_w, void* k_out, void* v_out, hipStream_t st)
 {
     const int B = budget, Le = L - B;
     if (B == 0) return LOOKM_OK;
     const LaunchCheck check;
     if (Le == 0) mode = LOOKM_MERGE_NONE;
-    const int G = merge_lanes(d);
-    // Without a sort up to 4096 waves (four a SIMD), each of which goes through the list by itself: sort and merge against the
-    // direct kernel in us, weighted, 38 waves of 102 entries 16.3 / 13.3, 2244 of 922 22.3 / 19.1, 3200 of 800 17.2 / 14.2,
-    // 4488 of 922 17.0 / 17.4, 7000 of 700 21.3 / 22.0, 8976 of 922 25.8 / 30.5 (back-to-back calls).  A lane group of eight
-    // and more, so that a wave has at most eight slots.
-    if (mode != LOOKM_MERGE_NONE && Le <= lookm::DIRECT_MAX && G >= 8 && (size_t)H * B * G / 64 <= 4096) {
+    const int G = 1 << merge_lanes(d);
+    // Without a sort where that is shorter: up to 2048 waves (two a SIMD), each of which goes through the list by itself, and
+    // sets of four members on average (a lane group per slot: the largest set sets the time).  Sort and merge against the
+    // direct kernel in us (20 calls in a graph): 38 waves, 102 entries in 154 slots 8.0 / 4.6; 400, 500 in 200 10.2 / 8.8;
+    // 1600, 500 in 200 10.9 / 9.3; 2244, 922 in 561 11.9 / 12.2; 8976, 922 in 561 21.4 / 22.1; 800, 400 in 100 11.1 / 10.6;
+    // 360, 1020 in 180 12.2 / 12.5; 120, 540 in 60 12.1 / 14.4; 640, 1020 in 80 15.1 / 20.5.  A lane group has eight lanes and
+    // more, so that a wave has at most eight slots.
+    if (mode != LOOKM_MERGE_NONE && Le <= lookm::DIRECT_MAX && Le <= 4 * (long)B && G >= 8 && (size_t)H * B * G / 64 <= 2048) {
         const int spb = 4 * (64 / G);
         auto go = [&](auto type) {
             typedef decltype(type) T;
@@ -465,30 +473,29 @@ int launch_merge(const void* k, const void* v, const int32_t* kept, const int32_
         mark(LOOKM_K_MERGE);
         return check.status();
     }
-    int4* plan = reinterpret_cast<int4*>(plan_words);
-    int S, NS;
-    bucket_segments(H, B, S, NS);
     if (mode != LOOKM_MERGE_NONE) {
+        int S, NS;
+        bucket_segments(H, B, S, NS);
         const int per_thread = (Le + lookm::BK_THREADS - 1) / lookm::BK_THREADS;
         int rc;
         if (per_thread <= 4)
-            rc = launch_bucket<4>(assign, evicted, sim, kept, H, Le, B, S, NS, plan, member_pos, member_w, st);
+            rc = launch_bucket<4>(assign, evicted, sim, H, Le, B, S, NS, first, member_pos, member_w, st);
         else if (per_thread <= 8)
-            rc = launch_bucket<8>(assign, evicted, sim, kept, H, Le, B, S, NS, plan, member_pos, member_w, st);
+            rc = launch_bucket<8>(assign, evicted, sim, H, Le, B, S, NS, first, member_pos, member_w, st);
         else if (per_thread <= 16)
-            rc = launch_bucket<16>(assign, evicted, sim, kept, H, Le, B, S, NS, plan, member_pos, member_w, st);
+            rc = launch_bucket<16>(assign, evicted, sim, H, Le, B, S, NS, first, member_pos, member_w, st);
         else if (per_thread <= 32)
-            rc = launch_bucket<32>(assign, evicted, sim, kept, H, Le, B, S, NS, plan, member_pos, member_w, st);
+            rc = launch_bucket<32>(assign, evicted, sim, H, Le, B, S, NS, first, member_pos, member_w, st);
         else
             return LOOKM_ERR_UNSUPPORTED;
         if (rc != LOOKM_OK) return rc;
         mark(LOOKM_K_BUCKET);
     }
     if (dt == LOOKM_BF16)
-        launch_merge_t((const lookm::bf16_t*)k, (const lookm::bf16_t*)v, kept, plan, member_pos, member_w, H, L, d,
-                       B, mode, S, NS, (lookm::bf16_t*)k_out, (lookm::bf16_t*)v_out, st);
+        launch_merge_t((const lookm::bf16_t*)k, (const lookm::bf16_t*)v, kept, first, member_pos, member_w, H, L, d,
+                       B, mode, (lookm::bf16_t*)k_out, (lookm::bf16_t*)v_out, st);
     else
-        launch_merge_t((const float*)k, (const float*)v, kept, plan, member_pos, member_w, H, L, d, B, mode, S, NS,
+        launch_merge_t((const float*)k, (const float*)v, kept, first, member_pos, member_w, H, L, d, B, mode,
                        (float*)k_out, (float*)v_out, st);
     mark(LOOKM_K_MERGE);
     return check.status();
