@@ -2,14 +2,12 @@
 // score_any.hip / nearest_any.hip).
 //
 // One step of a fragment is 16 bytes per lane: lane (c = lane % 16, q = lane / 16) holds, of row c, eight
-// consecutive bf16 (dims 32*ks + 8q, one v_mfma_f32_16x16x32_bf16) or four consecutive floats (dims 16*ks + 4q, four
-// v_mfma_f32_16x16x4_f32, number i taking element i of every lane: the dims are visited in another order than they are
-// stored in, the same one for both operands).  Products of bf16 pairs are exact and fp32 ones are fused
-// multiply-adds; both accumulate in fp32.
+// consecutive bf16 (dims 32*ks + 8q, one v_mfma_f32_16x16x32_bf16) or four consecutive floats (dims 16*ks + 4q; the dims
+// are multiplied in another order than they are stored in, the same one for both operands).  Products of bf16 pairs are
+// exact; everything accumulates in fp32.  For fp32 see frag_split.
 //
-// All rows pass through LDS on their way to registers: lanes of equal q hold
-// different rows, so a fragment read from global memory touches 16 cache lines for 1 KB and runs at a quarter of the
-// L1 rate (measured: scores of 32 heads x 2781 x 64 bf16, 44 us a pass; with 32 stationary rows per wave instead of
+// All rows pass through LDS on their way to registers: lanes of equal q hold different rows, so a fragment read from
+// global memory touches 16 cache lines for 1 KB and runs at a quarter of the L1 rate (measured: scores of 32 heads x 2781 x 64 bf16, 44 us a pass; with 32 stationary rows per wave instead of
 // 64, i.e. twice the loads, 66 us).  A wave copies its block of 32 rows with coalesced direct-to-LDS loads into a
 // buffer of its own - no barrier - and reads the fragments from there; the buffer is free again as soon as they are
 // in registers, so one buffer per wave is enough to have the next block in flight.
@@ -28,20 +26,10 @@ template <typename T> struct frag;
 template <> struct frag<bf16_t> {
     typedef frag_bf16 type;
     static constexpr int WIDTH = 8;     // dims per lane and step
-    static constexpr int SUB = 1;       // matrix instructions per step
-    static __device__ __forceinline__ acc_t mma(int, type a, type b, acc_t c)
-    {
-        return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
-    }
 };
 template <> struct frag<float> {
     typedef frag_f32 type;
     static constexpr int WIDTH = 4;
-    static constexpr int SUB = 4;
-    static __device__ __forceinline__ acc_t mma(int i, type a, type b, acc_t c)
-    {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[i], c, 0, 0, 0);
-    }
 };
 
 // Row of an LDS block: KS steps of 64 bytes, rounded up to a power of two.
@@ -127,6 +115,141 @@ __device__ __forceinline__ void frag_read(const void* lds, int rg, int c16, int 
             if ((ks * 4 + q4) * frag<T>::WIDTH >= d) a[ks] = typename frag<T>::type{};
     }
 }
+// fp32 products on the bf16 matrix instruction, which is sixteen times as fast as the fp32 one.  A float is the sum of three
+// bf16 values, each the remainder's nearest: 24 bits exactly.  Of the nine products of two such sums the six largest are
+// added up, smallest first; what is left out is at most 2^-24 of the product, with either sign, and the sum is rounded in
+// fp32 once per 32 dims of every kind where the fp32 instruction rounds once per 4 dims.  Against binary64, cosines of
+// 64 to 256 dims are off by half as much as with the fp32 instruction (1483 x 128: 3.7e-7 at most, 6.8e-7), scores by
+// 1.6 to 3.5e-7 rms (1.6 to 7.5e-7, the upper end with sharp rows).  Two steps of four floats make one step of eight
+// bf16 dims.  An infinity, or a value that rounds to one, leaves a NaN remainder: blocks whose results hold a NaN are done
+// again by the fp32 instruction.
+struct frag_split {
+    frag_bf16 p[3];
+};
+__device__ __forceinline__ frag_split split_steps(frag_f32 lo, frag_f32 hi)
+{
+    typedef __attribute__((ext_vector_type(2))) float f2;
+    typedef __attribute__((ext_vector_type(2))) __bf16 b2;
+    typedef __attribute__((ext_vector_type(4))) uint32_t u4;
+    frag_split s;
+    u4 w[3];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        f2 x = i < 2 ? f2{lo[2 * i], lo[2 * i + 1]} : f2{hi[2 * i - 4], hi[2 * i - 3]};
+#pragma unroll
+        for (int part = 0; part < 3; ++part) {
+            const uint32_t b = __builtin_bit_cast(uint32_t, __builtin_convertvector(x, b2));
+            w[part][i] = b;
+            x[0] -= __uint_as_float(b << 16);
+            x[1] -= __uint_as_float(b & 0xffff0000u);
+        }
+    }
+#pragma unroll
+    for (int part = 0; part < 3; ++part) s.p[part] = __builtin_bit_cast(frag_bf16, w[part]);
+    return s;
+}
+
+// A strip's stationary fragments as the products want them, and the products with a block of 32 streamed rows.
+// row(cg) and streamed(rg): this lane's rows of those groups in memory (past the end: any row), for blocks done again.
+template <typename T, int KS, int CG> struct frag_strip;
+template <int KS, int CG> struct frag_strip<bf16_t, KS, CG> {
+    frag_bf16 s[CG][KS];
+    __device__ __forceinline__ void set(int cg, const frag_bf16 (&f)[KS])
+    {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) s[cg][ks] = f[ks];
+    }
+    template <typename Row, typename Streamed>
+    __device__ __forceinline__ void multiply(const frag_bf16 (&a)[2][KS], acc_t (&acc)[2][CG], int, int, Row&&, Streamed&&) const
+    {
+#pragma unroll
+        for (int cg = 0; cg < CG; ++cg)
+#pragma unroll
+            for (int rg = 0; rg < 2; ++rg) acc[rg][cg] = acc_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int cg = 0; cg < CG; ++cg)
+#pragma unroll
+                for (int rg = 0; rg < 2; ++rg) acc[rg][cg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rg][ks], s[cg][ks], acc[rg][cg], 0, 0, 0);
+    }
+};
+// fp32 with a single group of stationary rows: strips so few that they do not fill the chip, where a block's latency counts and
+// the splitting of its rows only adds to it (2 heads x 256 x 64: 24.3 us the whole layer with bf16 parts, 23.5 without).
+template <int KS> struct frag_strip<float, KS, 1> {
+    frag_f32 s[KS];
+    __device__ __forceinline__ void set(int, const frag_f32 (&f)[KS])
+    {
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) s[ks] = f[ks];
+    }
+    template <typename Row, typename Streamed>
+    __device__ __forceinline__ void multiply(const frag_f32 (&a)[2][KS], acc_t (&acc)[2][1], int, int, Row&&, Streamed&&) const
+    {
+#pragma unroll
+        for (int rg = 0; rg < 2; ++rg) acc[rg][0] = acc_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int rg = 0; rg < 2; ++rg) acc[rg][0] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[rg][ks][i], s[ks][i], acc[rg][0], 0, 0, 0);
+    }
+};
+template <int KS, int CG> struct frag_strip<float, KS, CG> {
+    static constexpr int KB = (KS + 1) / 2;
+    frag_split s[CG][KB];
+    __device__ __forceinline__ void set(int cg, const frag_f32 (&f)[KS])
+    {
+#pragma unroll
+        for (int kb = 0; kb < KB; ++kb) s[cg][kb] = split_steps(f[2 * kb], 2 * kb + 1 < KS ? f[(2 * kb + 1) % KS] : frag_f32{});
+    }
+    template <typename Row, typename Streamed>
+    __device__ __forceinline__ void multiply(const frag_f32 (&a)[2][KS], acc_t (&acc)[2][CG], int q4, int d, Row&& row, Streamed&& streamed) const
+    {
+        constexpr int of_a[6] = {0, 2, 1, 0, 1, 0}, of_s[6] = {2, 0, 1, 1, 0, 0};
+#pragma unroll
+        for (int rg = 0; rg < 2; ++rg) {
+            frag_split t[KB];
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) t[kb] = split_steps(a[rg][2 * kb], 2 * kb + 1 < KS ? a[rg][(2 * kb + 1) % KS] : frag_f32{});
+#pragma unroll
+            for (int cg = 0; cg < CG; ++cg) acc[rg][cg] = acc_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int n = 0; n < 6; ++n)
+#pragma unroll
+                for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                    for (int cg = 0; cg < CG; ++cg)
+                        acc[rg][cg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t[kb].p[of_a[n]], s[cg][kb].p[of_s[n]], acc[rg][cg], 0, 0, 0);
+        }
+        bool nan = false;
+#pragma unroll
+        for (int cg = 0; cg < CG; ++cg)
+#pragma unroll
+            for (int rg = 0; rg < 2; ++rg)
+                nan = nan || __builtin_isunordered(acc[rg][cg][0], acc[rg][cg][1]) || __builtin_isunordered(acc[rg][cg][2], acc[rg][cg][3]);
+        if (__builtin_expect(__any(nan), 0)) {                 // wave-uniform
+#pragma unroll
+            for (int cg = 0; cg < CG; ++cg)
+#pragma unroll
+                for (int rg = 0; rg < 2; ++rg) {
+                    const float *x = streamed(rg), *y = row(cg);
+                    acc_t c = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+                    for (int ks = 0; ks < KS; ++ks) {
+                        const int at = (ks * 4 + q4) * 4;
+                        const frag_f32 u = at < d ? *reinterpret_cast<const frag_f32*>(x + at) : frag_f32{};
+                        const frag_f32 w = at < d ? *reinterpret_cast<const frag_f32*>(y + at) : frag_f32{};
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) c = __builtin_amdgcn_mfma_f32_16x16x4f32(u[i], w[i], c, 0, 0, 0);
+                    }
+                    acc[rg][cg] = c;
+                }
+        }
+    }
+};
+
 // Rows of a strip of 16 * CG stationary rows that a wave loads: a quarter, but 1 KB at least and whole patterns of the swizzle.
 template <int KS, int CG> constexpr int frag_strip_part() { return (frag_row_bytes<KS>() == 64 || CG == 4) ? 16 : 8; }
 // Everything a wave has asked for has arrived: direct-to-LDS loads are not tracked by the compiler.

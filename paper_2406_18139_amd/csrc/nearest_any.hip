@@ -92,7 +92,7 @@ k_nearest_any(const T* __restrict__ k, const float* __restrict__ rnorm, const in
     // lane r % 32 holds the position of row r of the block that is fetched next, and the inverse norm of the one in flight
     int pos_next = kept[min(wave * 32 + (lane & 31), B - 1)];
     // Evicted rows: every wave needs all of the strip, loads a quarter into the block buffers and reads all of it.
-    frag_t sf[CG][KS];
+    frag_strip<T, KS, CG> strip;
     {
         constexpr int RB = frag_row_bytes<KS>(), PART = frag_strip_part<KS, CG>();
         if (wave * PART < SR) {
@@ -103,7 +103,11 @@ k_nearest_any(const T* __restrict__ k, const float* __restrict__ rnorm, const in
         frag_wait_loads();
         __syncthreads();
 #pragma unroll
-        for (int cg = 0; cg < CG; ++cg) frag_read<T, KS>(&blocks[0][0], cg, c16, q4, d, sf[cg]);
+        for (int cg = 0; cg < CG; ++cg) {
+            frag_t f[KS];
+            frag_read<T, KS>(&blocks[0][0], cg, c16, q4, d, f);
+            strip.set(cg, f);
+        }
         __syncthreads();
     }
     float rn = 0.f;
@@ -135,18 +139,8 @@ k_nearest_any(const T* __restrict__ k, const float* __restrict__ rnorm, const in
         if (b + NA_WAVES < n_blocks) fetch(b + NA_WAVES);
         __builtin_amdgcn_sched_barrier(0);
         acc_t acc[2][CG];
-#pragma unroll
-        for (int cg = 0; cg < CG; ++cg)
-#pragma unroll
-            for (int rg = 0; rg < 2; ++rg) acc[rg][cg] = acc_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-            for (int i = 0; i < frag<T>::SUB; ++i)
-#pragma unroll
-                for (int cg = 0; cg < CG; ++cg)
-#pragma unroll
-                    for (int rg = 0; rg < 2; ++rg) acc[rg][cg] = frag<T>::mma(i, a[rg][ks], sf[cg][ks], acc[rg][cg]);
+        strip.multiply(a, acc, q4, d, [&](int cg) { return k + (size_t)evicted[min(e0 + 16 * cg + c16, Le - 1)] * d; },
+                       [&](int rg) { return k + (size_t)kept[min(b * 32 + 16 * rg + c16, B - 1)] * d; });
 #pragma unroll
         for (int cg = 0; cg < CG; ++cg)
 #pragma unroll
@@ -196,10 +190,11 @@ k_nearest_any(const T* __restrict__ k, const float* __restrict__ rnorm, const in
     int s = found.s1;
     // A sum of d products in any order, roundings to nearest or towards zero, is off by at most d 2^-23 |e| |c|, the chain of fused
     // multiply-adds by half of that, and the factor 1 / |c| adds a rounding to each: two values that the other order can swap
-    // are within 6 (d + 1) 2^-24 |e| of each other (|e| = 1 / e_rn).  A key of norm zero has all values zero in every order.
+    // are within 6 (d + 1) 2^-24 |e| of each other (|e| = 1 / e_rn).  fp32 products from bf16 parts leave out 2^-24 |e| |c| and
+    // add up their small parts, five times d terms of at most 2^-7 |e| |c| together, first: (7 d + 8) 2^-24.  A key of norm zero has all values zero in every order.
     // A bound, not an estimate: with d = 64 it sends a few keys in a hundred to the second look, and about one in a thousand
     // because of a third value (or of two in one lane) through a sixteenth of the slots or a few.
-    const float band = 6.f * (float)(d + 1) * 0x1p-24f;
+    const float band = (sizeof(T) == 4 ? 7.f * (float)d + 8.f : 6.f * (float)(d + 1)) * 0x1p-24f;
     auto close = [&](float x) { return (found.v1 - x) * e_rn <= band; };
     const uint64_t many = __ballot(mine && found.s1 < B && e_rn != 0.f && close(found.rest));      // alike in all four waves
     if (wave == 0 && mine && found.s2 < B && close(found.v2) && !((many >> lane) & 1)) {

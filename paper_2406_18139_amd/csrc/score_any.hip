@@ -13,15 +13,15 @@
 // kernel behind them, leaves short strips (64 rows; 32 or 16 in fp32), so that a few hundred tokens already make
 // enough workgroups, and nothing is written but the result.
 //
-// What bounds it: fp32 - the fp32 matrix instruction (64 flop per cycle and SIMD, and the vector ALU stands still
-// meanwhile: the co-execution counter reads zero; the matrix pipe is busy 68 % of the time a compute unit has work, the
-// longest strips run alone for the last fifth); bf16 - the vector ALU, busy 83 % of the time in pass 1 and 77 % in pass 2
-// with an exponential and its two companions per logit.  Both passes over 16 heads x 1483 x 128 fp32: 105 us
-// (on the vector ALU, with 64 x 64 tiles in LDS: 685 us); over 32 x 2781 x 64 bf16: 55 us (790 us); over
-// 2 x 256 x 64 fp32: 10 us (64 us).  Stationary rows through LDS, blocks through a buffer descriptor, log-sum-exps
-// straight to LDS, the first block of a wave without a sum against a reference that it has not got: 121 and 62 us before.
-// (Tried: every other 32 workgroups of an XCD in the opposite order, so that long strips meet short ones: 2 us slower;
-// fp32 blocks of 16 rows, three workgroups a compute unit instead of two: pass 1 52 -> 56 us, all strips start at once.)
+// What bounds it: bf16 - the vector ALU, busy 83 % of the time in pass 1 and 77 % in pass 2 with an exponential and its two
+// companions per logit; fp32 - the same unit, with the splitting of every streamed row into bf16 parts for every strip (five and
+// a half instructions a float), and the longest strips, which run alone for the last fifth of the time.  Both passes over
+// 16 heads x 1483 x 128 fp32: 80 us (105 us on the fp32 matrix instruction, beside which the vector ALU stands still; on the
+// vector ALU, with 64 x 64 tiles in LDS: 685 us); over 32 x 2781 x 64 bf16: 55 us (790 us); over 2 x 256 x 64 fp32: 10 us
+// (64 us).  Stationary rows through LDS, blocks through a buffer descriptor, log-sum-exps straight to LDS, the first block of
+// a wave without a sum against a reference that it has not got: from 121 and 62 us.
+// (Tried: every other 32 workgroups of an XCD in the opposite order, so that long strips meet short ones on a compute unit:
+// no gain, the third lot undoes it; fp32 blocks of 16 rows, three workgroups a compute unit: pass 1 52 -> 56 us.)
 #include "frag.h"
 
 #include <algorithm>
@@ -140,7 +140,7 @@ k_score_any(const T* __restrict__ q, const T* __restrict__ k, int heads, int gro
     // Stationary rows: every wave needs all of them, so each loads a quarter of the strip - into the buffers that the
     // streamed blocks take afterwards - and reads all of it.  (Fragments straight from global memory touch sixteen cache
     // lines for 1 KB: 3 us of a compute unit's L1 for its 128 KB.)
-    frag_t sf[CG][KS];
+    frag_strip<T, KS, CG> strip;
     {
         constexpr int RB = frag_row_bytes<KS>(), PART = frag_strip_part<KS, CG>();
         const auto srsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(S), 0, L * d * (int)sizeof(T), 0x00020000);
@@ -149,7 +149,11 @@ k_score_any(const T* __restrict__ q, const T* __restrict__ k, int heads, int gro
         frag_wait_loads();
         __syncthreads();
 #pragma unroll
-        for (int cg = 0; cg < CG; ++cg) frag_read<T, KS>(&blocks[0][0], cg, c16, q4, d, sf[cg]);
+        for (int cg = 0; cg < CG; ++cg) {
+            frag_t f[KS];
+            frag_read<T, KS>(&blocks[0][0], cg, c16, q4, d, f);
+            strip.set(cg, f);
+        }
         __syncthreads();
     }
 
@@ -196,18 +200,8 @@ k_score_any(const T* __restrict__ q, const T* __restrict__ k, int heads, int gro
             if (b + SA_WAVES < b_end) fetch(b + SA_WAVES);
             __builtin_amdgcn_sched_barrier(0);
             acc_t acc[2][CG];
-#pragma unroll
-            for (int cg = 0; cg < CG; ++cg)
-#pragma unroll
-                for (int rg = 0; rg < 2; ++rg) acc[rg][cg] = acc_t{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-                for (int i = 0; i < frag<T>::SUB; ++i)
-#pragma unroll
-                    for (int cg = 0; cg < CG; ++cg)
-#pragma unroll
-                        for (int rg = 0; rg < 2; ++rg) acc[rg][cg] = frag<T>::mma(i, a[rg][ks], sf[cg][ks], acc[rg][cg]);
+            strip.multiply(a, acc, q4, d, [&](int cg) { return S + (size_t)min(s0 + 16 * cg + c16, L - 1) * d; },
+                           [&](int rg) { return X + (size_t)min(b * 32 + 16 * rg + c16, L - 1) * d; });
             const int xq = b * 32 + 4 * q4;          // streamed row of entry i of acc[rg][.]: xq + 16*rg + i
             if (PASS == 1) {
                 if (b * 32 + 31 > s0) {              // blocks on the diagonal are masked element by element (wave-uniform)

@@ -93,6 +93,40 @@ def test_infinite_keys_and_nan_queries_stay_where_they_are(d, dtype):
     np.testing.assert_allclose(got.numpy(), p[bad + 1:].sum(0).numpy(), rtol=3e-5)
 
 
+@pytest.mark.parametrize("d", [8, 24, 64, 72, 96, 128])
+@pytest.mark.parametrize("what", ["plain", "infinite key", "key that rounds to infinity in bf16", "nan query", "tiny and huge"])
+def test_fp32_products_from_bf16_parts(d, what):
+    """fp32 with strips of 32 rows multiplies bf16 parts, with strips of 16 rows (few heads) floats: both are off by the fp32
+    rounding of a sum of d products, 3e-5 in an exponential, and agree where a block holds what the parts cannot hold."""
+    L, H = 203, 40
+    g = torch.Generator().manual_seed(d)
+    q, k = torch.randn(1, L, d, generator=g), torch.randn(1, L, d, generator=g)
+    if what == "infinite key":
+        q[:, :, 0] = -1.0
+        k[:, 40, 0] = float("inf")
+    if what == "key that rounds to infinity in bf16":
+        q[:, :, 1] = 1e-38
+        k[:, 50, 1] = 3.4e38
+    if what == "nan query":
+        q[:, 77] = float("nan")
+    if what == "tiny and huge":
+        q *= 1e-30
+        k *= 1e30
+    one = lookm.lookm_scores(q.cuda(), k.cuda())
+    many = lookm.lookm_scores(q.repeat(H, 1, 1).cuda(), k.repeat(H, 1, 1).cuda())
+    assert torch.equal(many.nan_to_num(-1), many[:1].nan_to_num(-1).expand_as(many))
+    np.testing.assert_allclose(many[0].cpu().numpy(), one[0].cpu().numpy(), rtol=3e-5)
+    if what != "nan query":
+        p = torch.softmax(((q.double()[0] @ k.double()[0].t()) / d ** 0.5).masked_fill(torch.ones(L, L).triu(1).bool(), -float("inf")), 1)
+        np.testing.assert_allclose(many[0].cpu().double().numpy(), p.sum(0).numpy(), rtol=3e-5)
+    kept, ev = torch.arange(0, L, 3, dtype=torch.int32)[None], torch.tensor([i for i in range(L) if i % 3], dtype=torch.int32)[None]
+    a1, s1 = lookm.lookm_nearest(k.cuda(), kept.cuda(), ev.cuda())
+    big = 80                                                  # 135 evicted keys: five strips of 32 a head
+    am, sm = lookm.lookm_nearest(k.repeat(big, 1, 1).cuda(), kept.repeat(big, 1).cuda(), ev.repeat(big, 1).cuda())
+    assert torch.equal(am, a1.expand_as(am)) and torch.equal(sm.nan_to_num(-9), sm[:1].nan_to_num(-9).expand_as(sm))
+    np.testing.assert_allclose(sm[0].cpu().numpy(), s1[0].cpu().numpy(), rtol=1e-5, atol=1e-6)
+
+
 @pytest.mark.parametrize("d,dtype", [(64, BF), (80, BF), (256, BF), (24, F32), (128, F32)])
 def test_scores_logits_that_jump_late_in_the_row(d, dtype):
     # the twin of the test of that name for bf16 x 128: a block more than 64 binades above the row's reference makes pass 1
