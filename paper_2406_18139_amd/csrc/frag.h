@@ -122,7 +122,11 @@ __device__ __forceinline__ void frag_read(const void* lds, int rg, int c16, int 
 // 64 to 256 dims are off by half as much as with the fp32 instruction (1483 x 128: 3.7e-7 at most, 6.8e-7), scores by
 // 1.6 to 3.5e-7 rms (1.6 to 7.5e-7, the upper end with sharp rows).  Two steps of four floats make one step of eight
 // bf16 dims.  An infinity, or a value that rounds to one, leaves a NaN remainder: blocks whose results hold a NaN are done
-// again by the fp32 instruction.
+// again by the fp32 instruction.  So are all blocks of a strip with values that the parts hold only in part, or that make what
+// the streamed rows' parts leave out count (a bf16 ends at 2^-133, a third part lies 16 to 17 binades below its float): stationary
+// values other than zero below 2^-100, or above 2^100.  What is left out of streamed values below 2^-110 is then at most
+// d 2^(100 - 134) of a logit.  (16 x 900 x 128, keys of 2^-122 and queries of 2^122, scores rms against binary64: 2.1e-5
+// without this rule, 1.7e-7 with it.)
 struct frag_split {
     frag_bf16 p[3];
 };
@@ -150,7 +154,8 @@ __device__ __forceinline__ frag_split split_steps(frag_f32 lo, frag_f32 hi)
 }
 
 // A strip's stationary fragments as the products want them, and the products with a block of 32 streamed rows.
-// row(cg) and streamed(rg): this lane's rows of those groups in memory (past the end: any row), for blocks done again.
+// row(cg) and streamed(rg): this lane's rows of those groups in memory (past the end: any row), for blocks done again, which
+// in_fp32 (wave-uniform) asks for.
 template <typename T, int KS, int CG> struct frag_strip;
 template <int KS, int CG> struct frag_strip<bf16_t, KS, CG> {
     frag_bf16 s[CG][KS];
@@ -160,7 +165,7 @@ template <int KS, int CG> struct frag_strip<bf16_t, KS, CG> {
         for (int ks = 0; ks < KS; ++ks) s[cg][ks] = f[ks];
     }
     template <typename Row, typename Streamed>
-    __device__ __forceinline__ void multiply(const frag_bf16 (&a)[2][KS], acc_t (&acc)[2][CG], int, int, Row&&, Streamed&&) const
+    __device__ __forceinline__ void multiply(const frag_bf16 (&a)[2][KS], acc_t (&acc)[2][CG], int, int, bool, Row&&, Streamed&&) const
     {
 #pragma unroll
         for (int cg = 0; cg < CG; ++cg)
@@ -184,7 +189,7 @@ template <int KS> struct frag_strip<float, KS, 1> {
         for (int ks = 0; ks < KS; ++ks) s[ks] = f[ks];
     }
     template <typename Row, typename Streamed>
-    __device__ __forceinline__ void multiply(const frag_f32 (&a)[2][KS], acc_t (&acc)[2][1], int, int, Row&&, Streamed&&) const
+    __device__ __forceinline__ void multiply(const frag_f32 (&a)[2][KS], acc_t (&acc)[2][1], int, int, bool, Row&&, Streamed&&) const
     {
 #pragma unroll
         for (int rg = 0; rg < 2; ++rg) acc[rg][0] = acc_t{0.f, 0.f, 0.f, 0.f};
@@ -199,13 +204,24 @@ template <int KS> struct frag_strip<float, KS, 1> {
 template <int KS, int CG> struct frag_strip<float, KS, CG> {
     static constexpr int KB = (KS + 1) / 2;
     frag_split s[CG][KB];
+    bool extreme = false;                      // wave-uniform
     __device__ __forceinline__ void set(int cg, const frag_f32 (&f)[KS])
     {
 #pragma unroll
         for (int kb = 0; kb < KB; ++kb) s[cg][kb] = split_steps(f[2 * kb], 2 * kb + 1 < KS ? f[(2 * kb + 1) % KS] : frag_f32{});
+        uint32_t low = ~0u;                    // twice the bits, without the sign, less one: a zero comes last
+        float high = 0.f;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                low = min(low, 2 * __float_as_uint(f[ks][i]) - 1);
+                high = fmaxf(high, fabsf(f[ks][i]));
+            }
+        extreme = extreme || __any(low < 2 * __float_as_uint(0x1p-100f) - 1 || high > 0x1p100f);
     }
     template <typename Row, typename Streamed>
-    __device__ __forceinline__ void multiply(const frag_f32 (&a)[2][KS], acc_t (&acc)[2][CG], int q4, int d, Row&& row, Streamed&& streamed) const
+    __device__ __forceinline__ void multiply(const frag_f32 (&a)[2][KS], acc_t (&acc)[2][CG], int q4, int d, bool in_fp32, Row&& row, Streamed&& streamed) const
     {
         constexpr int of_a[6] = {0, 2, 1, 0, 1, 0}, of_s[6] = {2, 0, 1, 1, 0, 0};
 #pragma unroll
@@ -229,7 +245,7 @@ template <int KS, int CG> struct frag_strip<float, KS, CG> {
 #pragma unroll
             for (int rg = 0; rg < 2; ++rg)
                 nan = nan || __builtin_isunordered(acc[rg][cg][0], acc[rg][cg][1]) || __builtin_isunordered(acc[rg][cg][2], acc[rg][cg][3]);
-        if (__builtin_expect(__any(nan), 0)) {                 // wave-uniform
+        if (__builtin_expect(__any(nan) || extreme || in_fp32, 0)) {     // wave-uniform
 #pragma unroll
             for (int cg = 0; cg < CG; ++cg)
 #pragma unroll

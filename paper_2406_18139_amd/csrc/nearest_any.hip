@@ -134,12 +134,13 @@ k_nearest_any(const T* __restrict__ k, const float* __restrict__ rnorm, const in
 #pragma unroll
             for (int i = 0; i < 4; ++i) r[rg][i] = __shfl(rn, 16 * rg + 4 * q4 + i);
         }
+        const bool tiny = sizeof(T) == 4 && __any(rn > 0x1p100f);    // a conserved row too short for bf16 parts to give its direction
         __builtin_amdgcn_s_waitcnt(0xC07F);          // lgkmcnt(0): the fragments are in registers, the block may be refilled
         __builtin_amdgcn_sched_barrier(0);
         if (b + NA_WAVES < n_blocks) fetch(b + NA_WAVES);
         __builtin_amdgcn_sched_barrier(0);
         acc_t acc[2][CG];
-        strip.multiply(a, acc, q4, d, [&](int cg) { return k + (size_t)evicted[min(e0 + 16 * cg + c16, Le - 1)] * d; },
+        strip.multiply(a, acc, q4, d, tiny, [&](int cg) { return k + (size_t)evicted[min(e0 + 16 * cg + c16, Le - 1)] * d; },
                        [&](int rg) { return k + (size_t)kept[min(b * 32 + 16 * rg + c16, B - 1)] * d; });
 #pragma unroll
         for (int cg = 0; cg < CG; ++cg)

@@ -200,7 +200,7 @@ k_score_any(const T* __restrict__ q, const T* __restrict__ k, int heads, int gro
             if (b + SA_WAVES < b_end) fetch(b + SA_WAVES);
             __builtin_amdgcn_sched_barrier(0);
             acc_t acc[2][CG];
-            strip.multiply(a, acc, q4, d, [&](int cg) { return S + (size_t)min(s0 + 16 * cg + c16, L - 1) * d; },
+            strip.multiply(a, acc, q4, d, false, [&](int cg) { return S + (size_t)min(s0 + 16 * cg + c16, L - 1) * d; },
                            [&](int rg) { return X + (size_t)min(b * 32 + 16 * rg + c16, L - 1) * d; });
             const int xq = b * 32 + 4 * q4;          // streamed row of entry i of acc[rg][.]: xq + 16*rg + i
             if (PASS == 1) {

@@ -94,7 +94,7 @@ def test_infinite_keys_and_nan_queries_stay_where_they_are(d, dtype):
 
 
 @pytest.mark.parametrize("d", [8, 24, 64, 72, 96, 128])
-@pytest.mark.parametrize("what", ["plain", "infinite key", "key that rounds to infinity in bf16", "nan query", "tiny and huge"])
+@pytest.mark.parametrize("what", ["plain", "infinite key", "key that rounds to infinity in bf16", "nan query", "tiny and huge", "tiny keys, huge queries", "tiny conserved keys"])
 def test_fp32_products_from_bf16_parts(d, what):
     """fp32 with strips of 32 rows multiplies bf16 parts, with strips of 16 rows (few heads) floats: both are off by the fp32
     rounding of a sum of d products, 3e-5 in an exponential, and agree where a block holds what the parts cannot hold."""
@@ -109,6 +109,11 @@ def test_fp32_products_from_bf16_parts(d, what):
         k[:, 50, 1] = 3.4e38
     if what == "nan query":
         q[:, 77] = float("nan")
+    if what == "tiny keys, huge queries":      # a key's third part is less than a bf16 holds
+        q *= 2.0 ** 122
+        k *= 2.0 ** -122
+    if what == "tiny conserved keys":
+        k[:, ::3] *= 2.0 ** -122
     if what == "tiny and huge":
         q *= 1e-30
         k *= 1e30
