@@ -118,9 +118,9 @@ __device__ __forceinline__ void frag_read(const void* lds, int rg, int c16, int 
 // fp32 products on the bf16 matrix instruction, which is sixteen times as fast as the fp32 one.  A float is the sum of three
 // bf16 values, each the remainder's nearest: 24 bits exactly.  Of the nine products of two such sums the six largest are
 // added up, smallest first; what is left out is at most 2^-24 of the product, with either sign, and the sum is rounded in
-// fp32 once per 32 dims of every kind where the fp32 instruction rounds once per 4 dims.  Against binary64, cosines of
-// 64 to 256 dims are off by half as much as with the fp32 instruction (1483 x 128: 3.7e-7 at most, 6.8e-7), scores by
-// 1.6 to 3.5e-7 rms (1.6 to 7.5e-7, the upper end with sharp rows).  Two steps of four floats make one step of eight
+// fp32 once per 32 dims of every kind where the fp32 instruction rounds once per 4 dims.  Against binary64, the largest
+// error of a cosine is 0.45 to 1 of the fp32 instruction's (8 to 128 dims; 1483 x 128: 4.1e-7, 6.9e-7), the rms of the scores' 0.45 to
+// 1.02 (1.6 to 3.6e-7, mostly the log-sum-exp's). Two steps of four floats make one step of eight
 // bf16 dims.  An infinity, or a value that rounds to one, leaves a NaN remainder: blocks whose results hold a NaN are done
 // again by the fp32 instruction.  So are all blocks of a strip with values that the parts hold only in part, or that make what
 // the streamed rows' parts leave out count (a bf16 ends at 2^-133, a third part lies 16 to 17 binades below its float): stationary
