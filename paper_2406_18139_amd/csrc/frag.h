@@ -92,9 +92,14 @@ __device__ __forceinline__ void frag_load_rows(__amdgpu_buffer_rsrc_t rsrc, int 
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)((char*)lds + n * 1024), 16, off[n % V],
                                                      (row0 + n / V * V * (64 / CH)) * row_bytes, 0, 0);
     } else {
+        // The row number is hidden from the compiler: where a piece is a row (fp32 wider than 128) it would otherwise carry one
+        // counter per piece through the caller's loop, 32 of them and more than the scalar registers hold (16 x 1483 x 136:
+        // pass 2 119 us, 108 without them; in narrower ones vector registers, 10 to 60 of them).
+        int last = rows - 1;
+        asm volatile("" : "+s"(last));
 #pragma unroll
         for (int n = 0; n < NI; ++n) {
-            const int r = n * (64 / CH) + lane / CH, past = min(rows - 1 - r, 0);
+            const int r = n * (64 / CH) + lane / CH, past = min(last - r, 0);
             __builtin_amdgcn_raw_ptr_buffer_load_lds(rsrc, (__attribute__((address_space(3))) void*)((char*)lds + n * 1024), 16,
                                                      off[n % V] + (row0 + n / V * V * (64 / CH) + past) * row_bytes, 0, 0, 0);
         }

@@ -13,7 +13,7 @@ MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
 
 @pytest.fixture(scope="module")
 def registers(tmp_path_factory):
-    """{mangled kernel name: (vector registers, bytes of scratch)} over the gfx950 code objects of the library."""
+    """{mangled kernel name: (vector registers, bytes of scratch, spilled scalar registers)} over the gfx950 code objects of the library."""
     if not READELF:
         pytest.skip("no llvm-readelf")
     lookm.lib()
@@ -27,7 +27,7 @@ def registers(tmp_path_factory):
             if "gfx950" in target and size:
                 path = tmp_path_factory.mktemp("co") / "code.elf"
                 path.write_bytes(blob[at + offset:at + offset + size])
-                name = scratch = None
+                name = scratch = spilled = None
                 for line in subprocess.run([READELF, "--notes", str(path)], capture_output=True, text=True, check=True).stdout.splitlines():
                     key, _, value = line.strip().partition(":")
                     value = value.strip()
@@ -35,8 +35,10 @@ def registers(tmp_path_factory):
                         name = value
                     elif key == ".private_segment_fixed_size":
                         scratch = int(value)
+                    elif key == ".sgpr_spill_count":
+                        spilled = int(value)
                     elif key == ".vgpr_count":
-                        found[name] = (int(value), scratch)
+                        found[name] = (int(value), scratch, spilled)
         at += len(MAGIC)
     assert found
     return found
@@ -46,8 +48,20 @@ def registers(tmp_path_factory):
 @pytest.mark.parametrize("kernel,limit", [("k_score_anyILi1EtLi3ELi4EE", 168), ("k_score_anyILi2EtLi3ELi4EE", 168),     # bf16, 72 to 96 wide
                                           ("k_nearest_anyItLi3ELi4EE", 168),
                                           ("k_score_anyILi1EtLi2ELi4EE", 128), ("k_score_anyILi2EtLi2ELi4EE", 128),     # bf16, 40 to 64 wide
-                                          ("k_nearest_anyItLi2ELi4EE", 128)])
+                                          ("k_nearest_anyItLi2ELi4EE", 128),
+                                          ("k_score_anyILi1EfLi4ELi2EE", 128), ("k_score_anyILi2EfLi4ELi2EE", 168),     # fp32, 56 and 64 wide
+                                          ("k_score_anyILi1EfLi8ELi2EE", 256), ("k_score_anyILi2EfLi8ELi2EE", 256)])    # 104 to 128: two waves
 def test_waves_per_simd(registers, kernel, limit):
     counts = [v for k, v in registers.items() if kernel in k]
     assert len(counts) == 1
     assert counts[0][0] <= limit and counts[0][1] == 0, counts
+
+
+@pytest.mark.parametrize("kernel", ["k_score_anyILi1EfLi12ELi1EE", "k_score_anyILi2EfLi12ELi1EE",       # fp32 wider than 128: one wave
+                                    "k_score_anyILi1EfLi16ELi1EE", "k_score_anyILi2EfLi16ELi1EE"])
+def test_scalar_registers_of_a_single_wave(registers, kernel):
+    """Where one wave has a SIMD to itself nothing hides the reloads of what the loop over the blocks keeps in scalar registers; a
+    few that are spilled lie outside it."""
+    counts = [v for k, v in registers.items() if kernel in k]
+    assert len(counts) == 1
+    assert counts[0][2] <= 16, counts
