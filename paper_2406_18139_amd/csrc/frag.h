@@ -131,52 +131,56 @@ __device__ __forceinline__ void frag_read(const void* lds, int rg, int c16, int 
 }
 // fp32 products on the bf16 matrix instruction, which is sixteen times as fast as the fp32 one.  A float is the sum of three
 // bf16 values, each the remainder's nearest: 24 bits exactly.  Of the nine products of two such sums the six largest are
-// added up, smallest first; what is left out is at most 2^-24 of the product, with either sign, and the sum is rounded in
-// fp32 once per 32 dims of every kind where the fp32 instruction rounds once per 4 dims.  Against binary64, the largest
-// error of a cosine is 0.45 to 1 of the fp32 instruction's (8 to 128 dims; 1483 x 128: 4.1e-7, 6.9e-7), the rms of the scores' 0.45 to
-// 1.02 (1.6 to 3.6e-7, mostly the log-sum-exp's). Two steps of four floats make one step of eight
-// bf16 dims.  An infinity, or a value that rounds to one, leaves a NaN remainder: blocks whose results hold a NaN are done
-// again by the fp32 instruction.  So are all blocks of a strip with values that the parts hold only in part, or that make what
-// the streamed rows' parts leave out count (a bf16 ends at 2^-133, a third part lies 16 to 17 binades below its float): stationary
-// values other than zero below 2^-100, or above 2^100.  What is left out of streamed values below 2^-110 is then at most
-// d 2^(100 - 134) of a logit.  (16 x 900 x 128, keys of 2^-122 and queries of 2^122, scores rms against binary64: 2.1e-5
-// without this rule, 1.7e-7 with it.)
+// added up, smallest first, and the sum is rounded in fp32 once per 32 dims of every kind where the fp32 instruction rounds once
+// per 4 dims.  What is left out is just over 2^-26 of the product at most, with either sign, and nothing of a product that fits into 24
+// bits (both factors need more than 8, one more than 16).  Against binary64, 32 heads x 700 and 12 to 60 seeds of each width and
+// distribution, parts / fp32 instruction: scores rms 1.68e-7 / 1.68e-7 (8 dims), 1.70e-7 / 1.73e-7 (64), 1.70e-7 / 1.75e-7 (128), of sharp
+// softmax rows 1.9e-7 / 2.2e-7, 3.2e-7 / 6.1e-7, 3.6e-7 / 8.1e-7; the largest of a seed, on average, 8.1e-7 / 8.3e-7, 7.8e-7 / 9.4e-7,
+// 7.7e-7 / 1.07e-6; cosines rms 4.8e-8 / 5.6e-8, 2.3e-8 / 4.6e-8, 1.9e-8 / 4.4e-8.  (All nine products: the same to three digits, and 15 %
+// of the time of a 1483 x 128 layer more.)  Two steps of four floats make one step of eight bf16 dims.
+//
+// What the parts cannot hold goes to the fp32 instruction.  An infinity in a streamed row, or a value that rounds to one, leaves
+// a NaN remainder: blocks whose results hold a NaN are done again.  A strip with stationary values other than zero below
+// 2^-100, above 2^100 or NaN keeps its rows as floats from the start: a bf16 ends at 2^-133 and a third part lies 16 to 17
+// binades below its float.  What the parts leave out of streamed values below 2^-110 is then at most d 2^(100 - 134) of a logit.
+// (16 x 900 x 128, keys of 2^-122 and queries of 2^122, scores rms against binary64: 2.1e-5 without this rule, 1.7e-7 with
+// it.  16 x 1483 x 128 with such a value in every strip: 158 us, 124 without any, 177 when all strips took the fp32 instruction.)
+typedef __attribute__((ext_vector_type(4))) uint32_t frag_words;
 struct frag_split {
-    frag_bf16 p[3];
+    frag_words w[3];           // as words: selected as eight bf16 they would be taken apart
+    __device__ __forceinline__ frag_bf16 p(int n) const { return __builtin_bit_cast(frag_bf16, w[n]); }
 };
 __device__ __forceinline__ frag_split split_steps(frag_f32 lo, frag_f32 hi)
 {
     typedef __attribute__((ext_vector_type(2))) float f2;
     typedef __attribute__((ext_vector_type(2))) __bf16 b2;
-    typedef __attribute__((ext_vector_type(4))) uint32_t u4;
     frag_split s;
-    u4 w[3];
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         f2 x = i < 2 ? f2{lo[2 * i], lo[2 * i + 1]} : f2{hi[2 * i - 4], hi[2 * i - 3]};
 #pragma unroll
         for (int part = 0; part < 3; ++part) {
             const uint32_t b = __builtin_bit_cast(uint32_t, __builtin_convertvector(x, b2));
-            w[part][i] = b;
+            s.w[part][i] = b;
             x[0] -= __uint_as_float(b << 16);
             x[1] -= __uint_as_float(b & 0xffff0000u);
         }
     }
-#pragma unroll
-    for (int part = 0; part < 3; ++part) s.p[part] = __builtin_bit_cast(frag_bf16, w[part]);
     return s;
 }
 
 // A strip's stationary fragments as the products want them, and the products with a block of 32 streamed rows.
-// row(cg) and streamed(rg): this lane's rows of those groups in memory (past the end: any row), for blocks done again, which
-// in_fp32 (wave-uniform) asks for.
+// row(cg) and streamed(rg): this lane's rows of those groups in memory (past the end: any row), for blocks done again and for
+// those that in_fp32 (wave-uniform) wants from the fp32 instruction whatever the strip holds.
 template <typename T, int KS, int CG> struct frag_strip;
 template <int KS, int CG> struct frag_strip<bf16_t, KS, CG> {
     frag_bf16 s[CG][KS];
-    __device__ __forceinline__ void set(int cg, const frag_bf16 (&f)[KS])
+    __device__ __forceinline__ void set(const frag_bf16 (&f)[CG][KS])
     {
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) s[cg][ks] = f[ks];
+        for (int cg = 0; cg < CG; ++cg)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) s[cg][ks] = f[cg][ks];
     }
     template <typename Row, typename Streamed>
     __device__ __forceinline__ void multiply(const frag_bf16 (&a)[2][KS], acc_t (&acc)[2][CG], int, int, bool, Row&&, Streamed&&) const
@@ -193,14 +197,16 @@ template <int KS, int CG> struct frag_strip<bf16_t, KS, CG> {
                 for (int rg = 0; rg < 2; ++rg) acc[rg][cg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[rg][ks], s[cg][ks], acc[rg][cg], 0, 0, 0);
     }
 };
-// fp32 with a single group of stationary rows: strips so few that they do not fill the chip, where a block's latency counts and
-// the splitting of its rows only adds to it (2 heads x 256 x 64: 24.3 us the whole layer with bf16 parts, 23.5 without).
+// fp32 with a single group of stationary rows.  Up to 128 dims: strips so few that they do not fill the chip, where a block's
+// latency counts and the splitting of its rows only adds to it (2 heads x 256 x 64: 24.3 us the whole layer with bf16 parts, 23.5
+// without).  Wider rows, at any number of strips: with one group every streamed row would be split for sixteen stationary
+// ones, and two groups of 256 floats in parts take 192 registers beside the streamed 128 (not tried).
 template <int KS> struct frag_strip<float, KS, 1> {
     frag_f32 s[KS];
-    __device__ __forceinline__ void set(int, const frag_f32 (&f)[KS])
+    __device__ __forceinline__ void set(const frag_f32 (&f)[1][KS])
     {
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks) s[ks] = f[ks];
+        for (int ks = 0; ks < KS; ++ks) s[ks] = f[0][ks];
     }
     template <typename Row, typename Streamed>
     __device__ __forceinline__ void multiply(const frag_f32 (&a)[2][KS], acc_t (&acc)[2][1], int, int, bool, Row&&, Streamed&&) const
@@ -218,48 +224,81 @@ template <int KS> struct frag_strip<float, KS, 1> {
 template <int KS, int CG> struct frag_strip<float, KS, CG> {
     static constexpr int KB = (KS + 1) / 2;
     frag_split s[CG][KB];
-    bool extreme = false;                      // wave-uniform
-    __device__ __forceinline__ void set(int cg, const frag_f32 (&f)[KS])
+    bool extreme = false;                      // wave-uniform; the rows are kept as floats then, two steps in the first two parts
+    __device__ __forceinline__ void set(const frag_f32 (&f)[CG][KS])
     {
+        uint32_t low = ~0u, high = 0;          // twice the bits, without the sign, in `low` less one: a zero comes last
 #pragma unroll
-        for (int kb = 0; kb < KB; ++kb) s[cg][kb] = split_steps(f[2 * kb], 2 * kb + 1 < KS ? f[(2 * kb + 1) % KS] : frag_f32{});
-        uint32_t low = ~0u;                    // twice the bits, without the sign, less one: a zero comes last
-        float high = 0.f;
+        for (int cg = 0; cg < CG; ++cg)
 #pragma unroll
-        for (int ks = 0; ks < KS; ++ks)
+            for (int ks = 0; ks < KS; ++ks)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                low = min(low, 2 * __float_as_uint(f[ks][i]) - 1);
-                high = fmaxf(high, fabsf(f[ks][i]));
+                for (int i = 0; i < 4; ++i) {
+                    low = min(low, 2 * __float_as_uint(f[cg][ks][i]) - 1);
+                    high = max(high, 2 * __float_as_uint(f[cg][ks][i]));
+                }
+        extreme = __any(low < 2 * __float_as_uint(0x1p-100f) - 1 || high > 2 * __float_as_uint(0x1p100f));   // (NaN: high)
+#pragma unroll
+        for (int cg = 0; cg < CG; ++cg)
+#pragma unroll
+            for (int kb = 0; kb < KB; ++kb) {
+                const frag_f32 second = 2 * kb + 1 < KS ? f[cg][(2 * kb + 1) % KS] : frag_f32{};
+                if (extreme) {
+                    s[cg][kb].w[0] = __builtin_bit_cast(frag_words, f[cg][2 * kb]);
+                    s[cg][kb].w[1] = __builtin_bit_cast(frag_words, second);
+                    s[cg][kb].w[2] = frag_words{};
+                } else {
+                    s[cg][kb] = split_steps(f[cg][2 * kb], second);
+                }
             }
-        extreme = extreme || __any(low < 2 * __float_as_uint(0x1p-100f) - 1 || high > 0x1p100f);
     }
     template <typename Row, typename Streamed>
     __device__ __forceinline__ void multiply(const frag_f32 (&a)[2][KS], acc_t (&acc)[2][CG], int q4, int d, bool in_fp32, Row&& row, Streamed&& streamed) const
     {
-        constexpr int of_a[6] = {0, 2, 1, 0, 1, 0}, of_s[6] = {2, 0, 1, 1, 0, 0};
+        if (__builtin_expect(extreme, 0)) {    // known beforehand: no parts, and all the rows are in registers
 #pragma unroll
-        for (int rg = 0; rg < 2; ++rg) {
-            frag_split t[KB];
+            for (int cg = 0; cg < CG; ++cg)
 #pragma unroll
-            for (int kb = 0; kb < KB; ++kb) t[kb] = split_steps(a[rg][2 * kb], 2 * kb + 1 < KS ? a[rg][(2 * kb + 1) % KS] : frag_f32{});
+                for (int rg = 0; rg < 2; ++rg) acc[rg][cg] = acc_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int cg = 0; cg < CG; ++cg) acc[rg][cg] = acc_t{0.f, 0.f, 0.f, 0.f};
+            for (int ks = 0; ks < KS; ++ks) {
 #pragma unroll
-            for (int n = 0; n < 6; ++n)
+                for (int i = 0; i < 4; ++i)
 #pragma unroll
-                for (int kb = 0; kb < KB; ++kb)
+                    for (int cg = 0; cg < CG; ++cg) {
+                        const frag_f32 y = __builtin_bit_cast(frag_f32, s[cg][ks / 2].w[ks % 2]);
 #pragma unroll
-                    for (int cg = 0; cg < CG; ++cg)
-                        acc[rg][cg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t[kb].p[of_a[n]], s[cg][kb].p[of_s[n]], acc[rg][cg], 0, 0, 0);
+                        for (int rg = 0; rg < 2; ++rg) acc[rg][cg] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[rg][ks][i], y[i], acc[rg][cg], 0, 0, 0);
+                    }
+            }
+            return;
         }
-        bool nan = false;
+        if (__builtin_expect(!in_fp32, 1)) {
+            constexpr int of_a[6] = {0, 2, 1, 0, 1, 0}, of_s[6] = {2, 0, 1, 1, 0, 0};
 #pragma unroll
-        for (int cg = 0; cg < CG; ++cg)
+            for (int rg = 0; rg < 2; ++rg) {
+                frag_split t[KB];
 #pragma unroll
-            for (int rg = 0; rg < 2; ++rg)
-                nan = nan || __builtin_isunordered(acc[rg][cg][0], acc[rg][cg][1]) || __builtin_isunordered(acc[rg][cg][2], acc[rg][cg][3]);
-        if (__builtin_expect(__any(nan) || extreme || in_fp32, 0)) {     // wave-uniform
+                for (int kb = 0; kb < KB; ++kb) t[kb] = split_steps(a[rg][2 * kb], 2 * kb + 1 < KS ? a[rg][(2 * kb + 1) % KS] : frag_f32{});
+#pragma unroll
+                for (int cg = 0; cg < CG; ++cg) acc[rg][cg] = acc_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int n = 0; n < 6; ++n)
+#pragma unroll
+                    for (int kb = 0; kb < KB; ++kb)
+#pragma unroll
+                        for (int cg = 0; cg < CG; ++cg)
+                            acc[rg][cg] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(t[kb].p(of_a[n]), s[cg][kb].p(of_s[n]), acc[rg][cg], 0, 0, 0);
+            }
+            bool nan = false;
+#pragma unroll
+            for (int cg = 0; cg < CG; ++cg)
+#pragma unroll
+                for (int rg = 0; rg < 2; ++rg)
+                    nan = nan || __builtin_isunordered(acc[rg][cg][0], acc[rg][cg][1]) || __builtin_isunordered(acc[rg][cg][2], acc[rg][cg][3]);
+            in_fp32 = __any(nan);
+        }
+        if (__builtin_expect(in_fp32, 0)) {                              // wave-uniform
 #pragma unroll
             for (int cg = 0; cg < CG; ++cg)
 #pragma unroll

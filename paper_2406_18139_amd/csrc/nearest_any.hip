@@ -102,12 +102,10 @@ k_nearest_any(const T* __restrict__ k, const float* __restrict__ rnorm, const in
         }
         frag_wait_loads();
         __syncthreads();
+        frag_t f[CG][KS];
 #pragma unroll
-        for (int cg = 0; cg < CG; ++cg) {
-            frag_t f[KS];
-            frag_read<T, KS>(&blocks[0][0], cg, c16, q4, d, f);
-            strip.set(cg, f);
-        }
+        for (int cg = 0; cg < CG; ++cg) frag_read<T, KS>(&blocks[0][0], cg, c16, q4, d, f[cg]);
+        strip.set(f);
         __syncthreads();
     }
     float rn = 0.f;

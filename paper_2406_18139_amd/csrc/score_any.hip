@@ -148,12 +148,10 @@ k_score_any(const T* __restrict__ q, const T* __restrict__ k, int heads, int gro
             frag_load_rows<T, KS, PART>(srsrc, d, &blocks[0][0] + wave * PART * RB, lane, off, min(s0 + wave * PART, L - 1), L - min(s0 + wave * PART, L - 1));
         frag_wait_loads();
         __syncthreads();
+        frag_t f[CG][KS];
 #pragma unroll
-        for (int cg = 0; cg < CG; ++cg) {
-            frag_t f[KS];
-            frag_read<T, KS>(&blocks[0][0], cg, c16, q4, d, f);
-            strip.set(cg, f);
-        }
+        for (int cg = 0; cg < CG; ++cg) frag_read<T, KS>(&blocks[0][0], cg, c16, q4, d, f[cg]);
+        strip.set(f);
         __syncthreads();
     }
 

@@ -132,6 +132,60 @@ def test_fp32_products_from_bf16_parts(d, what):
     np.testing.assert_allclose(sm[0].cpu().numpy(), s1[0].cpu().numpy(), rtol=1e-5, atol=1e-6)
 
 
+def small_value_in_every_strip(x, rows=None):
+    """One value that bf16 parts hold only in part in every 32 rows, in the second sixteen of some and the first of others."""
+    rows = torch.arange(x.shape[1]) if rows is None else rows
+    x[:, rows[5::64], 0] = 2.0 ** -105
+    x[:, rows[51::64], 1] = -2.0 ** -105
+    return x
+
+
+@pytest.mark.parametrize("d", [8, 24, 56, 64, 104, 128])
+def test_fp32_strips_that_bf16_parts_do_not_hold(d):
+    """Strips of 32 rows with such a value multiply floats, like strips of 16 rows: the same instruction in the same order, so
+    the same bits.  A strip with a NaN row does too, and nothing else changes for it."""
+    L, H = 203, 40
+    g = torch.Generator().manual_seed(d)
+    q, k = (small_value_in_every_strip(torch.randn(1, L, d, generator=g)) for _ in range(2))
+    for nan_rows in ([], [77, 150]):
+        q[:, nan_rows] = float("nan")
+        one = lookm.lookm_scores(q.cuda(), k.cuda())
+        many = lookm.lookm_scores(q.repeat(H, 1, 1).cuda(), k.repeat(H, 1, 1).cuda())
+        assert torch.equal(many.nan_to_num(-1), one.nan_to_num(-1).expand_as(many))
+        assert torch.isnan(many).sum() == H * ((nan_rows[-1] + 1) if nan_rows else 0)
+    kept, ev = torch.arange(0, L, 3, dtype=torch.int32)[None], torch.tensor([i for i in range(L) if i % 3], dtype=torch.int32)[None]
+    big = 80                                                  # 135 evicted keys: five strips of 32 a head
+    plain = torch.randn(1, L, d, generator=g)
+    short = plain.clone()
+    short[:, ::3] *= 2.0 ** -120
+    for k in (small_value_in_every_strip(plain, ev[0].long()), short):      # short conserved keys beside longer evicted ones
+        a1, s1 = lookm.lookm_nearest(k.cuda(), kept.cuda(), ev.cuda())
+        am, sm = lookm.lookm_nearest(k.repeat(big, 1, 1).cuda(), kept.repeat(big, 1).cuda(), ev.repeat(big, 1).cuda())
+        assert torch.equal(am, a1.expand_as(am)) and torch.equal(sm, s1.expand_as(sm))
+
+
+def test_fp32_strips_known_to_need_floats_skip_the_parts():
+    """Such strips cost what the fp32 instruction costs, 1.5 times the parts' time at 128 dims (with the parts first and the rows
+    from memory again: 3.6 times)."""
+    H, L, d = 16, 1483, 128
+    g = torch.Generator().manual_seed(0)
+    plain = [torch.randn(H, L, d, generator=g).cuda() for _ in range(2)]
+    small = [small_value_in_every_strip(x.clone()) for x in plain]
+    ws = lookm.alloc_workspace(H, L, d, 0, lookm.F32, "cuda")
+    times = {}
+    for _ in range(5):
+        for name, (q, k) in (("plain", plain), ("small", small)):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            lookm.lookm_scores(q, k, workspace=ws)
+            begin.record()
+            for _ in range(20):
+                lookm.lookm_scores(q, k, workspace=ws)
+            end.record()
+            end.synchronize()
+            times[name] = min(times.get(name, float("inf")), begin.elapsed_time(end))
+    assert times["small"] < 2.2 * times["plain"], times
+
+
 @pytest.mark.parametrize("d,dtype", [(64, BF), (80, BF), (256, BF), (24, F32), (128, F32)])
 def test_scores_logits_that_jump_late_in_the_row(d, dtype):
     # the twin of the test of that name for bf16 x 128: a block more than 64 binades above the row's reference makes pass 1
