@@ -301,7 +301,10 @@ k_merge(const T* __restrict__ k, const T* __restrict__ v, const int32_t* __restr
 // The same without the sort, for short lists: a wave looks after 64 / G consecutive slots, goes through the head's whole
 // assignment list by itself, collects the few entries of its slots, in order, and sorts those in LDS.  All of it is a chain of
 // memory latencies; this one is a kernel and four barriers shorter (2 heads x 256 x 64 fp32, the whole layer: 27.0 -> 23.5 us).
-constexpr int DIRECT_MAX = 1024;
+// Members are added up by the slot's lane group, up to SHARED of them: one after the other they would make the largest set the
+// time of the kernel.  (8 heads, 1020 members on 256 slots x 128 bf16, us, a slot's own lane group for all / shared: all in one
+// set 176 / 45, half of them 93 / 28, even sets 7.6 / 7.3; with a sort and a lane group per slot 171, 89, 10.6.)
+constexpr int DIRECT_MAX = 1024, SHARED = 32;
 template <typename T, int NB>
 __global__ void __launch_bounds__(256)
 k_merge_direct(const T* __restrict__ k, const T* __restrict__ v, const int32_t* __restrict__ kept, const int32_t* __restrict__ evicted,
@@ -362,41 +365,62 @@ k_merge_direct(const T* __restrict__ k, const T* __restrict__ v, const int32_t* 
         __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
-    if (s0 + g >= B || c0 >= d) return;
-    k += (size_t)h * L * d + c0;
-    v += (size_t)h * L * d + c0;
+    const int cc = (c0 < d) ? c0 : 0;
+    k += (size_t)h * L * d + cc;
+    v += (size_t)h * L * d + cc;
     raw8<T> own_k, own_v;
     own_k.load(k + (size_t)pos * d);
     own_v.load(v + (size_t)pos * d);
     float sk[8], sv[8];
+    auto add_up = [&](int t, int t_end) {               // ascending position; a short last batch repeats the last member
 #pragma unroll
-    for (int i = 0; i < 8; ++i) sk[i] = sv[i] = 0.f;
-    const int t0 = first[wave][g], t1 = first[wave][g + 1];
-    for (int t = t0; t < t1; t += NB) {                 // ascending position; a short last batch repeats the last member
-        raw8<T> xk[NB], xv[NB];
-        float w[NB];
+        for (int i = 0; i < 8; ++i) sk[i] = sv[i] = 0.f;
+        for (; t < t_end; t += NB) {
+            raw8<T> xk[NB], xv[NB];
+            float w[NB];
 #pragma unroll
-        for (int j = 0; j < NB; ++j) {
-            const int tt = min(t + j, t1 - 1), p = member_pos[wave][tt];
-            xk[j].load(k + (size_t)p * d);
-            xv[j].load(v + (size_t)p * d);
-            w[j] = (mode == LOOKM_MERGE_WEIGHTED) ? member_w[wave][tt] : 1.0f;
-        }
-#pragma unroll
-        for (int j = 0; j < NB; ++j)
-            if (t + j < t1) {
-                float e[8];
-                xk[j].get(e);
-#pragma unroll
-                for (int i = 0; i < 8; ++i) sk[i] = fmaf(e[i], w[j], sk[i]);
-                xv[j].get(e);
-#pragma unroll
-                for (int i = 0; i < 8; ++i) sv[i] = fmaf(e[i], w[j], sv[i]);
+            for (int j = 0; j < NB; ++j) {
+                const int tt = min(t + j, t_end - 1), p = member_pos[wave][tt];
+                xk[j].load(k + (size_t)p * d);
+                xv[j].load(v + (size_t)p * d);
+                w[j] = (mode == LOOKM_MERGE_WEIGHTED) ? member_w[wave][tt] : 1.0f;
             }
-    }
+#pragma unroll
+            for (int j = 0; j < NB; ++j)
+                if (t + j < t_end) {
+                    float e[8];
+                    xk[j].get(e);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) sk[i] = fmaf(e[i], w[j], sk[i]);
+                    xv[j].get(e);
+#pragma unroll
+                    for (int i = 0; i < 8; ++i) sv[i] = fmaf(e[i], w[j], sv[i]);
+                }
+        }
+    };
+    const int n = first[wave][g + 1] - first[wave][g];
     const size_t out_off = ((size_t)h * B + slot) * d + c0;
-    merged_row(own_k, sk, t1 - t0, mode, k_out + out_off);
-    merged_row(own_v, sv, t1 - t0, mode, v_out + out_off);
+    const bool writes = s0 + g < B && c0 < d;
+    // A set of more than SHARED members is added up by all the wave's lane groups, a stretch by each.
+    for (uint64_t large = __ballot(n > SHARED); large != 0;) {
+        const int at = __builtin_ctzll(large) / G, t0 = first[wave][at], t1 = first[wave][at + 1], per = (t1 - t0 + slots - 1) / slots;
+        large &= ~0ull << at * G << (G - 1) << 1;
+        add_up(t0 + g * per, min(t0 + g * per + per, t1));
+        for (int step = G; step < 64; step <<= 1)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                sk[i] += __shfl_xor(sk[i], step);
+                sv[i] += __shfl_xor(sv[i], step);
+            }
+        if (g == at && writes) {
+            merged_row(own_k, sk, n, mode, k_out + out_off);
+            merged_row(own_v, sv, n, mode, v_out + out_off);
+        }
+    }
+    if (n > SHARED || !writes) return;
+    add_up(first[wave][g], first[wave][g + 1]);
+    merged_row(own_k, sk, n, mode, k_out + out_off);
+    merged_row(own_v, sv, n, mode, v_out + out_off);
 }
 
 }  // namespace lookm
@@ -455,7 +479,7 @@ int launch_merge(const void* k, const void* v, const int32_t* kept, const int32_
     if (Le == 0) mode = LOOKM_MERGE_NONE;
     const int G = 1 << merge_lanes(d);
     // Without a sort where that is shorter: up to 2048 waves (two a SIMD), each of which goes through the list by itself, and
-    // sets of four members on average (a lane group per slot: the largest set sets the time).  Sort and merge against the
+    // sets of four members on average.  Sort and merge against the
     // direct kernel in us (20 calls in a graph): 38 waves, 102 entries in 154 slots 8.0 / 4.6; 400, 500 in 200 10.2 / 8.8;
     // 1600, 500 in 200 10.9 / 9.3; 2244, 922 in 561 11.9 / 12.2; 8976, 922 in 561 21.4 / 22.1; 800, 400 in 100 11.1 / 10.6;
     // 360, 1020 in 180 12.2 / 12.5; 120, 540 in 60 12.1 / 14.4; 640, 1020 in 80 15.1 / 20.5.  A lane group has eight lanes and

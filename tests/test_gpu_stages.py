@@ -521,6 +521,59 @@ def test_merge_with_and_without_a_sort(d, dtype, B, Le):
             assert np.abs(ko[h].float().cpu().numpy() - ref).max() < (2e-2 if dtype == torch.bfloat16 else 1e-4)
 
 
+@pytest.mark.parametrize("d,dtype", [(64, torch.float32), (64, torch.bfloat16), (104, torch.bfloat16), (256, torch.float32)])
+@pytest.mark.parametrize("sizes", [[33, 32, 0, 65, 31, 200, 1, 40], [0, 0, 0, 0, 0, 0, 0, 700], [64, 64, 64, 64, 64, 64, 64, 64]])
+def test_large_sets_without_a_sort(d, dtype, sizes):
+    """Sets of more than 32 members are shared out to a wave's two to eight lane groups.  Slots 0 to 7 and the last eight have
+    the given sizes (those of one wave at 64 dims), the others share the rest.  fp32 sums of n terms below 6 in any order are
+    within n 2^-23 6 of each other; a bf16 row is rounded once more, 2^-8 of its value."""
+    B, Le = 301, 1017
+    L = B + Le
+    g = torch.Generator().manual_seed(d)
+    k, v = torch.randn(2, L, d, generator=g).to(dtype), torch.randn(2, L, d, generator=g).to(dtype)
+    perm = torch.stack([torch.randperm(L, generator=g) for _ in range(2)])
+    kept, ev = perm[:, :B].sort(1)[0].int(), perm[:, B:].sort(1)[0].int()
+    assign = torch.randint(8, B - 8, (2, Le), generator=g).int()
+    for h, base in ((0, 0), (1, B - 8)):
+        at = torch.randperm(Le, generator=g)
+        for slot, n in enumerate(sizes):
+            assign[h, at[:n]], at = base + slot, at[n:]
+    sim = torch.rand(2, Le, generator=g)
+    args = (k, v, kept, ev, assign, sim)
+    for mode in ("averaged", "pivotal", "weighted"):
+        got = lookm.lookm_merge(*(x.cuda() for x in args), mode)
+        for x, out in zip((k, v), got):
+            for h in range(2):
+                ref = torch.from_numpy(oracle.merge(x[h].float().numpy(), *(y[h].numpy() for y in (kept, ev, assign, sim)), mode))
+                bound = max(sizes) * 2.0 ** -23 * 6 + (2.0 ** -8 * ref.abs() if dtype == torch.bfloat16 else 0.0)
+                assert ((out[h].double().cpu() - ref).abs() <= bound + 1e-6).all()
+
+
+def test_one_large_set_does_not_set_the_time_of_a_merge():
+    """1020 members in one set against as many on 256 slots: four times the time with the launch (18 times if the set's own lane
+    group adds them all up)."""
+    H, B, Le, d = 8, 256, 1020, 128
+    L = B + Le
+    g = torch.Generator().manual_seed(5)
+    k, v = (torch.randn(H, L, d, generator=g).bfloat16().cuda() for _ in range(2))
+    perm = torch.stack([torch.randperm(L, generator=g) for _ in range(H)])
+    kept, ev = perm[:, :B].sort(1)[0].int().cuda(), perm[:, B:].sort(1)[0].int().cuda()
+    sim = torch.rand(H, Le, generator=g).cuda()
+    assigns = {"even": torch.randint(0, B, (H, Le), generator=g).int().cuda(), "one": torch.full((H, Le), 100, dtype=torch.int32).cuda()}
+    times = {}
+    for _ in range(5):
+        for name, assign in assigns.items():
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            lookm.lookm_merge(k, v, kept, ev, assign, sim, "weighted")
+            begin.record()
+            for _ in range(20):
+                lookm.lookm_merge(k, v, kept, ev, assign, sim, "weighted")
+            end.record()
+            end.synchronize()
+            times[name] = min(times.get(name, float("inf")), begin.elapsed_time(end))
+    assert times["one"] < 7 * times["even"], times
+
+
 @pytest.mark.parametrize("L", [1, 64, 255, 256, 257, 511, 512, 513, 1023, 1024, 1025, 2047, 2048, 2049])
 @pytest.mark.parametrize("what", ["spread", "equal", "crowded"])
 def test_selection_at_the_edges_of_its_workgroup_sizes(L, what):
