@@ -56,11 +56,12 @@ __device__ __forceinline__ void lse_update(const acc_t (&acc)[2][CG], float scal
 #pragma unroll
             for (int i = 1; i < 8; ++i) bm = fmaxf(bm, acc[i >> 2][cg][i & 3]);
             const float mn = fmaxf(m[cg], bm * scale2);
-            sum[cg] = 0.f;
+            float s = 0.f;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) sum[cg] += __builtin_amdgcn_exp2f(fmaf(acc[i >> 2][cg][i & 3], scale2, -mn));
-            l[cg] *= __builtin_amdgcn_exp2f(m[cg] - mn);
+            for (int i = 0; i < 8; ++i) s += __builtin_amdgcn_exp2f(fmaf(acc[i >> 2][cg][i & 3], scale2, -mn));
+            l[cg] = fmaf(l[cg], __builtin_amdgcn_exp2f(m[cg] - mn), s);
             m[cg] = mn;
+            sum[cg] = 0.f;     // in l already, with one rounding
         }
     }
 #pragma unroll

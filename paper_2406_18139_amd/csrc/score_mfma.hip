@@ -93,13 +93,14 @@ __device__ __forceinline__ void lse_refresh(const f32x4& lo, const f32x4& hi, fl
 {
     const float bm = fmaxf(fmaxf(fmaxf(fmaxf(lo[0], lo[1]), lo[2]), fmaxf(fmaxf(lo[3], hi[0]), hi[1])), fmaxf(hi[2], hi[3]));
     const float mn = fmaxf(m, bm * scale2);
-    sum = 0.f;
+    float s = 0.f;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) sum += __builtin_amdgcn_exp2f(fmaf(lo[i], scale2, -mn));
+    for (int i = 0; i < 4; ++i) s += __builtin_amdgcn_exp2f(fmaf(lo[i], scale2, -mn));
 #pragma unroll
-    for (int i = 0; i < 4; ++i) sum += __builtin_amdgcn_exp2f(fmaf(hi[i], scale2, -mn));
-    l *= __builtin_amdgcn_exp2f(m - mn);
+    for (int i = 0; i < 4; ++i) s += __builtin_amdgcn_exp2f(fmaf(hi[i], scale2, -mn));
+    l = fmaf(l, __builtin_amdgcn_exp2f(m - mn), s);
     m = mn;
+    sum = 0.f;                 // in l already, with one rounding
 }
 
 __device__ __forceinline__ void lse_block_epilogue(const f32x4 (&acc)[2][4], float scale2, float (&m)[4], float (&l)[4])
@@ -688,23 +689,26 @@ k_score_combine(int group, int L, int R0, int C, const float* __restrict__ part_
     // heads on 8 key heads x 6144 11.5 -> 7.3.)
     constexpr int AHEAD = 8;
     if (PASS == 1) {
-        float M = -1e30f, Ls = 0.f;
+        float M = -1e30f, Ls = 0.f, a[AHEAD], b[AHEAD];
+        for (int c0 = AHEAD; c0 < nc; c0 += AHEAD) {         // the largest reference of all chunks before any sum, so that none is rescaled
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) a[i] = pa[(size_t)min(c0 + i, nc - 1) * stride];
+#pragma unroll
+            for (int i = 0; i < AHEAD; ++i) M = fmaxf(M, a[i]);
+        }
         for (int c0 = 0; c0 < nc; c0 += AHEAD) {
-            float a[AHEAD], b[AHEAD];
 #pragma unroll
             for (int i = 0; i < AHEAD; ++i) {
                 const size_t at = (size_t)min(c0 + i, nc - 1) * stride;
                 a[i] = pa[at];
                 b[i] = pb[at];
             }
-            float top = M;
+            if (c0 == 0)
 #pragma unroll
-            for (int i = 0; i < AHEAD; ++i) top = fmaxf(top, a[i]);
-            if (c0 > 0) Ls *= exp2f(M - top);
+                for (int i = 0; i < AHEAD; ++i) M = fmaxf(M, a[i]);
 #pragma unroll
             for (int i = 0; i < AHEAD; ++i)
-                if (c0 + i < nc) Ls = fmaf(b[i], exp2f(a[i] - top), Ls);
-            M = top;
+                if (c0 + i < nc) Ls = fmaf(b[i], exp2f(a[i] - M), Ls);
         }
         out[(size_t)h * L + row] = M + log2f(Ls);
     } else {
