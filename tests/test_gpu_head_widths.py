@@ -132,6 +132,27 @@ def test_fp32_products_from_bf16_parts(d, what):
     np.testing.assert_allclose(sm[0].cpu().numpy(), s1[0].cpu().numpy(), rtol=1e-5, atol=1e-6)
 
 
+@pytest.mark.parametrize("d", [8, 24, 64, 128])
+@pytest.mark.parametrize("sharp", [1.0, 4.0])
+def test_fp32_products_from_parts_are_no_further_off(d, sharp):
+    """Scores against binary64, sixteen heads at once (strips of 32 rows, bf16 parts) and the same heads one by one (strips of 16,
+    the fp32 instruction), over 45000 scores: the rms of the first is not above the second's (a sample's scatter is 0.5 %), nor,
+    on average over the heads, is the largest error of a head (2 to 4 %)."""
+    H, L = 16, 700
+    rms, largest = torch.zeros(2, dtype=torch.double), torch.zeros(2, dtype=torch.double)
+    for seed in range(4):
+        g = torch.Generator().manual_seed(10 * d + seed)
+        q, k = (torch.randn(H, L, d, generator=g).cuda() for _ in range(2))
+        q *= sharp
+        logits = torch.stack([q[h].double() @ k[h].double().t().contiguous() for h in range(H)]) / d ** 0.5
+        ref = torch.softmax(logits.masked_fill_(torch.ones(L, L, device="cuda").triu(1).bool(), -float("inf")), 2).sum(1)
+        for i, got in enumerate((lookm.lookm_scores(q, k), torch.cat([lookm.lookm_scores(q[h:h + 1], k[h:h + 1]) for h in range(H)]))):
+            error = ((got.double() - ref) / ref).cpu()
+            rms[i] += error.pow(2).mean()
+            largest[i] += error.abs().amax(1).mean()
+    assert rms[0].sqrt() <= 1.01 * rms[1].sqrt() and largest[0] <= 1.05 * largest[1], (rms.sqrt(), largest)
+
+
 def small_value_in_every_strip(x, rows=None):
     """One value that bf16 parts hold only in part in every 32 rows, in the second sixteen of some and the first of others."""
     rows = torch.arange(x.shape[1]) if rows is None else rows
