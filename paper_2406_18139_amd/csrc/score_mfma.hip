@@ -689,27 +689,33 @@ k_score_combine(int group, int L, int R0, int C, const float* __restrict__ part_
     // heads on 8 key heads x 6144 11.5 -> 7.3.)
     constexpr int AHEAD = 8;
     if (PASS == 1) {
-        float M = -1e30f, Ls = 0.f, a[AHEAD], b[AHEAD];
-        for (int c0 = AHEAD; c0 < nc; c0 += AHEAD) {         // the largest reference of all chunks before any sum, so that none is rescaled
+        float M = -1e30f, Ls = 0.f;
+        auto fold = [&](auto ahead) {
+            constexpr int N = decltype(ahead)::value;
+            float a[N], b[N];
+            for (int c0 = N; c0 < nc; c0 += N) {             // the largest reference of all chunks before any sum, so that none is rescaled
 #pragma unroll
-            for (int i = 0; i < AHEAD; ++i) a[i] = pa[(size_t)min(c0 + i, nc - 1) * stride];
+                for (int i = 0; i < N; ++i) a[i] = pa[(size_t)min(c0 + i, nc - 1) * stride];
 #pragma unroll
-            for (int i = 0; i < AHEAD; ++i) M = fmaxf(M, a[i]);
-        }
-        for (int c0 = 0; c0 < nc; c0 += AHEAD) {
-#pragma unroll
-            for (int i = 0; i < AHEAD; ++i) {
-                const size_t at = (size_t)min(c0 + i, nc - 1) * stride;
-                a[i] = pa[at];
-                b[i] = pb[at];
+                for (int i = 0; i < N; ++i) M = fmaxf(M, a[i]);
             }
-            if (c0 == 0)
+            for (int c0 = 0; c0 < nc; c0 += N) {
 #pragma unroll
-                for (int i = 0; i < AHEAD; ++i) M = fmaxf(M, a[i]);
+                for (int i = 0; i < N; ++i) {
+                    const size_t at = (size_t)min(c0 + i, nc - 1) * stride;
+                    a[i] = pa[at];
+                    b[i] = pb[at];
+                }
+                if (c0 == 0)
 #pragma unroll
-            for (int i = 0; i < AHEAD; ++i)
-                if (c0 + i < nc) Ls = fmaf(b[i], exp2f(a[i] - M), Ls);
-        }
+                    for (int i = 0; i < N; ++i) M = fmaxf(M, a[i]);
+#pragma unroll
+                for (int i = 0; i < N; ++i)
+                    if (c0 + i < nc) Ls = fmaf(b[i], exp2f(a[i] - M), Ls);
+            }
+        };
+        if (nc <= AHEAD) fold(std::integral_constant<int, AHEAD>{});
+        else fold(std::integral_constant<int, 2 * AHEAD>{});         // (more than one round trip costs a second one for the references)
         out[(size_t)h * L + row] = M + log2f(Ls);
     } else {
         float sum = 0.f;
