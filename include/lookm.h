@@ -142,7 +142,12 @@ int lookm_compress(const void* q, const void* k, const void* v, const uint8_t* m
 /*
  * Eq. 4: scores_out[h, j] = sum over rows i >= j of exp(q_i.k_j/sqrt(d) - lse_i), where lse_i is the
  * log-sum-exp of row i over columns <= i.  Two flash-style passes over Q K^T (row log-sum-exp, then
- * column sums), on the matrix cores with fp32 accumulation (fp32 inputs: fp32 products).
+ * column sums), on the matrix cores with fp32 accumulation.
+ *   fp32 inputs, d <= 128, from 256 strips of 32 rows on (H * ceil(rows / 32), rows = L or the observation window): every
+ *   product is the sum of six products of bf16 parts of the two values, exact to just over 2^-26 of it, with either sign; fewer
+ *   strips, wider heads and values that parts do not hold take the fp32 matrix instruction.  lookm_nearest likewise, by the
+ *   strips of evicted keys.  So the same head may differ in its last bits alone and among many; against binary64 the first way
+ *   is no further off (scores about 1.7e-7 rms and 1.3e-6 at most, both ways; less than the second way for sharp softmax rows).
  *   Attention weights below 2^-126 count as zero for bf16 with d = 128 and are kept, down to 2^-149, for other shapes.
  *   scores_out  device, float [H, L].
  */

@@ -108,8 +108,8 @@ __device__ __forceinline__ void frag_load_rows(__amdgpu_buffer_rsrc_t rsrc, int 
 // The fragments of rows 16*rg + c of a block.  Past the head width they are zeros like the stationary operand's: what the
 // block repeats there may hold an infinity, and 0 * inf would turn a logit of -inf into NaN.  Only the steps past the next
 // smaller fragment can hold such dims.  The words are selected whole: selected as eight bf16 the compiler takes them
-// apart and puts them together again, two instructions a word in every block (32 x 2781 x 72: 143 us the whole layer, 133 at 72
-// as whole words).
+// apart and puts them together again, two instructions a word in every block (32 x 2781 x 72: 143 us the whole layer, 121 with
+// whole words).
 template <int KS> constexpr int frag_full_steps() { return KS <= 4 ? KS - 1 : KS <= 8 ? KS - 2 : KS - 4; }     // see with_frag_shape
 template <typename T, int KS>
 __device__ __forceinline__ void frag_read(const void* lds, int rg, int c16, int q4, int d, typename frag<T>::type (&a)[KS])
@@ -349,12 +349,13 @@ __device__ __forceinline__ void inverse_norms(const T* __restrict__ k, size_t ro
 }
 
 // Calls f(steps, groups) with integral constants: the steps of a fragment that hold d dims, and how many groups of 16
-// stationary rows a wave keeps in registers next to them: as many as 64 registers hold (at most 4 groups, 2 for fp32,
-// whose matrix instructions take eight times as long per LDS byte) - or a single group where such strips would leave
-// most of the chip idle: strips(rows per strip), fewer than one per compute unit.  The score passes count the strips of
+// stationary rows a wave keeps in registers next to them: as many as 64 registers hold as they are stored (at most 4 groups, 2
+// for fp32, whose parts take half as much again: 96 at 128 dims) - or a single group where such strips would leave most of the
+// chip idle: strips(rows per strip), fewer than one per compute unit.  The score passes count the strips of
 // the query heads for both: with grouped heads pass 2 has fewer workgroups than that, each with several heads to go
-// through (32 query heads on 8 key heads x 700 x 64 bf16: 88 for 256 compute units; not tuned).  (A 256-token fp32 prompt of 2 x 64: score passes and matching 21 us with two groups, 16 us with one; 1483 tokens of 16 x 128, 750
-// workgroups: 163 us with two groups, 168 us with one, and a tenth of the LDS traffic more per flop than that shows.)
+// through (32 query heads on 8 key heads x 700 x 64 bf16: 88 for 256 compute units; not tuned).  (All on the fp32
+// instruction, a 256-token fp32 prompt of 2 x 64: score passes and matching 21 us with two groups, 16 us with one; 1483 tokens
+// of 16 x 128, 750 workgroups: 163 us with two groups, 168 us with one.)
 template <typename T, typename Strips, typename F>
 inline void with_frag_shape(int d, Strips&& strips, F&& f)
 {

@@ -15,9 +15,10 @@
 // not hang on the instruction's shape, and a merged row that went to another key would differ visibly.  Two lanes' best
 // values are settled by one thread of the key.  Where there may be a third value, or a lane's second, the workgroup goes through
 // all the slots of the lanes whose best value is close enough: rare, except among keys that are copies of each other.
-// Bound like the score passes, by the fp32 matrix instruction or (bf16) by the five vector operations per element of the
-// running maxima.  With the key norms, 922 evicted x 561 conserved keys of 16 x 128 fp32: 42 us (on the vector ALU 93 us);
-// 1843 x 938 of 32 x 64 bf16: 32 us (126 us; 35 us with both slots of a lane's best two kept, nine operations); the same
+// Bound like the score passes by the splitting of the streamed rows (fp32; the vector ALU is busy 52 % of the time at 128 dims and
+// 38 % of it is spent waiting) or by the five vector operations per element of the running maxima (bf16, 67 % at 64 dims).
+// 922 evicted x 561 conserved keys of 16 x 128 fp32: 30 us (39 on the fp32 instruction, 93 on the vector ALU); 1843 x 938 of
+// 32 x 64 bf16: 24 us (126 on the vector ALU; three more with both slots of a lane's best two kept, nine operations); the same
 // with some fifteen copies of every image key, so that all keys are looked through again: 280 us (120 us).
 #include "frag.h"
 
@@ -189,7 +190,7 @@ k_nearest_any(const T* __restrict__ k, const float* __restrict__ rnorm, const in
     int s = found.s1;
     // A sum of d products in any order, roundings to nearest or towards zero, is off by at most d 2^-23 |e| |c|, the chain of fused
     // multiply-adds by half of that, and the factor 1 / |c| adds a rounding to each: two values that the other order can swap
-    // are within 6 (d + 1) 2^-24 |e| of each other (|e| = 1 / e_rn).  fp32 products from bf16 parts leave out 2^-24 |e| |c| and
+    // are within 6 (d + 1) 2^-24 |e| of each other (|e| = 1 / e_rn).  fp32 products from bf16 parts leave out less than 2^-24 |e| |c| and
     // add up their small parts, five times d terms of at most 2^-7 |e| |c| together, first: (7 d + 8) 2^-24.  A key of norm zero has all values zero in every order.
     // A bound, not an estimate: with d = 64 it sends a few keys in a hundred to the second look, and about one in a thousand
     // because of a third value (or of two in one lane) through a sixteenth of the slots or a few.

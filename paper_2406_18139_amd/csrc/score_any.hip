@@ -13,13 +13,15 @@
 // kernel behind them, leaves short strips (64 rows; 32 or 16 in fp32), so that a few hundred tokens already make
 // enough workgroups, and nothing is written but the result.
 //
-// What bounds it: bf16 - the vector ALU, busy 83 % of the time in pass 1 and 77 % in pass 2 with an exponential and its two
-// companions per logit; fp32 - the same unit, with the splitting of every streamed row into bf16 parts for every strip (five and
-// a half instructions a float), and the longest strips, which run alone for the last fifth of the time.  Both passes over
-// 16 heads x 1483 x 128 fp32: 80 us (105 us on the fp32 matrix instruction, beside which the vector ALU stands still; on the
-// vector ALU, with 64 x 64 tiles in LDS: 685 us); over 32 x 2781 x 64 bf16: 55 us (790 us); over 2 x 256 x 64 fp32: 10 us
-// (64 us).  Stationary rows through LDS, blocks through a buffer descriptor, log-sum-exps straight to LDS, the first block of
-// a wave without a sum against a reference that it has not got: from 121 and 62 us.
+// What bounds it: bf16 - the vector ALU, busy 80 % of the time in pass 1 and 75 % in pass 2 at 64 dims with an exponential and its
+// two companions per logit.  fp32 - the splitting of every streamed row into bf16 parts for every strip (five and a half
+// instructions a float): at 64 dims and four waves a SIMD the vector ALU is busy 86 % (pass 1); at 128, two waves, 62 % and the
+// matrix pipe 35 %, 86 % of the time one or both, and the longest strips run alone for the last fifth.  Both passes, traced:
+// 16 heads x 1483 x 128 fp32 87 us (82 timed with events; 126 on the fp32 matrix instruction, beside which the vector ALU stands
+// still; 685 on the vector ALU, with 64 x 64 tiles in LDS), 32 x 2781 x 64 bf16 60 us (790), x 80 74 us, 2 x 256 x 64 fp32
+// 10 us (64).  Stationary rows through LDS, blocks through a buffer descriptor, log-sum-exps straight to LDS and the first block
+// of a wave without a sum against a reference that it has not got, all timed with events: 121 -> 105 us for the first (on the
+// fp32 instruction), 62 -> 55 for the second.
 // (Tried: every other 32 workgroups of an XCD in the opposite order, so that long strips meet short ones on a compute unit:
 // no gain, the third lot undoes it; fp32 blocks of 16 rows, three workgroups a compute unit: pass 1 52 -> 56 us.)
 #include "frag.h"

@@ -59,7 +59,7 @@ k_select(const float* __restrict__ scores, const uint8_t* __restrict__ mask, int
     constexpr int DIGIT = (SEL_THREADS == 1024) ? 12 : (SEL_THREADS == 512) ? 11 : 10, SEL_BINS = 1 << DIGIT;    // four bins a thread
     static_assert(SEL_BINS == 4 * SEL_THREADS, "");
     __shared__ int hist[SEL_BINS];
-    __shared__ uint32_t cand[SEL_CAND];     // keys that share the threshold's top 12 bits
+    __shared__ uint32_t cand[SEL_CAND];     // keys that share the threshold's first digit
     __shared__ int wtot[8][SEL_WAVES];      // one row per workgroup-wide scan
     __shared__ uint32_t wmin[SEL_WAVES], wmax[SEL_WAVES], wtmin[SEL_WAVES], wtmax[SEL_WAVES];
     __shared__ int sh_bin, sh_k, sh_ncand;
