@@ -200,8 +200,13 @@ k_merge(const T* __restrict__ k, const T* __restrict__ v, const int32_t* __restr
     __shared__ int begin[257];                                              // of the slots' members; one more: the end
     __shared__ __attribute__((aligned(16))) float slot_sum[2][256 * 8];     // sums of slots that begin inside a group's stretch
     __shared__ __attribute__((aligned(16))) float head_sum[2][256 * 8];     // .. and of the end of one that began before
-    // heads vary fastest over the grid
-    const int h = blockIdx.x, tid = threadIdx.x, G = 1 << lg_G, NG = 256 >> lg_G, grp = tid >> lg_G, s0 = (int)blockIdx.y * NG;
+    // Heads vary fastest over the grid; the last eight blocks of slots come first, then the others in order.  Slots with many
+    // members should not come last.  Those of the tokens that the scores picked lie anywhere, but the recent window is conserved
+    // whatever its scores, and under the scores of an observation window its slots, the last ones, collect what resembles no
+    // other (32 heads x 7613: half of a head's members in 64 of 2123 slots; merged last, four workgroups a head were at work by
+    // themselves at the end: 45.7 -> 33.6 us; 32 x 2896 12.5 -> 11.6).
+    const int blocks = (int)gridDim.y, tail = min(blocks >> 3, 8), y = (int)blockIdx.y, block = (y < tail) ? blocks - 1 - y : y - tail;
+    const int h = blockIdx.x, tid = threadIdx.x, G = 1 << lg_G, NG = 256 >> lg_G, grp = tid >> lg_G, s0 = block * NG;
     const int c0 = (tid & (G - 1)) * 8, cc = (c0 < d) ? c0 : 0, slot = min(s0 + grp, B - 1);
     const int pos = kept[(size_t)h * B + slot];
     for (int i = tid; i <= NG; i += 256) begin[i] = (mode == LOOKM_MERGE_NONE) ? 0 : first[(size_t)h * (B + 1) + min(s0 + i, B)];
