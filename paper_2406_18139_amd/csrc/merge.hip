@@ -180,6 +180,73 @@ __device__ __forceinline__ void merged_row(const raw8<T>& own, const float (&sum
     store8(out, x);
 }
 
+// The members of the slots s0 .. s0 + ns - 1 by a workgroup of four waves, without a sort of the whole list: a wave goes through a
+// quarter of the head's assignment list and keeps the entries of those slots, in order; then they are put into `members` by
+// slot, the waves' shares in order.  begin[0 .. NG]: where each slot's members begin.  scratch_a: Le ints, scratch_b: 8 * NG ints.
+constexpr int SCAN_MAX = 4096, SCAN_SLOTS = 32;      // entries of a list: 12 bits of a word, and 16 KB of them; slots: a lane each
+__device__ __forceinline__ void collect_members(const int32_t* __restrict__ assign, int Le, int s0, int ns, int NG, int B, int* begin,
+                                                float* scratch_a, float* scratch_b, unsigned short* members)
+{
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    int* count = reinterpret_cast<int*>(scratch_b);                          // [wave][slot]
+    int* next = count + 4 * NG + wave * NG;                                  // this wave's: where a slot's next member goes
+    for (int i = tid; i < 4 * NG; i += 256) count[i] = 0;
+    const int part = ((Le + 255) / 256) * 64, e_begin = min(Le, wave * part), e_end = min(Le, e_begin + part);
+    uint32_t* own = reinterpret_cast<uint32_t*>(scratch_a) + e_begin;        // this wave's entries: slot << 12 | entry
+    __syncthreads();
+    int n = 0;
+    for (int e0 = e_begin; e0 < e_end; e0 += 8 * 64) {                       // eight rows of 64 entries in flight
+        int a[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) a[i] = assign[min(e0 + i * 64 + lane, Le - 1)];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const int e = e0 + i * 64 + lane, key = min(max(a[i], 0), B - 1) - s0;
+            const bool mine = e < e_end && key >= 0 && key < ns;
+            const uint64_t m = __ballot(mine);
+            if (mine) {
+                own[n + mask_rank(m)] = (uint32_t)key << 12 | (uint32_t)e;
+                atomicAdd(&count[wave * NG + key], 1);
+            }
+            n += __popcll(m);
+        }
+    }
+    __syncthreads();
+    int c[4], all = 0, before = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        c[w] = lane < NG ? count[w * NG + lane] : 0;
+        before += w < wave ? c[w] : 0;
+        all += c[w];
+    }
+    int incl = all;
+#pragma unroll
+    for (int off = 1; off < SCAN_SLOTS; off <<= 1) {
+        const int v = __shfl_up(incl, off);
+        if (lane >= off) incl += v;
+    }
+    if (lane < NG) {
+        next[lane] = incl - all + before;
+        if (wave == 0) begin[lane] = incl - all;
+        if (wave == 0 && lane == NG - 1) begin[NG] = incl;
+    }
+    __builtin_amdgcn_wave_barrier();
+    for (int r0 = 0; r0 < n; r0 += 64) {
+        const bool valid = r0 + lane < n;
+        const uint32_t x = valid ? own[r0 + lane] : 0u;
+        const int key = (int)(x >> 12);
+        const uint64_t peers = match_key(key, valid, 5);
+        int base = 0;
+        if (valid) {
+            base = next[key];
+            members[base + mask_rank(peers)] = (unsigned short)(x & 4095u);
+        }
+        __builtin_amdgcn_wave_barrier();
+        if (valid && (peers >> lane) == 1ull) next[key] = base + __popcll(peers);   // highest peer updates
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
 // G lanes per row, each lane 8 consecutive head dims of the key row and of the value row (both use the same set, the
 // same weights and the same index reads).  A workgroup takes 256 / G consecutive slots, whose members are one stretch of the
 // sorted lists, and its lane groups share out the MEMBERS evenly, whatever slots they belong to: set sizes are very uneven
@@ -191,12 +258,15 @@ __device__ __forceinline__ void merged_row(const raw8<T>& own, const float (&sum
 // conserved, 248 MB 53 -> 41 us; 40 x 5904, 3139 conserved 54 -> 39; 32 x 2896 18 -> 14, against a lane group per slot in the
 // order of the set sizes, eight members of fp32 in flight (two workgroups a compute unit instead of four, and a plan of the
 // slots by size to be made: sort 18.3 -> 16.3).  NB = 2: 43 us (12644) and 39.7 (5904), 6: 41.4 and 41.7, 8: 43.0 and 48.3.
-template <typename T, int NB>
+// SCAN: the members come from the assignment list itself (collect_members), and member_pos and member_w are the evicted list and its
+// cosines; otherwise first, member_pos and member_w are what k_bucket made.
+template <typename T, int NB, bool SCAN>
 __global__ void __launch_bounds__(256)
 k_merge(const T* __restrict__ k, const T* __restrict__ v, const int32_t* __restrict__ kept, const int32_t* __restrict__ first,
-        const int32_t* __restrict__ member_pos, const float* __restrict__ member_w, int L, int d, int B, int Le, int mode, int lg_G,
-        T* __restrict__ k_out, T* __restrict__ v_out)
+        const int32_t* __restrict__ member_pos, const float* __restrict__ member_w, const int32_t* __restrict__ assign, int L, int d, int B,
+        int Le, int mode, int lg_G, T* __restrict__ k_out, T* __restrict__ v_out)
 {
+    extern __shared__ unsigned short members[];                             // SCAN: entry numbers of the slots' members, slot by slot
     __shared__ int begin[257];                                              // of the slots' members; one more: the end
     __shared__ __attribute__((aligned(16))) float slot_sum[2][256 * 8];     // sums of slots that begin inside a group's stretch
     __shared__ __attribute__((aligned(16))) float head_sum[2][256 * 8];     // .. and of the end of one that began before
@@ -209,12 +279,14 @@ k_merge(const T* __restrict__ k, const T* __restrict__ v, const int32_t* __restr
     const int h = blockIdx.x, tid = threadIdx.x, G = 1 << lg_G, NG = 256 >> lg_G, grp = tid >> lg_G, s0 = block * NG;
     const int c0 = (tid & (G - 1)) * 8, cc = (c0 < d) ? c0 : 0, slot = min(s0 + grp, B - 1);
     const int pos = kept[(size_t)h * B + slot];
-    for (int i = tid; i <= NG; i += 256) begin[i] = (mode == LOOKM_MERGE_NONE) ? 0 : first[(size_t)h * (B + 1) + min(s0 + i, B)];
+    if (!SCAN)
+        for (int i = tid; i <= NG; i += 256) begin[i] = (mode == LOOKM_MERGE_NONE) ? 0 : first[(size_t)h * (B + 1) + min(s0 + i, B)];
     k += (size_t)h * L * d + cc;
     v += (size_t)h * L * d + cc;
     raw8<T> own_k, own_v;
     own_k.load(k + (size_t)pos * d);
     own_v.load(v + (size_t)pos * d);
+    if (SCAN) collect_members(assign + (size_t)h * Le, Le, s0, min(NG, B - s0), NG, B, begin, &slot_sum[0][0], &head_sum[0][0], members);
     __syncthreads();
     const int m0 = begin[0], M = begin[NG] - m0, per = (M + NG - 1) >> (8 - lg_G);      // members of a group
     const int t_end = min(m0 + (grp + 1) * per, m0 + M);
@@ -244,9 +316,9 @@ k_merge(const T* __restrict__ k, const T* __restrict__ v, const int32_t* __restr
         auto fetch_members = [&](int from) {
 #pragma unroll
             for (int j = 0; j < NB; ++j) {
-                const int tt = min(from + j, t_end - 1);
-                p[j] = member_pos[tt];
-                w[j] = weighted ? member_w[tt] : 1.0f;
+                const int tt = min(from + j, t_end - 1), e = SCAN ? members[tt] : tt;
+                p[j] = member_pos[e];
+                w[j] = weighted ? member_w[e] : 1.0f;
             }
         };
         fetch_members(t);
@@ -303,13 +375,13 @@ k_merge(const T* __restrict__ k, const T* __restrict__ v, const int32_t* __restr
     merged_row(own_v, sv, n, mode, v_out + out_off);
 }
 
-// The same without the sort, for short lists: a wave looks after 64 / G consecutive slots, goes through the head's whole
+// The same for the shortest lists: a wave looks after 64 / G consecutive slots, goes through the head's whole
 // assignment list by itself, collects the few entries of its slots, in order, and sorts those in LDS.  All of it is a chain of
 // memory latencies; this one is a kernel and four barriers shorter (2 heads x 256 x 64 fp32, the whole layer: 27.0 -> 23.5 us).
 // Members are added up by the slot's lane group, up to SHARED of them: one after the other they would make the largest set the
 // time of the kernel.  (8 heads, 1020 members on 256 slots x 128 bf16, us, a slot's own lane group for all / shared: all in one
 // set 176 / 45, half of them 93 / 28, even sets 7.6 / 7.3; with a sort and a lane group per slot 171, 89, 10.6.)
-constexpr int DIRECT_MAX = 1024, SHARED = 32;
+constexpr int DIRECT_MAX = 256, SHARED = 32;
 template <typename T, int NB>
 __global__ void __launch_bounds__(256)
 k_merge_direct(const T* __restrict__ k, const T* __restrict__ v, const int32_t* __restrict__ kept, const int32_t* __restrict__ evicted,
@@ -455,11 +527,16 @@ static int merge_lanes(int d)
 
 template <typename T>
 static void launch_merge_t(const T* k, const T* v, const int32_t* kept, const int32_t* first, const int32_t* member_pos,
-                           const float* member_w, int H, int L, int d, int B, int mode, T* k_out, T* v_out, hipStream_t st)
+                           const float* member_w, const int32_t* assign, int H, int L, int d, int B, int mode, T* k_out, T* v_out, hipStream_t st)
 {
     const int lg_G = merge_lanes(d), slots = 256 >> lg_G;
-    hipLaunchKernelGGL((lookm::k_merge<T, 4>), dim3(H, (B + slots - 1) / slots), dim3(256), 0, st, k, v, kept, first, member_pos,
-                       member_w, L, d, B, L - B, mode, lg_G, k_out, v_out);
+    const dim3 grid(H, (B + slots - 1) / slots);
+    if (assign != nullptr)
+        hipLaunchKernelGGL((lookm::k_merge<T, 4, true>), grid, dim3(256), (L - B) * sizeof(unsigned short), st, k, v, kept, first, member_pos,
+                           member_w, assign, L, d, B, L - B, mode, lg_G, k_out, v_out);
+    else
+        hipLaunchKernelGGL((lookm::k_merge<T, 4, false>), grid, dim3(256), 0, st, k, v, kept, first, member_pos, member_w, assign, L, d, B,
+                           L - B, mode, lg_G, k_out, v_out);
 }
 
 template <int IPT>
@@ -483,12 +560,11 @@ int launch_merge(const void* k, const void* v, const int32_t* kept, const int32_
     const LaunchCheck check;
     if (Le == 0) mode = LOOKM_MERGE_NONE;
     const int G = 1 << merge_lanes(d);
-    // Without a sort where that is shorter: up to 2048 waves (two a SIMD), each of which goes through the list by itself, and
-    // sets of four members on average.  Sort and merge against the
-    // direct kernel in us (20 calls in a graph): 38 waves, 102 entries in 154 slots 8.0 / 4.6; 400, 500 in 200 10.2 / 8.8;
-    // 1600, 500 in 200 10.9 / 9.3; 2244, 922 in 561 11.9 / 12.2; 8976, 922 in 561 21.4 / 22.1; 800, 400 in 100 11.1 / 10.6;
-    // 360, 1020 in 180 12.2 / 12.5; 120, 540 in 60 12.1 / 14.4; 640, 1020 in 80 15.1 / 20.5.  A lane group has eight lanes and
-    // more, so that a wave has at most eight slots.
+    // The shortest lists: a wave collects the members of its slots by itself.  The whole layer in us against the merge whose
+    // workgroups scan (below) and against sort and merge: 2 heads, 102 entries in 154 slots x 64 fp32 23.8 / 24.6 / 27.2; 2, 173 in 119
+    // x 64 25.5 / 25.9 / 28.4; 8, 389 in 143 x 128 fp32 43.7 / 43.0 / 45.8; 8, 518 in 158 x 64 bf16 30.1 / 29.5 / 32.5, x 128
+    // 48.8 / 47.6 / 50.8.  Sets of four on average: 8 heads, 1020 in 180 slots 12.2 us sorted and merged, 12.5 this way, in 80
+    // slots 15.1 and 20.5.  A lane group has eight lanes and more, so that a wave has at most eight slots.
     if (mode != LOOKM_MERGE_NONE && Le <= lookm::DIRECT_MAX && Le <= 4 * (long)B && G >= 8 && (size_t)H * B * G / 64 <= 2048) {
         const int spb = 4 * (64 / G);
         auto go = [&](auto type) {
@@ -502,7 +578,18 @@ int launch_merge(const void* k, const void* v, const int32_t* kept, const int32_
         mark(LOOKM_K_MERGE);
         return check.status();
     }
-    if (mode != LOOKM_MERGE_NONE) {
+    // Short lists: every workgroup of the merge goes through the head's list, instead of a kernel that sorts it.  What that
+    // costs goes by the workgroups and the list together; sort and merge, without the gap between the two, against the
+    // merge that scans, us: 32 heads x 66 workgroups x 1843 entries 5.2 + 11.7 / 15.0; 32 x 30 x 1843 5.2 + 8.6 / 10.9;
+    // 16 x 36 x 922 4.9 + 7.1 / 9.1; 40 x 197 x 2765 7.9 + 37.1 / 54.1.  A batch of 32 x 84 x 2733 lost 6 us a layer on two streams.
+    const long scanned = (long)H * ((B + (256 / G) - 1) / (256 / G)) * Le;
+    const bool scan = mode != LOOKM_MERGE_NONE && G >= 8 && Le <= lookm::SCAN_MAX && scanned <= 4l << 20;
+    static_assert(256 / 8 <= lookm::SCAN_SLOTS, "a lane for each slot of a workgroup");
+    if (scan) {
+        member_pos = const_cast<int32_t*>(evicted);          // (read only) by entry number
+        member_w = const_cast<float*>(sim);
+        mark(LOOKM_K_BUCKET);
+    } else if (mode != LOOKM_MERGE_NONE) {
         int S, NS;
         bucket_segments(H, B, S, NS);
         const int per_thread = (Le + lookm::BK_THREADS - 1) / lookm::BK_THREADS;
@@ -521,10 +608,10 @@ int launch_merge(const void* k, const void* v, const int32_t* kept, const int32_
         mark(LOOKM_K_BUCKET);
     }
     if (dt == LOOKM_BF16)
-        launch_merge_t((const lookm::bf16_t*)k, (const lookm::bf16_t*)v, kept, first, member_pos, member_w, H, L, d,
+        launch_merge_t((const lookm::bf16_t*)k, (const lookm::bf16_t*)v, kept, first, member_pos, member_w, scan ? assign : nullptr, H, L, d,
                        B, mode, (lookm::bf16_t*)k_out, (lookm::bf16_t*)v_out, st);
     else
-        launch_merge_t((const float*)k, (const float*)v, kept, first, member_pos, member_w, H, L, d, B, mode,
+        launch_merge_t((const float*)k, (const float*)v, kept, first, member_pos, member_w, scan ? assign : nullptr, H, L, d, B, mode,
                        (float*)k_out, (float*)v_out, st);
     mark(LOOKM_K_MERGE);
     return check.status();

@@ -549,6 +549,30 @@ def test_large_sets_without_a_sort(d, dtype, sizes):
                 assert ((out[h].double().cpu() - ref).abs() <= bound + 1e-6).all()
 
 
+@pytest.mark.parametrize("d,dtype", [(64, torch.float32), (128, torch.bfloat16), (256, torch.bfloat16)])
+@pytest.mark.parametrize("B,Le", [(257, 257), (300, 1000), (33, 2049), (200, 3071), (70, 4095), (129, 4096), (129, 4097)])
+def test_merge_that_scans_the_list_and_merge_of_a_sorted_one(d, dtype, B, Le):
+    """Up to 4096 entries the merge's workgroups collect their slots' members from the list, for few enough workgroups; enough
+    heads take the sort.  Both add the same members in the same order: equal bit for bit.  Even sets, all in one, uneven."""
+    L, slots = B + Le, 256 // (8 if d <= 64 else 16 if d <= 128 else 32)
+    many = (4 << 20) // (-(-B // slots) * Le) + 1           # heads that take the sort
+    g = torch.Generator().manual_seed(B + Le + d)
+    k, v = torch.randn(3, L, d, generator=g).to(dtype).cuda(), torch.randn(3, L, d, generator=g).to(dtype).cuda()
+    perm = torch.stack([torch.randperm(L, generator=g) for _ in range(3)])
+    kept, ev = perm[:, :B].sort(1)[0].int().cuda(), perm[:, B:].sort(1)[0].int().cuda()
+    u = torch.rand(3, Le, generator=g)
+    assign = torch.stack([(u[0] * B).long(), torch.full((Le,), B - 1), (u[2] ** 4 * B).long()]).int().cuda()
+    args = (k, v, kept, ev, assign, torch.rand(3, Le, generator=g).cuda())
+    times = -(-many // 3)
+    for mode in ("averaged", "pivotal", "weighted"):
+        scanned = lookm.lookm_merge(*args, mode)
+        for a, b in zip(scanned, lookm.lookm_merge(*(x.repeat((times,) + (1,) * (x.dim() - 1)) for x in args), mode)):
+            assert torch.equal(a, b[:3]) and torch.equal(a, b[-3:])
+        for h in range(3):
+            ref = oracle.merge(k[h].float().cpu().numpy(), *(x[h].cpu().numpy() for x in args[2:]), mode)
+            assert np.abs(scanned[0][h].float().cpu().numpy() - ref).max() < (2e-2 if dtype == torch.bfloat16 else 1e-4)
+
+
 def test_one_large_set_does_not_set_the_time_of_a_merge():
     """1020 members in one set against as many on 256 slots: four times the time with the launch (18 times if the set's own lane
     group adds them all up)."""
