@@ -382,35 +382,26 @@ k_nearest_mfma(const bf16_t* __restrict__ k, const float* __restrict__ rnorm, co
 // cosine of two keys under the exact contract: sequential binary64 sums over k = 0..127 (every product of two
 // bf16 values is exact in binary64, so a fused multiply-add gives the same bits as multiply-then-add), binary64
 // square roots (correctly rounded), one product, one division; 0 when either norm vanishes.  Both rows come from
-// global memory an eighth at a time, the next eighth in flight while one is summed (a loop, not unrolled
-// further: this runs on a handful of threads per call).
+// global memory by quarters, two of either in flight.
 __device__ __forceinline__ double cosine_exact(const bf16_t* __restrict__ a, const bf16_t* __restrict__ b)
 {
     double na = 0.0, nb = 0.0, ab = 0.0;
-    uint4 an[2], bn[2];
+    uint4 ar[2][4], br[2][4];        // two quarters of either row: the second one on its way while the first is summed
+    auto load = [&](int q) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        an[j] = *reinterpret_cast<const uint4*>(a + 8 * j);
-        bn[j] = *reinterpret_cast<const uint4*>(b + 8 * j);
-    }
-    // a row is two cache lines: the second ones are asked for now, so that only one memory latency is paid per row
-    uint4 a_mid = *reinterpret_cast<const uint4*>(a + 64), b_mid = *reinterpret_cast<const uint4*>(b + 64);
-#pragma unroll 1
-    for (int q = 0; q < 8; ++q) {
-        uint4 ac[2], bc[2];
-#pragma unroll
-        for (int j = 0; j < 2; ++j) { ac[j] = an[j]; bc[j] = bn[j]; }
-        if (q < 7) {
-#pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                an[j] = *reinterpret_cast<const uint4*>(a + 16 * (q + 1) + 8 * j);
-                bn[j] = *reinterpret_cast<const uint4*>(b + 16 * (q + 1) + 8 * j);
-            }
-            if (q == 3) { an[0] = a_mid; bn[0] = b_mid; }      // element 64: already here
+        for (int j = 0; j < 4; ++j) {
+            ar[q & 1][j] = *reinterpret_cast<const uint4*>(a + 32 * q + 8 * j);
+            br[q & 1][j] = *reinterpret_cast<const uint4*>(b + 32 * q + 8 * j);
         }
+    };
+    load(0);
+    load(1);
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const uint32_t aw[4] = {ac[j].x, ac[j].y, ac[j].z, ac[j].w}, bw[4] = {bc[j].x, bc[j].y, bc[j].z, bc[j].w};
+    for (int q = 0; q < 4; ++q) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const uint32_t aw[4] = {ar[q & 1][j].x, ar[q & 1][j].y, ar[q & 1][j].z, ar[q & 1][j].w};
+            const uint32_t bw[4] = {br[q & 1][j].x, br[q & 1][j].y, br[q & 1][j].z, br[q & 1][j].w};
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 const double xa = (double)__uint_as_float((i & 1) ? (aw[i >> 1] & 0xffff0000u) : (aw[i >> 1] << 16));
@@ -423,6 +414,7 @@ __device__ __forceinline__ double cosine_exact(const bf16_t* __restrict__ a, con
             // and keeps every widened value alive in between, which spills)
             asm volatile("" : "+v"(na), "+v"(nb), "+v"(ab));
         }
+        if (q < 2) load(q + 2);
     }
     if (na == 0.0 || nb == 0.0) return 0.0;
     return ab / (sqrt(na) * sqrt(nb));
@@ -443,10 +435,12 @@ constexpr int NF_LDS_CHUNKS = 4;  // chunks whose block masks the fold keeps in 
 // that reaches it = the first maximum in slot order).  A key
 // whose best value is not positive (integer order of the bits is not float order there), or whose best cosine is
 // below COS_MIN, takes every slot.
-// (few registers and little LDS on purpose: all workgroups of the headline shape are resident at once, so the
-// kernel takes as long as its slowest workgroup, not twice that)
+// (Four waves a SIMD at 126 registers: at six, 80 of them, fourteen values and more went through scratch memory, which cost more than
+// the 1312 workgroups of 32 heads x 12644 gained from being resident all at once.  us: 32 x 2896 10.1 -> 8.1, 40 x 5904 15.2 -> 10.1,
+// 32 x 12644 21.7 -> 16.9, 32 x 7613 with 2123 conserved keys 12.8 -> 8.7; with rows fetched an eighth ahead at 94 registers 8.8,
+// 10.9, 16.9, 9.4.)
 template <int cbits>   // counter width of the mark words (near_counter_bits of the chunk length)
-__global__ void __launch_bounds__(NF_THREADS, 6)
+__global__ void __launch_bounds__(NF_THREADS, 4)
 k_nearest_fold(const bf16_t* __restrict__ k, const float* __restrict__ rnorm, const int32_t* __restrict__ kept,
                const int32_t* __restrict__ evicted, int L, int B, int Le, int n_strips, int n_chunks, int CT,
                const NearestPartial* __restrict__ part, int32_t* __restrict__ assign, float* __restrict__ sim)
@@ -469,9 +463,15 @@ k_nearest_fold(const bf16_t* __restrict__ k, const float* __restrict__ rnorm, co
     sim += (size_t)h * Le;
     const int ev = blockIdx.x * NF_THREADS + tid;
 
+    // the first round's list is empty (see the loop below)
+    if (tid < NF_GROUPS) grp_pos_e[tid] = -1;
+    best_s[tid] = 0ull;
+    best_r[tid] = 0x7fffffff;
+    if (tid == 0) n_groups = 0;
+
     bool pending = false;                     // this thread's key still needs the exact decision
     bool all_slots = false;                   // ... over every slot: its best value is too small to trust any order
-    int pos_e = 0, bk = 0, band = NEAR_UNITS_MAX;
+    int pos_e = 0, bk = 0, band = NEAR_UNITS_MAX, marked = 0;
     const NearestPartial* mine = part;        // this key's partial of chunk 0; chunk c is n_strips * NBS entries further
     if (ev < Le) {
         pos_e = evicted[ev];
@@ -493,7 +493,6 @@ k_nearest_fold(const bf16_t* __restrict__ k, const float* __restrict__ rnorm, co
         // this key's band, from the lower edge of its best key's truncation interval
         const float rn_e = rnorm[pos_e], cos_low = __uint_as_float((uint32_t)bk << 4) * rn_e;
         band = near_units(cos_low);
-        int marked = 0;
 #pragma unroll
         for (int c = 0; c < NEAR_MAX_CHUNKS; ++c) {
             const bool reach = key[c] >= bk - band;                // chunks within reach only
@@ -558,6 +557,7 @@ k_nearest_fold(const bf16_t* __restrict__ k, const float* __restrict__ rnorm, co
     int cnt = 0;                                  // groups of this thread's key
     if (pending) {
         if (all_slots) cnt = (B + 15) / 16;
+        else if (cbits == 1) cnt = marked;        // a class is a block
         else
             for (int c = 0; c < n_chunks; ++c) {
                 uint32_t m[2];
@@ -582,11 +582,6 @@ k_nearest_fold(const bf16_t* __restrict__ k, const float* __restrict__ rnorm, co
         return __longlong_as_double((long long)((u >> 63) ? (u & 0x7fffffffffffffffull) : ~u));
     };
     while (true) {
-        if (tid < NF_GROUPS) grp_pos_e[tid] = -1;
-        best_s[tid] = 0ull;                   // below the image of every number
-        best_r[tid] = 0x7fffffff;
-        if (tid == 0) n_groups = 0;
-        __syncthreads();
         // keys whose groups fit into this round's list write them (whoever reserves first always fits if its count
         // is at most the capacity; the order of the reservations decides no result): a few LDS stores per key -
         // the slots of a group and their conserved positions are worked out by the threads that evaluate them
@@ -647,6 +642,11 @@ k_nearest_fold(const bf16_t* __restrict__ k, const float* __restrict__ rnorm, co
             pending = false;
         }
         if (!__syncthreads_or(pending)) break;
+        if (tid < NF_GROUPS) grp_pos_e[tid] = -1;
+        best_s[tid] = 0ull;                   // below the image of every number
+        best_r[tid] = 0x7fffffff;
+        if (tid == 0) n_groups = 0;
+        __syncthreads();
     }
 }
 
