@@ -375,9 +375,10 @@ k_merge(const T* __restrict__ k, const T* __restrict__ v, const int32_t* __restr
     merged_row(own_v, sv, n, mode, v_out + out_off);
 }
 
-// The same for the shortest lists: a wave looks after 64 / G consecutive slots, goes through the head's whole
-// assignment list by itself, collects the few entries of its slots, in order, and sorts those in LDS.  All of it is a chain of
-// memory latencies; this one is a kernel and four barriers shorter (2 heads x 256 x 64 fp32, the whole layer: 27.0 -> 23.5 us).
+// The same for the shortest lists: a wave looks after 64 / G consecutive slots, loads the head's whole assignment list by
+// itself and puts the few entries of its slots, in order, into LDS.  All of it is a chain of
+// memory latencies; this one is a kernel and a round trip shorter (2 heads x 256 x 64 fp32, the whole layer: 27.0 -> 23.4 us; 23.8 when
+// a wave read positions and cosines of its own entries after it had found them).
 // Members are added up by the slot's lane group, up to SHARED of them: one after the other they would make the largest set the
 // time of the kernel.  (8 heads, 1020 members on 256 slots x 128 bf16, us, a slot's own lane group for all / shared: all in one
 // set 176 / 45, half of them 93 / 28, even sets 7.6 / 7.3; with a sort and a lane group per slot 171, 89, 10.6.)
@@ -388,8 +389,8 @@ k_merge_direct(const T* __restrict__ k, const T* __restrict__ v, const int32_t* 
                const int32_t* __restrict__ assign, const float* __restrict__ sim, int L, int d, int B, int Le, int mode, int G,
                T* __restrict__ k_out, T* __restrict__ v_out)
 {
-    __shared__ unsigned short own[4][DIRECT_MAX];       // the wave's entries, ascending
-    __shared__ int member_pos[4][DIRECT_MAX];           // .. by slot
+    constexpr int ROWS = DIRECT_MAX / 64;
+    __shared__ int member_pos[4][DIRECT_MAX];           // the wave's members, slot by slot
     __shared__ float member_w[4][DIRECT_MAX];
     __shared__ int first[4][9], next[4][8];             // of each slot: its first member, and where the next one goes
     const int h = blockIdx.x, wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -398,23 +399,23 @@ k_merge_direct(const T* __restrict__ k, const T* __restrict__ v, const int32_t* 
     evicted += (size_t)h * Le;
     sim += (size_t)h * Le;
     const int slot = min(s0 + g, B - 1), pos = kept[(size_t)h * B + slot];
+    // the whole list at once, positions and cosines too: what belongs to other waves is cheaper than a round trip more for the own
+    int key[ROWS], p[ROWS];
+    float w[ROWS];
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+        const int e = min(i * 64 + lane, Le - 1);
+        key[i] = assign[e];
+        p[i] = evicted[e];
+        w[i] = sim[e];
+    }
     if (lane < 8) next[wave][lane] = 0;
-    int n_own = 0;
-    for (int e0 = 0; e0 < Le; e0 += 256) {              // four rows of 64 entries in flight
-        int a[4];
+    __syncthreads();
 #pragma unroll
-        for (int i = 0; i < 4; ++i) a[i] = assign[min(e0 + i * 64 + lane, Le - 1)];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int e = e0 + i * 64 + lane, key = min(max(a[i], 0), B - 1) - s0;
-            const bool mine = e < Le && key >= 0 && key < slots;
-            const uint64_t m = __ballot(mine);
-            if (mine) {
-                own[wave][n_own + mask_rank(m)] = (unsigned short)e;
-                atomicAdd(&next[wave][key], 1);
-            }
-            n_own += __popcll(m);
-        }
+    for (int i = 0; i < ROWS; ++i) {
+        key[i] = i * 64 + lane < Le ? min(max(key[i], 0), B - 1) - s0 : -1;
+        if (key[i] >= 0 && key[i] < slots) atomicAdd(&next[wave][key[i]], 1);
+        else key[i] = -1;
     }
     __syncthreads();
     if (lane < 9) {
@@ -425,20 +426,19 @@ k_merge_direct(const T* __restrict__ k, const T* __restrict__ v, const int32_t* 
     __syncthreads();
     if (lane < 8) next[wave][lane] = first[wave][lane];
     __syncthreads();
-    for (int r0 = 0; r0 < n_own; r0 += 64) {
-        const bool valid = r0 + lane < n_own;
-        const int e = valid ? own[wave][r0 + lane] : 0, key = valid ? min(max(assign[e], 0), B - 1) - s0 : 0;
-        const int p = evicted[e];
-        const float w = sim[e];
-        const uint64_t peers = match_key(key, valid, 3);
+#pragma unroll
+    for (int i = 0; i < ROWS; ++i) {
+        if (!__any(key[i] >= 0)) continue;
+        const bool valid = key[i] >= 0;
+        const uint64_t peers = match_key(key[i], valid, 3);
         int base = 0;
         if (valid) {
-            base = next[wave][key];
-            member_pos[wave][base + mask_rank(peers)] = p;
-            member_w[wave][base + mask_rank(peers)] = w;
+            base = next[wave][key[i]];
+            member_pos[wave][base + mask_rank(peers)] = p[i];
+            member_w[wave][base + mask_rank(peers)] = w[i];
         }
         __builtin_amdgcn_wave_barrier();
-        if (valid && (peers >> lane) == 1ull) next[wave][key] = base + __popcll(peers);   // highest peer updates
+        if (valid && (peers >> lane) == 1ull) next[wave][key[i]] = base + __popcll(peers);   // highest peer updates
         __builtin_amdgcn_wave_barrier();
     }
     __syncthreads();
