@@ -290,7 +290,7 @@ static int scores_impl(const void* q, const void* k, const float* row_lse, int H
     if ((rc = lookm_host::ensure_device_ready()) != LOOKM_OK) return rc;
     return lookm_host::launch_scores(q, k, H, kv_heads, L, d, dt, window ? L - window : 0, at<float>(workspace, w.lse),
                                      row_lse, scores_out, nullptr, at<float>(workspace, w.partials),
-                                     (workspace_bytes - w.partials) / sizeof(float), nullptr, 0, nullptr, (hipStream_t)hip_stream);
+                                     (workspace_bytes - w.partials) / sizeof(float), nullptr, 0, nullptr, nullptr, (hipStream_t)hip_stream);
 }
 
 int lookm_scores(const void* q, const void* k, int H, int L, int d, lookm_dtype dt, float* scores_out,
@@ -332,7 +332,7 @@ int lookm_select_rule_(const float* scores, const uint8_t* modality_mask, int H,
     // an empty list (budget 0, or budget L) may be passed as NULL
     if ((budget > 0 && !kept_idx) || (budget < L && !evicted_idx)) return LOOKM_ERR_INVALID_ARG;
     if ((rc = lookm_host::ensure_device_ready()) != LOOKM_OK) return rc;
-    return lookm_host::launch_select(scores, modality_mask, H, L, budget, recent_window, (int)rule, kept_idx,
+    return lookm_host::launch_select(scores, lookm_host::ScoreParts{}, modality_mask, H, L, budget, recent_window, (int)rule, kept_idx,
                                      evicted_idx, status_out, (hipStream_t)hip_stream);
 }
 
@@ -437,14 +437,15 @@ int enqueue_job(const lookm_job& j, hipStream_t st)
     // Only the image tokens before the window compete for places (Eq. 5-8): when the caller does not ask for the
     // scores themselves and every text token is protected, the other keys' scores are never looked at
     const bool competing_only = j.scores_out == nullptr && j.rule == LOOKM_SELECT_PROTECT_TEXT;
+    lookm_host::ScoreParts parts;
     int rc = lookm_host::launch_scores(j.q, j.k, Hq, H, L, d, dt, j.score_window ? L - j.score_window : 0,
                                        at<float>(workspace, w.lse), j.row_lse, scores,
                                        match ? rnorm : nullptr, at<float>(workspace, w.partials),
                                        (j.workspace_bytes - w.partials) / sizeof(float),
                                        competing_only ? j.modality_mask : nullptr, j.recent_window,
-                                       competing_only ? at<int32_t>(workspace, w.lists) : nullptr, st);
+                                       competing_only ? at<int32_t>(workspace, w.lists) : nullptr, &parts, st);
     if (rc != LOOKM_OK) return rc;
-    rc = lookm_host::launch_select(scores, j.modality_mask, H, L, budget, j.recent_window, (int)j.rule, j.kept_idx,
+    rc = lookm_host::launch_select(scores, parts, j.modality_mask, H, L, budget, j.recent_window, (int)j.rule, j.kept_idx,
                                    evicted, j.status_out, st);
     if (rc != LOOKM_OK) return rc;
     if (j.merge_mode != LOOKM_MERGE_NONE && budget < L) {

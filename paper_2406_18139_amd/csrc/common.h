@@ -121,6 +121,16 @@ constexpr float kLog2e = 1.4426950408889634f;
 // host-side launch plumbing shared by the stage launchers (api.hip owns validation)
 namespace lookm_host {
 
+// Partial scores of the competing keys that nobody has summed yet, [H][chunks][strips][256], and the key norms that are missing.
+struct ScoreParts {
+    const float* part = nullptr;
+    const int32_t* lists = nullptr;
+    const void* k = nullptr;
+    float* rnorm = nullptr;       // may be null
+    int CT = 0, G = 0, R0 = 0;    // rows of a chunk, chunks, first row of the observation window
+};
+constexpr int SELECT_SUMS_MAX_L = 4096;     // four positions a thread
+
 // lse_in: optional caller-supplied natural-log row log-sum-exp [H, L]; when given, pass 1 is skipped
 // rnorm: optional [kv_heads, L]; filled with 1/||k row|| on the way
 // first_row: only the query rows first_row .. L-1 are summed (0 = all rows, Eq. 4 as printed)
@@ -130,14 +140,16 @@ namespace lookm_host {
 // tokens before the recent window); with bf16 and d = 128 the other keys are then skipped in pass 2 and their
 // entries of `scores` left unwritten (other shapes compute every score regardless).  lists: device scratch of
 // score_list_ints(L) ints.
+// parts: optional.  Where the selection sums the chunks' partials itself (lists given, short prompts), launch_scores leaves
+// them unsummed and describes them here, and `scores` is not written; parts->part stays null otherwise.
 int launch_scores(const void* q, const void* k, int H, int kv_heads, int L, int d, lookm_dtype dt, int first_row,
                   float* lse, const float* lse_in, float* scores, float* rnorm, float* scratch, size_t scratch_floats,
-                  const uint8_t* mask, int M, int32_t* lists, hipStream_t st);
+                  const uint8_t* mask, int M, int32_t* lists, ScoreParts* parts, hipStream_t st);
 inline size_t score_list_ints(int L) { return (size_t)2 * L + 64; }
 // floats of scratch that the score passes like to have, or the least that they run with
 size_t scores_scratch_floats(int H, int L, int d, lookm_dtype dt, bool least);
-int launch_select(const float* scores, const uint8_t* mask, int H, int L, int budget, int M, int rule, int32_t* kept,
-                  int32_t* evicted, int32_t* status, hipStream_t st);
+int launch_select(const float* scores, const ScoreParts& parts, const uint8_t* mask, int H, int L, int budget, int M, int rule,
+                  int32_t* kept, int32_t* evicted, int32_t* status, hipStream_t st);
 // rnorm_ready: rnorm already holds the inverse key norms (written by launch_scores)
 int launch_nearest(const void* k, const int32_t* kept, const int32_t* evicted, int H, int L, int d, lookm_dtype dt,
                    int budget, float* rnorm, bool rnorm_ready, int32_t* assign, float* sim, void* scratch,

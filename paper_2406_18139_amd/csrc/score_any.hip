@@ -329,7 +329,7 @@ namespace lookm_host {
 
 int launch_scores_mfma(const void* q, const void* k, int H, int kv_heads, int L, int d, int R0, float* lse,
                        const float* lse_in, float* scores, float* rnorm, float* scratch, size_t scratch_floats,
-                       const uint8_t* mask, int M, int32_t* lists, hipStream_t st);
+                       const uint8_t* mask, int M, int32_t* lists, ScoreParts* parts, hipStream_t st);
 size_t scores_mfma_scratch_floats(int H, int L, bool least);
 
 template <typename T>
@@ -368,12 +368,12 @@ size_t scores_scratch_floats(int H, int L, int d, lookm_dtype dt, bool least)
 
 int launch_scores(const void* q, const void* k, int H, int kv_heads, int L, int d, lookm_dtype dt, int first_row,
                   float* lse, const float* lse_in, float* scores, float* rnorm, float* scratch, size_t scratch_floats,
-                  const uint8_t* mask, int M, int32_t* lists, hipStream_t st)
+                  const uint8_t* mask, int M, int32_t* lists, ScoreParts* parts, hipStream_t st)
 {
     const int R0 = first_row;
     if (dt == LOOKM_BF16) {
         if (d == 128)
-            return launch_scores_mfma(q, k, H, kv_heads, L, d, R0, lse, lse_in, scores, rnorm, scratch, scratch_floats, mask, M, lists, st);
+            return launch_scores_mfma(q, k, H, kv_heads, L, d, R0, lse, lse_in, scores, rnorm, scratch, scratch_floats, mask, M, lists, parts, st);
         return launch_scores_any((const lookm::bf16_t*)q, (const lookm::bf16_t*)k, H, kv_heads, L, d, R0, lse, lse_in, scores,
                                  rnorm, st);
     }

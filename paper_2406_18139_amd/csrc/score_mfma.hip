@@ -17,7 +17,7 @@
 // with the epilogues the two score passes together are 6 % faster this way.)
 // Nothing is atomically accumulated; every sum has a fixed order, so results are bitwise
 // repeatable.  c = log2(e)/sqrt(d) folds the softmax scale into the exp2 argument.
-#include "common.h"
+#include "score_parts.h"
 
 #include <algorithm>
 #include <cmath>
@@ -28,9 +28,6 @@ namespace lookm {
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) float f32x4;
 
-constexpr int SD = 128;        // head dim
-constexpr int BS = 256;        // stationary rows per workgroup
-constexpr int BX = 64;         // streamed rows per iteration
 static_assert(BX == 64, "the lse staging of pass 2 is done by wave 0, one row per lane");
 constexpr int XROW = 128;       // LDS row = 256 B, unpadded; the 16-byte chunk c of row r sits at chunk c ^ (r & 7),
                                // so 16-byte reads of 8 consecutive rows at the same c hit all 32 banks once
@@ -165,7 +162,6 @@ __host__ __device__ inline int strip_chunks(int pass, int t, int L, int CT, int 
 // kernel of its own when pass 1 is skipped):
 //   lists[0] = number of competing keys, lists[1] = number of protected keys,
 //   lists[LIST_HEAD .. +L) competing positions ascending, lists[LIST_HEAD + L .. +L) protected positions ascending.
-constexpr int LIST_HEAD = 64;
 
 // By a workgroup of NT threads.  A wave classifies 64 consecutive positions at a time (coalesced mask bytes, one ballot),
 // eight such rows in flight; the ballots stay in LDS, their counts are scanned, and a second sweep writes both lists.
@@ -643,26 +639,7 @@ k_score_combine(int group, int L, int R0, int C, const float* __restrict__ part_
     const int h = blockIdx.y, r = threadIdx.x;
     int tile = blockIdx.x;
     if (PASS == 2 && lists != nullptr && tile >= nS) {
-        // inverse norms of the protected keys: eight lanes per key, lane p summing the dims 8p .. 8p+7 and
-        // 64+8p .. 64+8p+7 in order, then a pairwise tree over the lanes - the order of the stand-alone norm kernel
-        if (rnorm == nullptr) return;
-        const int NP = lists[1], sub = r & 7;
-        for (int idx = (tile - nS) * 32 + (r >> 3); idx < NP; idx += 32 * nS) {     // uniform per group of eight lanes
-            const int pos = lists[LIST_HEAD + L + idx];
-            const bf16_t* row = k + ((size_t)h * L + pos) * SD;
-            double ss = 0.0;
-#pragma unroll
-            for (int rep = 0; rep < 2; ++rep) {
-                float v[8];
-                load8(row + sub * 8 + rep * 64, v);
-#pragma unroll
-                for (int i = 0; i < 8; ++i) ss = fma((double)v[i], (double)v[i], ss);
-            }
-            ss += __shfl_xor(ss, 1);
-            ss += __shfl_xor(ss, 2);
-            ss += __shfl_xor(ss, 4);
-            if (sub == 0) rnorm[(size_t)h * L + pos] = inverse_norm(ss);
-        }
+        if (rnorm != nullptr) protected_norms(lists, h, L, k, rnorm, (tile - nS) * 32 + (r >> 3), 32 * nS);
         return;
     }
     const bool sparse = PASS == 2 && lists != nullptr;
@@ -674,7 +651,7 @@ k_score_combine(int group, int L, int R0, int C, const float* __restrict__ part_
         const int in_list = row, rows = lists[0], p_strip = lists[LIST_HEAD + tile * BS];
         row = lists[LIST_HEAD + min(in_list, L - 1)];
         if (in_list >= rows) return;
-        g0 = max((p_strip / BX) * BX, (R0 / BX) * BX) / CT;    // as in k_score_mfma
+        g0 = sparse_first_chunk(p_strip, R0, CT);
         nc = G - g0;
     } else if (row >= L) return;
     if (nc == 0) return;     // pass 1 under a window: a strip with no row that counts (its values are never read)
@@ -814,7 +791,7 @@ size_t scores_mfma_scratch_floats(int H, int L, bool least)
 // competing keys only; lists: device, 2 * L + LIST_HEAD ints
 int launch_scores_mfma(const void* q, const void* k, int H, int kv_heads, int L, int d, int R0, float* lse,
                        const float* lse_in, float* scores, float* rnorm, float* scratch, size_t scratch_floats,
-                       const uint8_t* mask, int M, int32_t* lists, hipStream_t st)
+                       const uint8_t* mask, int M, int32_t* lists, ScoreParts* parts, hipStream_t st)
 {
     if (d != lookm::SD) return LOOKM_ERR_UNSUPPORTED;
     const LaunchCheck check;
@@ -862,6 +839,20 @@ int launch_scores_mfma(const void* q, const void* k, int H, int kv_heads, int L,
                            R0, scale2, C, U2, lse_in ? lse_in : lse, (lse_in ? lookm::kLog2e : 1.0f) / scale2, part_a,
                            part_b, rnorm, (const uint8_t*)nullptr, M, (int32_t*)nullptr);
     mark(LOOKM_K_SCORE_COLSUM);
+    // Short prompts: the selection sums the chunks itself, a kernel less (see k_select).  Where a thread has four positions, only up
+    // to eight chunks, one round trip: 8 heads x 2896 in twelve chunks 72.7 us the whole layer, 73.1 with them summed there.
+    // (H: the heads' workgroups and those of the norms are one grid.)
+    if (parts && sparse && group == 1 && H <= 4096 && L <= SELECT_SUMS_MAX_L && (G <= 8 || L <= 2048)) {
+        parts->part = part_a;
+        parts->lists = lists;
+        parts->k = k;
+        parts->rnorm = rnorm;
+        parts->CT = C * lookm::BX;
+        parts->G = G;
+        parts->R0 = R0;
+        mark(LOOKM_K_SCORE_COLSUM_FOLD);
+        return check.status();
+    }
     hipLaunchKernelGGL(lookm::k_score_combine<2>, dim3(sparse ? 2 * nS : nS, kv_heads), dim3(256), 0, st, group, L, R0, C,
                        part_a, part_b, scores, sparse ? (const int32_t*)lists : (const int32_t*)nullptr, kk, rnorm, nS);
     mark(LOOKM_K_SCORE_COLSUM_FOLD);

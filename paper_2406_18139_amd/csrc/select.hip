@@ -10,7 +10,7 @@
 // digits); equal scores are resolved towards the lower position by an ordered prefix
 // count.  Kept and evicted index lists come out ascending.
 // Supports L <= 32 * 1024 (32 positions per thread).
-#include "common.h"
+#include "score_parts.h"
 
 #include <type_traits>
 
@@ -50,10 +50,17 @@ __device__ __forceinline__ int wave_scan_excl(int wave_value, int* wtot, int& to
 // positions seg + i*64 + l, i < IPT, so global reads and writes are coalesced.  Keys and classes are
 // read once and stay in registers for the radix passes and the compaction; ordered counts are ballots
 // inside the wave plus one 16-entry scan across waves.
-template <int IPT, int SEL_THREADS>
+//
+// SUMS (short prompts, bf16 x 128): the scores of the competing tokens arrive as the score pass' partials per chunk of query
+// rows, and every thread adds up those of its own positions, in the order of k_score_combine.  Competing tokens are numbered as in
+// the pass: by an ordered count.  Workgroups past the H heads compute the inverse norms of the protected keys, which that
+// kernel does otherwise.  A launch and a round trip less, for a barrier and a longer load.  Whole layers, us, summed by a kernel of
+// its own / here: 8 heads x 676 47.1 / 45.5, 32 x 876 63.4 / 60.7, 32 x 1482 78.0 / 76.5, 40 x 2228 130.4 / 128.9, 32 x 4056 with
+// a row log-sum-exp 150.2 / 148.2 (32 x 2896: fold and selection 4.8 + 7.0 / 10.6, without the gap between the two).
+template <int IPT, int SEL_THREADS, bool SUMS>
 __global__ void __launch_bounds__(SEL_THREADS)
-k_select(const float* __restrict__ scores, const uint8_t* __restrict__ mask, int L, int B, int M, int rule,
-         int32_t* __restrict__ kept, int32_t* __restrict__ evicted, int32_t* __restrict__ status)
+k_select(const float* __restrict__ scores, lookm_host::ScoreParts parts, int H, int norm_blocks, const uint8_t* __restrict__ mask,
+         int L, int B, int M, int rule, int32_t* __restrict__ kept, int32_t* __restrict__ evicted, int32_t* __restrict__ status)
 {
     constexpr int SEL_WAVES = SEL_THREADS / 64;
     constexpr int DIGIT = (SEL_THREADS == 1024) ? 12 : (SEL_THREADS == 512) ? 11 : 10, SEL_BINS = 1 << DIGIT;    // four bins a thread
@@ -66,7 +73,13 @@ k_select(const float* __restrict__ scores, const uint8_t* __restrict__ mask, int
     __shared__ uint32_t sh_thr;
 
     const int h = blockIdx.x, tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    scores += (size_t)h * L;
+    if (SUMS && h >= H) {
+        const int u = h - H;
+        protected_norms(parts.lists, u / norm_blocks, L, static_cast<const bf16_t*>(parts.k), parts.rnorm,
+                        (u % norm_blocks) * (SEL_THREADS / 8) + (tid >> 3), norm_blocks * (SEL_THREADS / 8));
+        return;
+    }
+    if (!SUMS) scores += (size_t)h * L;
     kept += (size_t)h * B;
     evicted += (size_t)h * (L - B);
     const int head_len = L - M;   // positions [0, head_len) are outside the recent window
@@ -78,11 +91,47 @@ k_select(const float* __restrict__ scores, const uint8_t* __restrict__ mask, int
 #pragma unroll
     for (int i = 0; i < IPT; ++i) {
         const int jc = min(seg + i * 64 + lane, L - 1);   // unconditional loads of a clamped index: nothing waits on a branch
-        key[i] = __float_as_uint(scores[jc]);
+        key[i] = SUMS ? 0u : __float_as_uint(scores[jc]);
         img[i] = mask[jc];
     }
     for (int i = tid; i < SEL_BINS; i += SEL_THREADS) hist[i] = 0;
     if (tid == 0) sh_ncand = 0;
+    if constexpr (SUMS) {
+        uint64_t comp[IPT];                      // competing positions of the wave's rows
+        int n = 0, all;
+#pragma unroll
+        for (int i = 0; i < IPT; ++i) {
+            comp[i] = __ballot(img[i] != 0 && seg + i * 64 + lane < head_len);
+            n += __popcll(comp[i]);
+        }
+        n = wave_scan_excl<SEL_WAVES>(n, wtot[5], all);
+        const int nS = (L + BS - 1) / BS;
+        const size_t stride = (size_t)nS * BS;
+        int at[IPT], g0[IPT];
+        float sum[IPT];
+#pragma unroll
+        for (int i = 0; i < IPT; ++i) {
+            at[i] = min(n + mask_rank(comp[i]), L - 1);       // number among the competing tokens
+            n += __popcll(comp[i]);
+            g0[i] = sparse_first_chunk(parts.lists[LIST_HEAD + (at[i] / BS) * BS], parts.R0, parts.CT);
+            sum[i] = 0.f;
+        }
+        const float* part = parts.part + (size_t)h * parts.G * stride;
+        for (int g = 0; g < parts.G; g += 8) {                // eight chunks of all positions in flight
+            float x[IPT][8];
+#pragma unroll
+            for (int i = 0; i < IPT; ++i)
+#pragma unroll
+                for (int c = 0; c < 8; ++c) x[i][c] = part[min(g + c, parts.G - 1) * stride + at[i]];
+#pragma unroll
+            for (int i = 0; i < IPT; ++i)
+#pragma unroll
+                for (int c = 0; c < 8; ++c)
+                    if (g + c >= g0[i] && g + c < parts.G) sum[i] += x[i][c];      // (below: not the strip's, never written)
+        }
+#pragma unroll
+        for (int i = 0; i < IPT; ++i) key[i] = __float_as_uint(sum[i]);
+    }
 
     // bit i of each mask: position seg + i*64 + lane is in the recent window / a text token before it / an image
     // token before it
@@ -296,13 +345,21 @@ k_select(const float* __restrict__ scores, const uint8_t* __restrict__ mask, int
 
 namespace lookm_host {
 
-int launch_select(const float* scores, const uint8_t* mask, int H, int L, int budget, int M, int rule, int32_t* kept,
+int launch_select(const float* scores, const ScoreParts& parts, const uint8_t* mask, int H, int L, int budget, int M, int rule, int32_t* kept,
                   int32_t* evicted, int32_t* status, hipStream_t st)
 {
     const LaunchCheck check;
     auto go = [&](auto ipt, auto threads) {
-        hipLaunchKernelGGL((lookm::k_select<decltype(ipt)::value, decltype(threads)::value>), dim3(H), dim3(decltype(threads)::value), 0, st,
-                           scores, mask, L, budget, M, rule, kept, evicted, status);
+        constexpr int IPT = decltype(ipt)::value, THREADS = decltype(threads)::value;
+        if constexpr (IPT * THREADS <= SELECT_SUMS_MAX_L)
+            if (parts.part != nullptr) {
+                const int norm_blocks = (L + THREADS / 2 - 1) / (THREADS / 2);            // up to four keys for eight threads
+                hipLaunchKernelGGL((lookm::k_select<IPT, THREADS, true>), dim3(parts.rnorm ? H + H * norm_blocks : H), dim3(THREADS), 0, st, scores,
+                                   parts, H, norm_blocks, mask, L, budget, M, rule, kept, evicted, status);
+                return;
+            }
+        hipLaunchKernelGGL((lookm::k_select<IPT, THREADS, false>), dim3(H), dim3(THREADS), 0, st, scores, parts, H, 0, mask, L, budget, M, rule,
+                           kept, evicted, status);
     };
 #define LOOKM_SELECT(ipt, threads) go(std::integral_constant<int, ipt>{}, std::integral_constant<int, threads>{})
     // Barriers and scans across sixteen waves cost more than a short prompt's positions.  32 heads, us with 1024 / 512 / 256

@@ -624,3 +624,27 @@ def test_selection_at_the_edges_of_its_workgroup_sizes(L, what):
             rest = torch.ones(L, dtype=torch.bool)
             rest[want] = False
             assert torch.equal(ev[h].cpu().long(), torch.nonzero(rest)[:, 0])
+
+
+@pytest.mark.parametrize("H,L", [(1, 64), (3, 256), (2, 257), (8, 512), (8, 513), (32, 1024), (8, 1025), (32, 2048), (8, 2048), (40, 2049), (32, 4096), (2, 4096), (32, 4097)])
+@pytest.mark.parametrize("what", ["mixed", "images", "text first"])
+def test_selection_that_sums_the_chunks(H, L, what):
+    """Up to 4096 positions the selection adds up the score chunks of the competing tokens itself, one to sixteen of them; with the
+    scores asked for, and beyond, a kernel of its own does.  The same sums: kept tokens and cache are equal bit for bit, under an
+    observation window and with a row log-sum-exp too."""
+    g = torch.Generator().manual_seed(L + H)
+    q, k, v = (torch.randn(H, L, 128, generator=g).bfloat16().cuda() for _ in range(3))
+    mask = torch.ones(L, dtype=torch.uint8)
+    if what == "mixed":
+        mask = (torch.rand(L, generator=g) < 0.7).to(torch.uint8)
+    if what == "text first":
+        mask[:L // 2] = 0
+    M = 16
+    protected = lookm.protected_count(mask, M)
+    B = protected + (L - protected) // 5
+    lse = torch.randn(H, L, generator=g).cuda() + 5.0
+    for extra in ({}, {"score_window": min(L, 64)}, {"row_lse": lse}):
+        without = lookm.lookm_compress(q, k, v, mask.cuda(), B, M, "weighted", **extra)
+        asked = lookm.lookm_compress(q, k, v, mask.cuda(), B, M, "weighted", want_scores=True, **extra)
+        assert torch.equal(without.kept_idx, asked.kept_idx)
+        assert torch.equal(without.k_out, asked.k_out) and torch.equal(without.v_out, asked.v_out)
