@@ -283,10 +283,11 @@ k_merge(const T* __restrict__ k, const T* __restrict__ v, const int32_t* __restr
         for (int i = tid; i <= NG; i += 256) begin[i] = (mode == LOOKM_MERGE_NONE) ? 0 : first[(size_t)h * (B + 1) + min(s0 + i, B)];
     k += (size_t)h * L * d + cc;
     v += (size_t)h * L * d + cc;
+    // (SCAN: the lists first - behind the own rows, which wait for `pos`, they would come a round trip later.)
+    if (SCAN) collect_members(assign + (size_t)h * Le, Le, s0, min(NG, B - s0), NG, B, begin, &slot_sum[0][0], &head_sum[0][0], members);
     raw8<T> own_k, own_v;
     own_k.load(k + (size_t)pos * d);
     own_v.load(v + (size_t)pos * d);
-    if (SCAN) collect_members(assign + (size_t)h * Le, Le, s0, min(NG, B - s0), NG, B, begin, &slot_sum[0][0], &head_sum[0][0], members);
     __syncthreads();
     const int m0 = begin[0], M = begin[NG] - m0, per = (M + NG - 1) >> (8 - lg_G);      // members of a group
     const int t_end = min(m0 + (grp + 1) * per, m0 + M);
