@@ -8,6 +8,8 @@
 // dimension.  Keys and values use the same sets and (for weighted merging) the same cosine weights.
 #include "common.h"
 
+#include <algorithm>
+
 namespace lookm {
 
 constexpr int BK_THREADS = 1024;
@@ -505,11 +507,11 @@ k_merge_direct(const T* __restrict__ k, const T* __restrict__ v, const int32_t* 
 
 namespace lookm_host {
 
-// Segments per head: enough workgroups to cover the chip's 256 compute units, and no more than
-// BK_MAX_SEG slots in one segment.
+// Segments per head: as many as make no more workgroups than there are compute units (40 heads x 2765 entries in seven segments,
+// 280 workgroups, 8.0 us, in six 6.7), and no more than BK_MAX_SEG slots in one segment.
 static void bucket_segments(int H, int B, int& S, int& NS)
 {
-    int ns = (256 + H - 1) / H;
+    int ns = std::max(1, 256 / H);
     if (ns > 16) ns = 16;
     const int need = (B + lookm::BK_MAX_SEG - 1) / lookm::BK_MAX_SEG;
     if (ns < need) ns = need;
