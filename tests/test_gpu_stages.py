@@ -492,8 +492,8 @@ def test_mfma_probe_reports_a_plausible_rate():
 @pytest.mark.parametrize("B,Le", [(1, 1), (16, 63), (16, 64), (16, 65), (17, 65), (70, 257), (154, 102), (256, 1023), (256, 1024), (257, 1025), (500, 1000),
                                   (2, 300), (12, 1023), (31, 4000)])
 def test_merge_with_and_without_a_sort(d, dtype, B, Le):
-    """Short lists are merged by waves that collect their slots' members themselves; many heads, large
-    sets, or one entry more than 1024, go through the sort: the same heads on both paths.  Both add a slot's members in ascending position, the second
+    """Short lists are merged without a sort, the shortest by waves that collect their slots' members themselves; many heads, large
+    sets or longer lists take the other kernels: the same heads on both paths.  Both add a slot's members in ascending position, the second
     in up to 256 pieces: fp32 sums of n terms in two orders differ by at most n 2^-23 times the largest term, and a bf16
     row rounded from either by one unit in the last place, 2^-7 of its value, more."""
     L, lanes = B + Le, 8 if d <= 64 else 16 if d <= 128 else 32
@@ -550,10 +550,11 @@ def test_large_sets_without_a_sort(d, dtype, sizes):
 
 
 @pytest.mark.parametrize("d,dtype", [(64, torch.float32), (128, torch.bfloat16), (256, torch.bfloat16)])
-@pytest.mark.parametrize("B,Le", [(257, 257), (300, 1000), (33, 2049), (200, 3071), (70, 4095), (129, 4096), (129, 4097)])
+@pytest.mark.parametrize("B,Le", [(70, 255), (64, 256), (257, 257), (300, 1000), (33, 2049), (200, 3071), (70, 4095), (129, 4096), (129, 4097)])
 def test_merge_that_scans_the_list_and_merge_of_a_sorted_one(d, dtype, B, Le):
     """Up to 4096 entries the merge's workgroups collect their slots' members from the list, for few enough workgroups; enough
-    heads take the sort.  Both add the same members in the same order: equal bit for bit.  Even sets, all in one, uneven."""
+    heads take the sort.  Both add the same members in the same order: equal bit for bit.  Even sets, all in one, uneven.  (Up to 256
+    entries three heads have a kernel of their own, which adds in another order: the oracle's tolerance only.)"""
     L, slots = B + Le, 256 // (8 if d <= 64 else 16 if d <= 128 else 32)
     many = (4 << 20) // (-(-B // slots) * Le) + 1           # heads that take the sort
     g = torch.Generator().manual_seed(B + Le + d)
@@ -567,7 +568,7 @@ def test_merge_that_scans_the_list_and_merge_of_a_sorted_one(d, dtype, B, Le):
     for mode in ("averaged", "pivotal", "weighted"):
         scanned = lookm.lookm_merge(*args, mode)
         for a, b in zip(scanned, lookm.lookm_merge(*(x.repeat((times,) + (1,) * (x.dim() - 1)) for x in args), mode)):
-            assert torch.equal(a, b[:3]) and torch.equal(a, b[-3:])
+            assert Le <= 256 or torch.equal(a, b[:3]) and torch.equal(a, b[-3:])
         for h in range(3):
             ref = oracle.merge(k[h].float().cpu().numpy(), *(x[h].cpu().numpy() for x in args[2:]), mode)
             assert np.abs(scanned[0][h].float().cpu().numpy() - ref).max() < (2e-2 if dtype == torch.bfloat16 else 1e-4)
