@@ -6,6 +6,8 @@
 // reads the rows of some consecutive conserved slots and those of all their members and writes the compact output
 // rows - no scatter, no float atomics, fixed summation order, coalesced 16-byte accesses along the head
 // dimension.  Keys and values use the same sets and (for weighted merging) the same cosine weights.
+// Short lists are not sorted beforehand: the merge's workgroups collect their slots' members from the assignment list
+// (collect_members), for the shortest ones every wave by itself (k_merge_direct).
 #include "common.h"
 
 #include <algorithm>
