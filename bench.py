@@ -124,7 +124,7 @@ def stack(args) -> int:
     for pi, w in enumerate(prompts):
         kms = lookm.lookm_job_profile(batch[pi], 5)
         kms.pop("rnorm", None)
-        per_prompt_kernels[w.name] = {k_: round(v_, 5) for k_, v_ in kms.items()}
+        per_prompt_kernels[w.name] = {k_: round(v_, 5) for k_, v_ in kms.items() if v_ > 0}
         name = max(kms, key=kms.get)
         if dom is None or kms[name] > dom[2]:
             dom = (w, name, kms[name])
@@ -354,15 +354,15 @@ def main() -> int:
     if args.reuse_lse:
         kms.pop("score_lse"), kms.pop("score_lse_fold")          # not launched: the prefill's values are used
     kernels = {}
-    event_gap_ms = None
-    if w.dtype == "bf16" and w.d == 128:
-        # on the matrix-core path the key norms come out of score pass 2 and no norm kernel is launched: its slot
-        # is an empty interval between two events, i.e. what the event records themselves cost on the stream
-        event_gap_ms = kms.pop("rnorm")
+    # the key norms come out of the score passes and no norm kernel is launched: its slot is an empty interval
+    # between two events, i.e. what the event records themselves cost on the stream
+    event_gap_ms = kms.pop("rnorm")
     for name, ms in kms.items():
+        if ms == 0.0:
+            continue                                             # not launched at these sizes
         bound, amount = work[name]
         peak = PEAK_MFMA_BF16 if bound == "mfma" else PEAK_HBM
-        ach = amount / (ms * 1e-3) if ms > 0 else 0.0
+        ach = amount / (ms * 1e-3)
         kernels[name] = {"ms": round(ms, 5), "bound": bound,
                          "achieved": round(ach / (1e12 if bound == "mfma" else 1e9), 3),
                          "unit": "TFLOP/s" if bound == "mfma" else "GB/s", "frac": round(ach / peak, 4)}

@@ -361,10 +361,12 @@ size_t lookm_workspace_offset(int H, int kv_heads, int L, int d, int budget, loo
 
 /* Kernels of the path, in launch order (Section 3.2: the two score passes and the selection;
  * Section 3.3: key norms, matching, similarity sets, merge + compaction).  The key norms are written by
- * the score passes and no norm kernel is launched: that slot reads the cost of an empty event interval. */
+ * the score passes and no norm kernel is launched: that slot reads the cost of an empty event interval.  The other kernels
+ * that the given sizes skip read 0 (see lookm_compress_profile): a supplied row log-sum-exp, the folds of shapes that need
+ * none, the score fold of short prompts (part of the selection), the sort of short lists (part of the merge). */
 enum {
     LOOKM_K_SCORE_LSE = 0, LOOKM_K_SCORE_LSE_FOLD = 1,        /* pass 1 and the fold of its chunk partials */
-    LOOKM_K_SCORE_COLSUM = 2, LOOKM_K_SCORE_COLSUM_FOLD = 3,  /* pass 2 and the fold of its chunk partials (short prompts: part of the selection) */
+    LOOKM_K_SCORE_COLSUM = 2, LOOKM_K_SCORE_COLSUM_FOLD = 3,  /* pass 2 and the fold of its chunk partials */
     LOOKM_K_SELECT = 4, LOOKM_K_RNORM = 5, LOOKM_K_NEAREST = 6, LOOKM_K_NEAREST_FOLD = 7,
     LOOKM_K_BUCKET = 8, LOOKM_K_MERGE = 9, LOOKM_N_KERNELS = 10
 };

@@ -577,7 +577,6 @@ int launch_merge(const void* k, const void* v, const int32_t* kept, const int32_
             hipLaunchKernelGGL((lookm::k_merge_direct<T, 8>), dim3(H, (B + spb - 1) / spb), dim3(256), 0, st, (const T*)k, (const T*)v, kept,
                                evicted, assign, sim, L, d, B, Le, mode, G, (T*)k_out, (T*)v_out);
         };
-        mark(LOOKM_K_BUCKET);
         if (dt == LOOKM_BF16) go(lookm::bf16_t{});
         else go(float{});
         mark(LOOKM_K_MERGE);
@@ -593,7 +592,6 @@ int launch_merge(const void* k, const void* v, const int32_t* kept, const int32_
     if (scan) {
         member_pos = const_cast<int32_t*>(evicted);          // (read only) by entry number
         member_w = const_cast<float*>(sim);
-        mark(LOOKM_K_BUCKET);
     } else if (mode != LOOKM_MERGE_NONE) {
         int S, NS;
         bucket_segments(H, B, S, NS);

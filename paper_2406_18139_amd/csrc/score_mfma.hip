@@ -850,7 +850,6 @@ int launch_scores_mfma(const void* q, const void* k, int H, int kv_heads, int L,
         parts->CT = C * lookm::BX;
         parts->G = G;
         parts->R0 = R0;
-        mark(LOOKM_K_SCORE_COLSUM_FOLD);
         return check.status();
     }
     hipLaunchKernelGGL(lookm::k_score_combine<2>, dim3(sparse ? 2 * nS : nS, kv_heads), dim3(256), 0, st, group, L, R0, C,

@@ -649,3 +649,30 @@ def test_selection_that_sums_the_chunks(H, L, what):
         asked = lookm.lookm_compress(q, k, v, mask.cuda(), B, M, "weighted", want_scores=True, **extra)
         assert torch.equal(without.kept_idx, asked.kept_idx)
         assert torch.equal(without.k_out, asked.k_out) and torch.equal(without.v_out, asked.v_out)
+
+
+def kernel_times(H, L, B, d, dtype, mode="weighted", row_lse=False, scores=False):
+    """lookm_job_profile of a prompt whose image tokens are all but the first eight and the last sixteen."""
+    g = torch.Generator(device="cuda").manual_seed(L)
+    q, k, v = (torch.randn(H, L, d, generator=g, device="cuda").to(dtype) for _ in range(3))
+    mask = torch.ones(L, dtype=torch.uint8, device="cuda")
+    mask[:8] = 0
+    out = lookm.alloc_outputs(H, L, d, B, dtype, "cuda", scores)
+    ws = lookm.alloc_workspace(H, L, d, B, lookm.BF16 if dtype == torch.bfloat16 else lookm.F32, "cuda")
+    lse = torch.randn(H, L, generator=g, device="cuda") + 5.0 if row_lse else None
+    return lookm.lookm_job_profile(lookm.make_job(q, k, v, mask, B, 16, mode, out, ws, row_lse=lse), 3)
+
+
+@pytest.mark.parametrize("skipped,args", [
+    ({"score_colsum_fold", "bucket"}, dict(H=8, L=700, B=300, d=128, dtype=torch.bfloat16)),
+    ({"score_colsum_fold", "bucket", "score_lse", "score_lse_fold"}, dict(H=8, L=700, B=300, d=128, dtype=torch.bfloat16, row_lse=True)),
+    ({"score_colsum_fold", "bucket", "nearest", "nearest_fold"}, dict(H=8, L=700, B=300, d=128, dtype=torch.bfloat16, mode="none")),
+    ({"bucket"}, dict(H=8, L=700, B=300, d=128, dtype=torch.bfloat16, scores=True)),
+    (set(), dict(H=8, L=5000, B=800, d=128, dtype=torch.bfloat16)),
+    ({"score_lse_fold", "score_colsum_fold", "nearest_fold", "bucket"}, dict(H=2, L=256, B=154, d=64, dtype=torch.float32)),
+    ({"score_lse_fold", "score_colsum_fold", "nearest_fold"}, dict(H=2, L=5000, B=800, d=64, dtype=torch.bfloat16)),
+])
+def test_profile_reads_zero_for_what_is_not_launched(skipped, args):
+    ms = kernel_times(**args)
+    del ms["rnorm"]                     # the price of the events: an empty interval
+    assert {name for name, t in ms.items() if t == 0.0} == skipped, ms
