@@ -839,10 +839,14 @@ int launch_scores_mfma(const void* q, const void* k, int H, int kv_heads, int L,
                            R0, scale2, C, U2, lse_in ? lse_in : lse, (lse_in ? lookm::kLog2e : 1.0f) / scale2, part_a,
                            part_b, rnorm, (const uint8_t*)nullptr, M, (int32_t*)nullptr);
     mark(LOOKM_K_SCORE_COLSUM);
-    // Short prompts: the selection sums the chunks itself, a kernel less (see k_select).  Where a thread has four positions, only up
-    // to eight chunks, one round trip: 8 heads x 2896 in twelve chunks 72.7 us the whole layer, 73.1 with them summed there.
+    // Short prompts: the selection sums the chunks itself, a kernel less (see k_select).  Up to sixteen chunks, two round trips, where
+    // it has 512 threads at most, up to eight, one, where it has 1024: beyond, a single workgroup a head reads for longer than the
+    // launch costs.  Whole layers, us, with the fold's kernel / summed there: one head x 1024 (16 chunks), nearly all images 43.3 / 42.8, half
+    // text 50.6 / 48.3; two heads x 1024 47.5 / 46.8; one head, nearly all images, x 1088 (17 chunks) 48.8 / 49.8, x 1344 (21) 51.2 / 52.0,
+    // x 2048 (32) 59.8 / 60.8, two x 1088 49.4 / 50.3, x 1600 (25) 54.5 / 56.0 (prompts of mostly text gain 1 there, from the norms); 1024
+    // threads: 8 heads x 2896 in twelve chunks 72.7 / 73.1, one head x 2428 in nineteen 57.9 / 61.2.
     // (H: the heads' workgroups and those of the norms are one grid.)
-    if (parts && sparse && group == 1 && H <= 4096 && L <= SELECT_SUMS_MAX_L && (G <= 8 || L <= 2048)) {
+    if (parts && sparse && group == 1 && H <= 4096 && L <= SELECT_SUMS_MAX_L && G <= (L <= 2048 ? 16 : 8)) {
         parts->part = part_a;
         parts->lists = lists;
         parts->k = k;

@@ -627,11 +627,11 @@ def test_selection_at_the_edges_of_its_workgroup_sizes(L, what):
             assert torch.equal(ev[h].cpu().long(), torch.nonzero(rest)[:, 0])
 
 
-@pytest.mark.parametrize("H,L", [(1, 64), (3, 256), (2, 257), (8, 512), (8, 513), (32, 1024), (8, 1025), (32, 2048), (8, 2048), (40, 2049), (32, 4096), (2, 4096), (32, 4097)])
+@pytest.mark.parametrize("H,L", [(1, 64), (3, 256), (2, 257), (8, 512), (8, 513), (32, 1024), (1, 1024), (8, 1025), (32, 2048), (8, 2048), (2, 2048), (1, 2048), (40, 2049), (32, 4096), (2, 4096), (32, 4097)])
 @pytest.mark.parametrize("what", ["mixed", "images", "text first"])
 def test_selection_that_sums_the_chunks(H, L, what):
-    """Up to 4096 positions the selection adds up the score chunks of the competing tokens itself, one to sixteen of them; with the
-    scores asked for, and beyond, a kernel of its own does.  The same sums: kept tokens and cache are equal bit for bit, under an
+    """Up to 4096 positions the selection adds up the score chunks of the competing tokens itself, one to sixteen of them (see the test
+    below for which); with the scores asked for, and beyond, a kernel of its own does.  The same sums: kept tokens and cache are equal bit for bit, under an
     observation window and with a row log-sum-exp too."""
     g = torch.Generator().manual_seed(L + H)
     q, k, v = (torch.randn(H, L, 128, generator=g).bfloat16().cuda() for _ in range(3))
@@ -676,3 +676,11 @@ def test_profile_reads_zero_for_what_is_not_launched(skipped, args):
     ms = kernel_times(**args)
     del ms["rnorm"]                     # the price of the events: an empty interval
     assert {name for name, t in ms.items() if t == 0.0} == skipped, ms
+
+
+@pytest.mark.parametrize("H,L,summed", [(1, 1024, True), (1, 1025, False), (1, 2048, False), (2, 1088, False), (2, 2048, True), (8, 2048, True),
+                                        (40, 2049, True), (8, 2896, False), (32, 4096, True), (32, 4097, False)])
+def test_which_prompts_have_their_chunks_summed_in_the_selection(H, L, summed):
+    """Sixteen chunks at most (1 x 1024, 2 x 2048), past 2048 positions eight (32 x 4096; 8 x 2896 has twelve); 1 x 1025 has seventeen,
+    1 x 2048 thirty-two."""
+    assert (kernel_times(H, L, L // 2, 128, torch.bfloat16)["score_colsum_fold"] == 0.0) == summed
