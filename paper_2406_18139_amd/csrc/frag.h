@@ -157,6 +157,12 @@ struct frag_split {
 // products of that row, which it does without that.
 // (The pairs of factors are hidden in registers: from the constant 0x0000bf80 the compiler makes the inline constant
 // -1.0, which the instruction takes for 0xbf800000.)
+// BOTH: false where `hi` lies past the row (widths of an odd number of steps) and its parts are zeros: from behind those registers
+// the compiler does not see that it need not work them out (whole layers, us, subtracted / dots of zeros too / this: 32 x 2804 x 8
+// 145.2 / 149.5 / 146.8, x 40 258.9 / 260.4 / 257.4, x 48 282.0 / 287.9 / 282.1; 32 x 5308 x 8 399 / 414 / 401, x 48 806 / 818 / 809).
+// Against the subtraction, whole layers at 8 to 64 dims gain up to 3 % where few strips or many are resident and lose 1 to 3 % where
+// all are, three or four a SIMD (3 x 9916 x 40 313 / 322, x 64 358 / 363; 1 x 9916 x 40 234 / 226, x 64 247 / 240; 32 x 5308 x 64 916 / 904).
+template <bool BOTH>
 __device__ __forceinline__ frag_split split_steps(frag_f32 lo, frag_f32 hi)
 {
     typedef __attribute__((ext_vector_type(2))) float f2;
@@ -164,9 +170,9 @@ __device__ __forceinline__ frag_split split_steps(frag_f32 lo, frag_f32 hi)
     uint32_t first, second;
     asm("s_mov_b32 %0, 0x0000bf80" : "=s"(first));
     asm("s_mov_b32 %0, 0xbf800000" : "=s"(second));
-    frag_split s;
+    frag_split s = {};
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
+    for (int i = 0; i < (BOTH ? 4 : 2); ++i) {
         f2 x = i < 2 ? f2{lo[2 * i], lo[2 * i + 1]} : f2{hi[2 * i - 4], hi[2 * i - 3]};
 #pragma unroll
         for (int part = 0; part < 3; ++part) {
@@ -259,7 +265,7 @@ template <int KS, int CG> struct frag_strip<float, KS, CG> {
                     s[cg][kb].w[1] = __builtin_bit_cast(frag_words, second);
                     s[cg][kb].w[2] = frag_words{};
                 } else {
-                    s[cg][kb] = split_steps(f[cg][2 * kb], second);
+                    s[cg][kb] = 2 * kb + 1 < KS ? split_steps<true>(f[cg][2 * kb], second) : split_steps<false>(f[cg][2 * kb], second);
                 }
             }
     }
@@ -290,7 +296,8 @@ template <int KS, int CG> struct frag_strip<float, KS, CG> {
             for (int rg = 0; rg < 2; ++rg) {
                 frag_split t[KB];
 #pragma unroll
-                for (int kb = 0; kb < KB; ++kb) t[kb] = split_steps(a[rg][2 * kb], 2 * kb + 1 < KS ? a[rg][(2 * kb + 1) % KS] : frag_f32{});
+                for (int kb = 0; kb < KB; ++kb)
+                    t[kb] = 2 * kb + 1 < KS ? split_steps<true>(a[rg][2 * kb], a[rg][(2 * kb + 1) % KS]) : split_steps<false>(a[rg][2 * kb], frag_f32{});
 #pragma unroll
                 for (int cg = 0; cg < CG; ++cg) acc[rg][cg] = acc_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
