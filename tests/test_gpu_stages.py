@@ -684,3 +684,15 @@ def test_which_prompts_have_their_chunks_summed_in_the_selection(H, L, summed):
     """Sixteen chunks at most (1 x 1024, 2 x 2048), past 2048 positions eight (32 x 4096; 8 x 2896 has twelve); 1 x 1025 has seventeen,
     1 x 2048 thirty-two."""
     assert (kernel_times(H, L, L // 2, 128, torch.bfloat16)["score_colsum_fold"] == 0.0) == summed
+
+
+@pytest.mark.parametrize("H,B,Le,d,dtype,sort", [
+    (256, 512, 58, 128, torch.bfloat16, True), (32, 2448, 230, 256, torch.bfloat16, True),      # short lists, many workgroups
+    (128, 448, 300, 128, torch.bfloat16, False), (128, 449, 300, 128, torch.bfloat16, True),    # 3584 and 3712 of them
+    (80, 512, 300, 128, torch.float32, False), (80, 513, 300, 128, torch.float32, True),        # 2560 and 2640
+    (64, 192, 3600, 64, torch.bfloat16, False), (64, 800, 3600, 64, torch.bfloat16, True), (64, 800, 2600, 64, torch.bfloat16, False),
+    (64, 1024, 2048, 64, torch.bfloat16, False), (64, 1024, 2049, 64, torch.bfloat16, True),    # 2^22 entries gone through, and more
+    (2, 100, 4096, 64, torch.bfloat16, False), (2, 100, 4097, 64, torch.bfloat16, True)])
+def test_which_lists_are_sorted(H, B, Le, d, dtype, sort):
+    """Where the merge's workgroups go through the list themselves no sort is launched."""
+    assert (kernel_times(H, B + Le, B, d, dtype)["bucket"] > 0.0) == sort
