@@ -160,9 +160,8 @@ struct frag_split {
 // BOTH: false where `hi` lies past the row (widths of an odd number of steps) and its parts are zeros: from behind those registers
 // the compiler does not see that it need not work them out (whole layers, us, subtracted / dots of zeros too / this: 32 x 2804 x 8
 // 145.2 / 149.5 / 146.8, x 40 258.9 / 260.4 / 257.4, x 48 282.0 / 287.9 / 282.1; 32 x 5308 x 8 399 / 414 / 401, x 48 806 / 818 / 809).
-// Against the subtraction, whole layers at 8 to 64 dims gain up to 3 % where few strips or many are resident and lose 1 to 3 % where
-// all are, three or four a SIMD (3 x 9916 x 40 313 / 322, x 64 358 / 363; 1 x 9916 x 40 234 / 226, x 64 247 / 240; 32 x 5308 x 64 916 / 904).
-template <bool BOTH>
+// DOTS: false for remainders by subtraction, the same bits (see score_kernel in score_any.hip).
+template <bool BOTH, bool DOTS>
 __device__ __forceinline__ frag_split split_steps(frag_f32 lo, frag_f32 hi)
 {
     typedef __attribute__((ext_vector_type(2))) float f2;
@@ -179,8 +178,13 @@ __device__ __forceinline__ frag_split split_steps(frag_f32 lo, frag_f32 hi)
             const b2 b = __builtin_convertvector(x, b2);
             s.w[part][i] = __builtin_bit_cast(uint32_t, b);
             if (part == 2) break;
-            x[0] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(b2, first), b, x[0], false);
-            x[1] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(b2, second), b, x[1], false);
+            if constexpr (DOTS) {
+                x[0] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(b2, first), b, x[0], false);
+                x[1] = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(b2, second), b, x[1], false);
+            } else {
+                x[0] -= __uint_as_float(s.w[part][i] << 16);
+                x[1] -= __uint_as_float(s.w[part][i] & 0xffff0000u);
+            }
         }
     }
     return s;
@@ -199,7 +203,7 @@ template <int KS, int CG> struct frag_strip<bf16_t, KS, CG> {
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) s[cg][ks] = f[cg][ks];
     }
-    template <typename Row, typename Streamed>
+    template <bool DOTS, typename Row, typename Streamed>
     __device__ __forceinline__ void multiply(const frag_bf16 (&a)[2][KS], acc_t (&acc)[2][CG], int, int, bool, Row&&, Streamed&&) const
     {
 #pragma unroll
@@ -225,7 +229,7 @@ template <int KS> struct frag_strip<float, KS, 1> {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) s[ks] = f[0][ks];
     }
-    template <typename Row, typename Streamed>
+    template <bool DOTS, typename Row, typename Streamed>
     __device__ __forceinline__ void multiply(const frag_f32 (&a)[2][KS], acc_t (&acc)[2][1], int, int, bool, Row&&, Streamed&&) const
     {
 #pragma unroll
@@ -265,11 +269,11 @@ template <int KS, int CG> struct frag_strip<float, KS, CG> {
                     s[cg][kb].w[1] = __builtin_bit_cast(frag_words, second);
                     s[cg][kb].w[2] = frag_words{};
                 } else {
-                    s[cg][kb] = 2 * kb + 1 < KS ? split_steps<true>(f[cg][2 * kb], second) : split_steps<false>(f[cg][2 * kb], second);
+                    s[cg][kb] = 2 * kb + 1 < KS ? split_steps<true, true>(f[cg][2 * kb], second) : split_steps<false, true>(f[cg][2 * kb], second);
                 }
             }
     }
-    template <typename Row, typename Streamed>
+    template <bool DOTS, typename Row, typename Streamed>
     __device__ __forceinline__ void multiply(const frag_f32 (&a)[2][KS], acc_t (&acc)[2][CG], int q4, int d, bool in_fp32, Row&& row, Streamed&& streamed) const
     {
         if (__builtin_expect(extreme, 0)) {    // known beforehand: no parts, and all the rows are in registers
@@ -297,7 +301,7 @@ template <int KS, int CG> struct frag_strip<float, KS, CG> {
                 frag_split t[KB];
 #pragma unroll
                 for (int kb = 0; kb < KB; ++kb)
-                    t[kb] = 2 * kb + 1 < KS ? split_steps<true>(a[rg][2 * kb], a[rg][(2 * kb + 1) % KS]) : split_steps<false>(a[rg][2 * kb], frag_f32{});
+                    t[kb] = 2 * kb + 1 < KS ? split_steps<true, DOTS>(a[rg][2 * kb], a[rg][(2 * kb + 1) % KS]) : split_steps<false, DOTS>(a[rg][2 * kb], frag_f32{});
 #pragma unroll
                 for (int cg = 0; cg < CG; ++cg) acc[rg][cg] = acc_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll

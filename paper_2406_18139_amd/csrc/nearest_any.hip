@@ -139,7 +139,7 @@ k_nearest_any(const T* __restrict__ k, const float* __restrict__ rnorm, const in
         if (b + NA_WAVES < n_blocks) fetch(b + NA_WAVES);
         __builtin_amdgcn_sched_barrier(0);
         acc_t acc[2][CG];
-        strip.multiply(a, acc, q4, d, tiny, [&](int cg) { return k + (size_t)evicted[min(e0 + 16 * cg + c16, Le - 1)] * d; },
+        strip.template multiply<true>(a, acc, q4, d, tiny, [&](int cg) { return k + (size_t)evicted[min(e0 + 16 * cg + c16, Le - 1)] * d; },
                        [&](int rg) { return k + (size_t)kept[min(b * 32 + 16 * rg + c16, B - 1)] * d; });
 #pragma unroll
         for (int cg = 0; cg < CG; ++cg)

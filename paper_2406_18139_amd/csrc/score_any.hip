@@ -103,12 +103,15 @@ __device__ __forceinline__ void weights_of_keys(const T* __restrict__ q, const T
 
 // PASS 1: stationary q (query heads), streamed k; writes lse2.  PASS 2: stationary k (key heads), streamed q of each of
 // the `group` query heads in turn; writes scores.  Workgroups from n_units on compute the inverse norms of norm_rows keys.
-template <int PASS, typename T, int KS, int CG>
+// MODE: the pass, and SUBTRACT where the remainders of fp32 parts are differences instead of dots.
+constexpr int SUBTRACT = 4;
+template <int MODE, typename T, int KS, int CG>
 __global__ void __launch_bounds__(256, 2)
 k_score_any(const T* __restrict__ q, const T* __restrict__ k, int heads, int group, int L, int R0, int d, float scale2,
             const float* __restrict__ lse2, float lse_scale, float* __restrict__ out, int n_strips, int together, unsigned n_units,
             size_t norm_rows, float* __restrict__ rnorm)
 {
+    constexpr int PASS = MODE % SUBTRACT;
     typedef typename frag<T>::type frag_t;
     constexpr int SR = 16 * CG;                      // stationary rows
     __shared__ float fold_a[SA_WAVES][SR], fold_b[PASS == 1 ? SA_WAVES : 1][SR];
@@ -201,7 +204,7 @@ k_score_any(const T* __restrict__ q, const T* __restrict__ k, int heads, int gro
             if (b + SA_WAVES < b_end) fetch(b + SA_WAVES);
             __builtin_amdgcn_sched_barrier(0);
             acc_t acc[2][CG];
-            strip.multiply(a, acc, q4, d, false, [&](int cg) { return S + (size_t)min(s0 + 16 * cg + c16, L - 1) * d; },
+            strip.template multiply<MODE < SUBTRACT>(a, acc, q4, d, false, [&](int cg) { return S + (size_t)min(s0 + 16 * cg + c16, L - 1) * d; },
                            [&](int rg) { return X + (size_t)min(b * 32 + 16 * rg + c16, L - 1) * d; });
             const int xq = b * 32 + 4 * q4;          // streamed row of entry i of acc[rg][.]: xq + 16*rg + i
             if (PASS == 1) {
@@ -332,6 +335,19 @@ int launch_scores_mfma(const void* q, const void* k, int H, int kv_heads, int L,
                        const uint8_t* mask, int M, int32_t* lists, ScoreParts* parts, hipStream_t st);
 size_t scores_mfma_scratch_floats(int H, int L, bool least);
 
+// The kernel of a pass for these strips.  Remainders of fp32 parts come from the dot instruction: fewer instructions, a longer chain.  At
+// 40 to 64 dims that is no gain where three and four waves share a SIMD.  By strips per compute unit, subtracted / dots, us: 3
+// heads x 5308 x 64 (1.9) pass 1 54.9 / 52.3, pass 2 57.0 / 55.0; 4 (2.6) 58.7 / 60.8, 59.2 / 61.2; 3 x 9916 x 48 (3.6) 119 / 128, 122 / 125; 8
+// x 5308 x 64 (5.2) 96.8 / 98.5, 94.8 / 93.5; 24 query heads on 6 x 3576 x 64 pass 1 (10.5) 131 / 137, pass 2 (2.6) 153 / 159; 32 x 5308 x 48
+// (21) 306 / 312, 313 / 317, x 64 354 / 354, 353 / 350.  (x 32: dots gain 2 to 6 % throughout, x 128 3 to 4 %.)
+template <int PASS, typename T, int KS, int CG>
+static auto score_kernel(long strips)
+{
+    if constexpr (sizeof(T) == 4 && (KS == 3 || KS == 4) && CG == 2)
+        if (strips > 512 && (PASS == 1 || strips <= 1024)) return &lookm::k_score_any<PASS + lookm::SUBTRACT, T, KS, CG>;
+    return &lookm::k_score_any<PASS, T, KS, CG>;
+}
+
 template <typename T>
 static int launch_scores_any(const T* q, const T* k, int H, int kv_heads, int L, int d, int R0, float* lse,
                              const float* lse_in, float* scores, float* rnorm, hipStream_t st)
@@ -348,12 +364,12 @@ static int launch_scores_any(const T* q, const T* k, int H, int kv_heads, int L,
         const int nS = (L + 16 * CG - 1) / (16 * CG);
         if (!lse_in) {
             const int n1 = nS - R0 / (16 * CG);       // strips with a query row that counts (observation window)
-            hipLaunchKernelGGL((lookm::k_score_any<1, T, KS, CG>), wide_grid(units(H, n1) + norm_blocks), dim3(256), 0, st, q, k, H, group,
+            hipLaunchKernelGGL((score_kernel<1, T, KS, CG>((long)H * n1)), wide_grid(units(H, n1) + norm_blocks), dim3(256), 0, st, q, k, H, group,
                                L, R0, d, scale2, (const float*)nullptr, 1.0f, lse, n1, together, units(H, n1), norm_rows, rnorm);
             mark(LOOKM_K_SCORE_LSE);
         }
         // a caller-supplied row log-sum-exp is natural-log: one factor log2(e) brings it to the kernels' base
-        hipLaunchKernelGGL((lookm::k_score_any<2, T, KS, CG>), wide_grid(units(kv_heads, nS) + (lse_in ? norm_blocks : 0)), dim3(256), 0,
+        hipLaunchKernelGGL((score_kernel<2, T, KS, CG>((long)kv_heads * nS)), wide_grid(units(kv_heads, nS) + (lse_in ? norm_blocks : 0)), dim3(256), 0,
                            st, q, k, kv_heads, group, L, R0, d, scale2, lse_in ? lse_in : lse, lse_in ? lookm::kLog2e : 1.0f,
                            scores, nS, together, units(kv_heads, nS), lse_in ? norm_rows : 0, rnorm);
         mark(LOOKM_K_SCORE_COLSUM);

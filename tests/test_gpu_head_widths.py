@@ -336,3 +336,15 @@ def test_more_than_two_nearly_equal_cosines(d, dtype, n, padding):
     k[0, 1] = 0
     got, _ = lookm.lookm_nearest(k.cuda(), kept, ev)
     assert (got == 0).all()
+
+
+@pytest.mark.parametrize("d", [40, 48, 56, 64])
+@pytest.mark.parametrize("group", [1, 4])
+def test_remainders_by_dots_and_by_subtraction(d, group):
+    """From 513 strips of 32 rows on the remainders of fp32 parts are differences, below they are dots: the same bits.  Sixteen
+    heads of 33 strips against eight; with grouped heads pass 1 changes the kernel and pass 2 does not."""
+    L = 1050
+    g = torch.Generator(device="cuda").manual_seed(d)
+    q, k = torch.randn(16, L, d, generator=g, device="cuda"), torch.randn(16 // group, L, d, generator=g, device="cuda")
+    halves = [lookm.lookm_scores_grouped(q[a:a + 8].contiguous(), k[a // group:(a + 8) // group].contiguous()) for a in (0, 8)]
+    assert torch.equal(lookm.lookm_scores_grouped(q, k), torch.cat(halves))

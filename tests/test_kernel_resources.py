@@ -60,6 +60,7 @@ def registers(code_objects):
                                           ("k_score_anyILi1EtLi2ELi4EE", 128), ("k_score_anyILi2EtLi2ELi4EE", 128),     # bf16, 40 to 64 wide
                                           ("k_nearest_anyItLi2ELi4EE", 128),
                                           ("k_score_anyILi1EfLi4ELi2EE", 128), ("k_score_anyILi2EfLi4ELi2EE", 168),     # fp32, 56 and 64 wide
+                                          ("k_score_anyILi5EfLi4ELi2EE", 128), ("k_score_anyILi6EfLi4ELi2EE", 168),     # .. remainders by subtraction
                                           ("k_score_anyILi1EfLi8ELi2EE", 256), ("k_score_anyILi2EfLi8ELi2EE", 256),     # 104 to 128: two waves
                                           ("k_nearest_foldILi1EE", 128), ("k_nearest_foldILi2EE", 128), ("k_nearest_foldILi4EE", 128)])
 def test_waves_per_simd(registers, kernel, limit):
