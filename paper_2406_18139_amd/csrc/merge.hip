@@ -188,7 +188,6 @@ __device__ __forceinline__ void merged_row(const raw8<T>& own, const float (&sum
 // quarter of the head's assignment list and keeps the entries of those slots, in order; then they are put into `members` by
 // slot, the waves' shares in order.  begin[0 .. NG]: where each slot's members begin.  scratch_a: Le ints, scratch_b: 8 * NG ints.
 constexpr int SCAN_MAX = 4096, SCAN_SLOTS = 32;      // entries of a list: 12 bits of a word, and 16 KB of them; slots: a lane each
-constexpr int SCAN_FOUR = 3500;                      // entries up to which four workgroups share a compute unit's 160 KB of LDS
 __device__ __forceinline__ void collect_members(const int32_t* __restrict__ assign, int Le, int s0, int ns, int NG, int B, int* begin,
                                                 float* scratch_a, float* scratch_b, unsigned short* members)
 {
@@ -584,17 +583,16 @@ int launch_merge(const void* k, const void* v, const int32_t* kept, const int32_
         return check.status();
     }
     // Short lists: every workgroup of the merge goes through the head's list, instead of a kernel that sorts it.  That kernel and
-    // its launch are 6 to 8 us whatever the merge's size; going through the list is one or two round trips and five barriers
-    // for every round of workgroups (four to a compute unit, three where the list's entry numbers take more of its LDS), so the
-    // line is a number of workgroups.  Even sets, sort and merge / scan, us, by workgroups: 32 heads x 128 bf16, 512 entries, 1024 11.3 / 8.8, 2048
-    // 14.8 / 13.9, 3072 19.1 / 18.6, 4096 22.1 / 23.1, 8192 33.7 / 39.7; 256 heads, 32 entries, 3072 18.1 / 17.3, 8192 31.3 / 36.0; 16 heads x 128
-    // fp32, 1024 entries, 2048 22.1 / 21.0, 2560 25.4 / 25.3, 3584 29.6 / 30.9; 8 heads x 128 bf16, 4096 entries, 768 11.5 / 9.3, 1024 12.3 /
-    // 13.4, 2048 17.7 / 20.0.  Whole layers: 40 heads x 89 workgroups, 461 entries 106.5 / 105.7; 32 x 125, 1037 154.8 / 155.0.
+    // its launch are 6 to 8 us whatever the merge's size (a little less for the shortest lists); going through the list is a
+    // round trip and five barriers for every round of workgroups, four to a compute unit: the line is a number of workgroups.  Whole layers, us, sort and
+    // merge / scan: 32 heads x 128 bf16, 300 entries, 2560 workgroups 88.0 / 85.4, 3584 104.6 / 103.5, 5120 134.8 / 134.8, 6144 151.3 / 153.0,
+    // 8192 209 / 211; 60 entries, 2560 70.4 / 69.8, 3072 81.9 / 81.4, 4096 92.6 / 93.2, 8192 179 / 181; 128 heads, 700 entries, 5120 169.6
+    // / 168.6, 8192 204.3 / 205.3; 32 heads x 256, 300 entries, 5120 138.4 / 138.2, 8192 218.5 / 223.0; 32 x 128 fp32, 300, 5120 524 / 520.
     // Entries times workgroups: past 2048 entries a second round trip; one stream gains up to 2 us more of it (32 x 84 workgroups
     // x 2765 226.4 / 223.9), but two streams, one job's sort beside the other's long kernels, lose: a batch of 32 x 84 x 2733 6 us a layer.
     const long workgroups = (long)H * ((B + (256 / G) - 1) / (256 / G));
-    const long in_time = Le > lookm::SCAN_FOUR ? 768 : dt == LOOKM_F32 ? 2560 : 3584;
-    const bool scan = mode != LOOKM_MERGE_NONE && G >= 8 && Le <= lookm::SCAN_MAX && workgroups <= in_time && workgroups * Le <= 4l << 20;
+    const bool scan = mode != LOOKM_MERGE_NONE && G >= 8 && Le <= lookm::SCAN_MAX && workgroups <= (Le < 256 ? 3072 : 5120) &&
+                      workgroups * Le <= 4l << 20;
     static_assert(256 / 8 <= lookm::SCAN_SLOTS, "a lane for each slot of a workgroup");
     if (scan) {
         member_pos = const_cast<int32_t*>(evicted);          // (read only) by entry number

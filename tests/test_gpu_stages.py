@@ -688,9 +688,9 @@ def test_which_prompts_have_their_chunks_summed_in_the_selection(H, L, summed):
 
 @pytest.mark.parametrize("H,B,Le,d,dtype,sort", [
     (256, 512, 58, 128, torch.bfloat16, True), (32, 2448, 230, 256, torch.bfloat16, True),      # short lists, many workgroups
-    (128, 448, 300, 128, torch.bfloat16, False), (128, 449, 300, 128, torch.bfloat16, True),    # 3584 and 3712 of them
-    (80, 512, 300, 128, torch.float32, False), (80, 513, 300, 128, torch.float32, True),        # 2560 and 2640
-    (64, 192, 3600, 64, torch.bfloat16, False), (64, 800, 3600, 64, torch.bfloat16, True), (64, 800, 2600, 64, torch.bfloat16, False),
+    (128, 384, 255, 128, torch.bfloat16, False), (128, 385, 255, 128, torch.bfloat16, True),    # 3072 and 3200 of them
+    (128, 640, 256, 128, torch.bfloat16, False), (128, 641, 256, 128, torch.bfloat16, True),    # 5120 and 5248
+    (80, 1024, 300, 128, torch.float32, False), (80, 1025, 300, 128, torch.float32, True),
     (64, 1024, 2048, 64, torch.bfloat16, False), (64, 1024, 2049, 64, torch.bfloat16, True),    # 2^22 entries gone through, and more
     (2, 100, 4096, 64, torch.bfloat16, False), (2, 100, 4097, 64, torch.bfloat16, True)])
 def test_which_lists_are_sorted(H, B, Le, d, dtype, sort):
