@@ -628,7 +628,7 @@ k_score_mfma(const bf16_t* __restrict__ q, const bf16_t* __restrict__ k, int H, 
 // head; pass 2 -> scores[h, j] = A_s[j] per key head, the partials of its `group` query heads added in head
 // order (group = 1: one query head per key head).  One thread per (head, row).  With key lists (pass 2 over the
 // competing keys only) row r of strip t is the list's entry t * 256 + r and its score goes to that key's
-// position; the workgroups nS .. 2 nS - 1 of the grid then write the inverse norms of the PROTECTED keys, which
+// position; the workgroups of the grid from nS on then write the inverse norms of the PROTECTED keys, which
 // pass 2 no longer holds (summed in the order of the stand-alone norm kernel, so all three give the same bits).
 template <int PASS>
 __global__ void __launch_bounds__(256)
@@ -639,7 +639,7 @@ k_score_combine(int group, int L, int R0, int C, const float* __restrict__ part_
     const int h = blockIdx.y, r = threadIdx.x;
     int tile = blockIdx.x;
     if (PASS == 2 && lists != nullptr && tile >= nS) {
-        if (rnorm != nullptr) protected_norms(lists, h, L, k, rnorm, (tile - nS) * 32 + (r >> 3), 32 * nS);
+        if (rnorm != nullptr) protected_norms(lists, h, L, k, rnorm, (tile - nS) * 32 + (r >> 3), 32 * ((int)gridDim.x - nS));
         return;
     }
     const bool sparse = PASS == 2 && lists != nullptr;
@@ -843,7 +843,7 @@ int launch_scores_mfma(const void* q, const void* k, int H, int kv_heads, int L,
     // it has 512 threads at most, up to eight, one, where it has 1024: beyond, a single workgroup a head reads for longer than the
     // launch costs.  Whole layers, us, with the fold's kernel / summed there: one head x 1024 (16 chunks), nearly all images 43.3 / 42.8, half
     // text 50.6 / 48.3; two heads x 1024 47.5 / 46.8; one head, nearly all images, x 1088 (17 chunks) 48.8 / 49.8, x 1344 (21) 51.2 / 52.0,
-    // x 2048 (32) 59.8 / 60.8, two x 1088 49.4 / 50.3, x 1600 (25) 54.5 / 56.0 (prompts of mostly text gain 1 there, from the norms); 1024
+    // x 2048 (32) 59.8 / 60.8, two x 1088 49.4 / 50.3, x 1600 (25) 54.5 / 56.0; 1024
     // threads: 8 heads x 2896 in twelve chunks 72.7 / 73.1, one head x 2428 in nineteen 57.9 / 61.2.
     // (H: the heads' workgroups and those of the norms are one grid.)
     if (parts && sparse && group == 1 && H <= 4096 && L <= SELECT_SUMS_MAX_L && G <= (L <= 2048 ? 16 : 8)) {
@@ -856,7 +856,11 @@ int launch_scores_mfma(const void* q, const void* k, int H, int kv_heads, int L,
         parts->R0 = R0;
         return check.status();
     }
-    hipLaunchKernelGGL(lookm::k_score_combine<2>, dim3(sparse ? 2 * nS : nS, kv_heads), dim3(256), 0, st, group, L, R0, C,
+    // Workgroups for the norms of the protected keys: as many as strips.  Few heads of up to 2048 tokens: up to four times as many, with
+    // which eight threads have two keys at most instead of eight (one head x 1344, half text, 58.4 -> 56.4 us the whole layer, 57.2
+    // in the selection; x 2048 with 1472 text tokens 60.6 -> 57.4, 58.6; 2 x 1600, nearly all images, 54.4 -> 54.6, 55.9).
+    const int norm_blocks = !sparse ? 0 : L > 2048 ? nS : std::min(4 * nS, std::max(nS, 1024 / kv_heads - nS));
+    hipLaunchKernelGGL(lookm::k_score_combine<2>, dim3(nS + norm_blocks, kv_heads), dim3(256), 0, st, group, L, R0, C,
                        part_a, part_b, scores, sparse ? (const int32_t*)lists : (const int32_t*)nullptr, kk, rnorm, nS);
     mark(LOOKM_K_SCORE_COLSUM_FOLD);
     return check.status();
