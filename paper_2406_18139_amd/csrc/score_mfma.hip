@@ -858,8 +858,9 @@ int launch_scores_mfma(const void* q, const void* k, int H, int kv_heads, int L,
     }
     // Workgroups for the norms of the protected keys: as many as strips.  Few heads of up to 2048 tokens: up to four times as many, with
     // which eight threads have two keys at most instead of eight (one head x 1344, half text, 58.4 -> 56.4 us the whole layer, 57.2
-    // in the selection; x 2048 with 1472 text tokens 60.6 -> 57.4, 58.6; 2 x 1600, nearly all images, 54.4 -> 54.6, 55.9).
-    const int norm_blocks = !sparse ? 0 : L > 2048 ? nS : std::min(4 * nS, std::max(nS, 1024 / kv_heads - nS));
+    // in the selection; x 2048 with 1472 text tokens 60.6 -> 57.4, 58.6; 2 x 1600, nearly all images, 54.4 -> 54.6, 55.9) - one a
+    // compute unit in all: 800 workgroups that find no key more, 128 query heads on 32 x 1748, nearly all images, 6.5 -> 8.3 us.
+    const int norm_blocks = !sparse ? 0 : L > 2048 ? nS : std::min(4 * nS, std::max(nS, 256 / kv_heads - nS));
     hipLaunchKernelGGL(lookm::k_score_combine<2>, dim3(nS + norm_blocks, kv_heads), dim3(256), 0, st, group, L, R0, C,
                        part_a, part_b, scores, sparse ? (const int32_t*)lists : (const int32_t*)nullptr, kk, rnorm, nS);
     mark(LOOKM_K_SCORE_COLSUM_FOLD);
