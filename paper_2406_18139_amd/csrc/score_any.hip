@@ -335,16 +335,17 @@ int launch_scores_mfma(const void* q, const void* k, int H, int kv_heads, int L,
                        const uint8_t* mask, int M, int32_t* lists, ScoreParts* parts, hipStream_t st);
 size_t scores_mfma_scratch_floats(int H, int L, bool least);
 
-// The kernel of a pass for these strips.  Remainders of fp32 parts come from the dot instruction: fewer instructions, a longer chain.  At
-// 40 to 64 dims that is no gain where three and four waves share a SIMD.  By strips per compute unit, subtracted / dots, us: 3
-// heads x 5308 x 64 (1.9) pass 1 54.9 / 52.3, pass 2 57.0 / 55.0; 4 (2.6) 58.7 / 60.8, 59.2 / 61.2; 3 x 9916 x 48 (3.6) 119 / 128, 122 / 125; 8
-// x 5308 x 64 (5.2) 96.8 / 98.5, 94.8 / 93.5; 24 query heads on 6 x 3576 x 64 pass 1 (10.5) 131 / 137, pass 2 (2.6) 153 / 159; 32 x 5308 x 48
-// (21) 306 / 312, 313 / 317, x 64 354 / 354, 353 / 350.  (x 32: dots gain 2 to 6 % throughout, x 128 3 to 4 %.)
+// The kernel of a pass for these strips, each of up to `streamed` rows.  Remainders of fp32 parts come from the dot instruction: fewer
+// instructions, a longer chain.  At 40 to 64 dims that is a loss where long strips keep three and four waves a SIMD busy.  By strips per
+// compute unit, subtracted / dots, us: 3 heads x 5308 x 64 (1.9) pass 1 54.9 / 52.3, pass 2 57.0 / 55.0; 4 (2.6) 58.7 / 60.8, 59.2 / 61.2; 3 x
+// 9916 x 48 (3.6) 119 / 126, 120 / 123; 8 x 5308 x 64 (5.2) 96.8 / 98.5, 94.8 / 93.5; 24 query heads on 6 x 3576 x 64 pass 1 (10.5) 131 /
+// 137, pass 2 (2.6) 153 / 159; 24 x 5308 x 64 (15.6) 271 / 268, 269 / 266.  Short strips, whole layers: 4 heads x 4156 x 64 (2.0) 126 / 123, 32 x
+// 956 (3.8) 66.0 / 64.8, 64 x 1692 (13) 219 / 215.  (x 32: dots gain 2 to 6 % throughout, x 128 3 to 4 %.)
 template <int PASS, typename T, int KS, int CG>
-static auto score_kernel(long strips)
+static auto score_kernel(long strips, long streamed)
 {
     if constexpr (sizeof(T) == 4 && (KS == 3 || KS == 4) && CG == 2)
-        if (strips > 512 && (PASS == 1 || strips <= 1024)) return &lookm::k_score_any<PASS + lookm::SUBTRACT, T, KS, CG>;
+        if (streamed >= 3500 && strips > 576 && strips <= (PASS == 1 ? 2816 : 1024)) return &lookm::k_score_any<PASS + lookm::SUBTRACT, T, KS, CG>;
     return &lookm::k_score_any<PASS, T, KS, CG>;
 }
 
@@ -364,12 +365,12 @@ static int launch_scores_any(const T* q, const T* k, int H, int kv_heads, int L,
         const int nS = (L + 16 * CG - 1) / (16 * CG);
         if (!lse_in) {
             const int n1 = nS - R0 / (16 * CG);       // strips with a query row that counts (observation window)
-            hipLaunchKernelGGL((score_kernel<1, T, KS, CG>((long)H * n1)), wide_grid(units(H, n1) + norm_blocks), dim3(256), 0, st, q, k, H, group,
+            hipLaunchKernelGGL((score_kernel<1, T, KS, CG>((long)H * n1, L)), wide_grid(units(H, n1) + norm_blocks), dim3(256), 0, st, q, k, H, group,
                                L, R0, d, scale2, (const float*)nullptr, 1.0f, lse, n1, together, units(H, n1), norm_rows, rnorm);
             mark(LOOKM_K_SCORE_LSE);
         }
         // a caller-supplied row log-sum-exp is natural-log: one factor log2(e) brings it to the kernels' base
-        hipLaunchKernelGGL((score_kernel<2, T, KS, CG>((long)kv_heads * nS)), wide_grid(units(kv_heads, nS) + (lse_in ? norm_blocks : 0)), dim3(256), 0,
+        hipLaunchKernelGGL((score_kernel<2, T, KS, CG>((long)kv_heads * nS, (long)group * (L - R0))), wide_grid(units(kv_heads, nS) + (lse_in ? norm_blocks : 0)), dim3(256), 0,
                            st, q, k, kv_heads, group, L, R0, d, scale2, lse_in ? lse_in : lse, lse_in ? lookm::kLog2e : 1.0f,
                            scores, nS, together, units(kv_heads, nS), lse_in ? norm_rows : 0, rnorm);
         mark(LOOKM_K_SCORE_COLSUM);

@@ -341,10 +341,11 @@ def test_more_than_two_nearly_equal_cosines(d, dtype, n, padding):
 @pytest.mark.parametrize("d", [40, 48, 56, 64])
 @pytest.mark.parametrize("group", [1, 4])
 def test_remainders_by_dots_and_by_subtraction(d, group):
-    """From 513 strips of 32 rows on the remainders of fp32 parts are differences, below they are dots: the same bits.  Sixteen
-    heads of 33 strips against eight; with grouped heads pass 1 changes the kernel and pass 2 does not."""
-    L = 1050
+    """Between 577 and 1024 strips of 32 rows (pass 1: 2816) that go along 3500 rows and more the remainders of fp32 parts are
+    differences, otherwise they are dots: the same bits.  Eight heads of 110 strips against each half of them; of grouped heads the
+    strips of pass 2 go along four queries a row, and are too few for it."""
+    L = 3517
     g = torch.Generator(device="cuda").manual_seed(d)
-    q, k = torch.randn(16, L, d, generator=g, device="cuda"), torch.randn(16 // group, L, d, generator=g, device="cuda")
-    halves = [lookm.lookm_scores_grouped(q[a:a + 8].contiguous(), k[a // group:(a + 8) // group].contiguous()) for a in (0, 8)]
+    q, k = torch.randn(8, L, d, generator=g, device="cuda"), torch.randn(8 // group, L, d, generator=g, device="cuda")
+    halves = [lookm.lookm_scores_grouped(q[a:a + 4].contiguous(), k[a // group:(a + 4) // group].contiguous()) for a in (0, 4)]
     assert torch.equal(lookm.lookm_scores_grouped(q, k), torch.cat(halves))
