@@ -588,11 +588,11 @@ int launch_merge(const void* k, const void* v, const int32_t* kept, const int32_
     // merge / scan: 32 heads x 128 bf16, 300 entries, 2560 workgroups 88.0 / 85.4, 3584 104.6 / 103.5, 5120 134.8 / 134.8, 6144 151.3 / 153.0,
     // 8192 209 / 211; 60 entries, 2560 70.4 / 69.8, 3072 81.9 / 81.4, 4096 92.6 / 93.2, 8192 179 / 181; 128 heads, 700 entries, 5120 169.6
     // / 168.6, 8192 204.3 / 205.3; 32 heads x 256, 300 entries, 5120 138.4 / 138.2, 8192 218.5 / 223.0; 32 x 128 fp32, 300, 5120 524 / 520;
-    // 240 entries, 3136 91.9 / 90.5, 180, 3584 62.1 / 61.0; rows that leave lanes idle, 32 x 80, 300, 3072 81.9 / 80.6, 3392 94.2 / 94.9, 4880 128.4 / 130.6.
+    // 240 entries, 3136 91.9 / 90.5, 180, 3584 62.1 / 61.0; rows that leave lanes idle, 32 x 80, 461, 3232 92.8 / 91.5, 691, 3936 87.2 / 88.4, 4880 128.4 / 130.6.
     // Entries times workgroups: past 2048 entries a second round trip; one stream gains up to 2 us more of it (32 x 84 workgroups
     // x 2765 226.4 / 223.9), but two streams, one job's sort beside the other's long kernels, lose: a batch of 32 x 84 x 2733 6 us a layer.
     const long workgroups = (long)H * ((B + (256 / G) - 1) / (256 / G));
-    const bool scan = mode != LOOKM_MERGE_NONE && G >= 8 && Le <= lookm::SCAN_MAX && workgroups <= (8 * G != d ? 3072 : Le < 256 ? 3584 : 5120) &&
+    const bool scan = mode != LOOKM_MERGE_NONE && G >= 8 && Le <= lookm::SCAN_MAX && workgroups <= (8 * G != d || Le < 256 ? 3584 : 5120) &&
                       workgroups * Le <= 4l << 20;
     static_assert(256 / 8 <= lookm::SCAN_SLOTS, "a lane for each slot of a workgroup");
     if (scan) {
