@@ -339,13 +339,13 @@ size_t scores_mfma_scratch_floats(int H, int L, bool least);
 // instructions, a longer chain.  At 40 to 64 dims that is a loss where long strips keep three and four waves a SIMD busy.  By strips per
 // compute unit, subtracted / dots, us: 3 heads x 5308 x 64 (1.9) pass 1 54.9 / 52.3, pass 2 57.0 / 55.0; 4 (2.6) 58.7 / 60.8, 59.2 / 61.2; 3 x
 // 9916 x 48 (3.6) 119 / 126, 120 / 123; 8 x 5308 x 64 (5.2) 96.8 / 98.5, 94.8 / 93.5; 24 query heads on 6 x 3576 x 64 pass 1 (10.5) 131 /
-// 137, pass 2 (2.6) 153 / 159; 24 x 5308 x 64 (15.6) 271 / 268, 269 / 266.  Short strips, whole layers: 4 heads x 4156 x 64 (2.0) 126 / 123, 32 x
+// 137, pass 2 (2.6) 153 / 159; 40 on 10 x 3384 pass 2 (4.1), layer, 306 / 315; 24 x 5308 x 64 (15.6) 271 / 268, 269 / 266.  Short strips, whole layers: 4 heads x 4156 x 64 (2.0) 126 / 123, 32 x
 // 956 (3.8) 66.0 / 64.8, 64 x 1692 (13) 219 / 215.  (x 32: dots gain 2 to 6 % throughout, x 128 3 to 4 %.)
 template <int PASS, typename T, int KS, int CG>
 static auto score_kernel(long strips, long streamed)
 {
     if constexpr (sizeof(T) == 4 && (KS == 3 || KS == 4) && CG == 2)
-        if (streamed >= 3500 && strips > 576 && strips <= (PASS == 1 ? 2816 : 1024)) return &lookm::k_score_any<PASS + lookm::SUBTRACT, T, KS, CG>;
+        if (streamed >= 3500 && strips > 576 && strips <= (PASS == 1 ? 2816 : 1152)) return &lookm::k_score_any<PASS + lookm::SUBTRACT, T, KS, CG>;
     return &lookm::k_score_any<PASS, T, KS, CG>;
 }
 

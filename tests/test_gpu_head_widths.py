@@ -341,7 +341,7 @@ def test_more_than_two_nearly_equal_cosines(d, dtype, n, padding):
 @pytest.mark.parametrize("d", [40, 48, 56, 64])
 @pytest.mark.parametrize("group", [1, 4])
 def test_remainders_by_dots_and_by_subtraction(d, group):
-    """Between 577 and 1024 strips of 32 rows (pass 1: 2816) that go along 3500 rows and more the remainders of fp32 parts are
+    """Between 577 and 1152 strips of 32 rows (pass 1: 2816) that go along 3500 rows and more the remainders of fp32 parts are
     differences, otherwise they are dots: the same bits.  Eight heads of 110 strips against each half of them; of grouped heads the
     strips of pass 2 go along four queries a row, and are too few for it."""
     L = 3517
