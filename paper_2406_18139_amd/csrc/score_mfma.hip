@@ -844,9 +844,11 @@ int launch_scores_mfma(const void* q, const void* k, int H, int kv_heads, int L,
     // launch costs.  Whole layers, us, with the fold's kernel / summed there: one head x 1024 (16 chunks), nearly all images 43.3 / 42.8, half
     // text 50.6 / 48.3; two heads x 1024 47.5 / 46.8; one head, nearly all images, x 1088 (17 chunks) 48.8 / 49.8, x 1344 (21) 51.2 / 52.0,
     // x 2048 (32) 59.8 / 60.8, two x 1088 49.4 / 50.3, x 1600 (25) 54.5 / 56.0; 1024
-    // threads: 8 heads x 2896 in twelve chunks 72.7 / 73.1, one head x 2428 in nineteen 57.9 / 61.2.
+    // threads: 8 heads x 2896 in twelve chunks 72.7 / 73.1, one head x 2428 in nineteen 57.9 / 61.2.  Workgroups of 1024 threads, two to a
+    // compute unit, are also a slow way through many norms once the heads' own ones are on every compute unit: x 2100, most of it text, 128
+    // heads 278.3 / 273.6, 192 386.2 / 383.5, 256 490.8 / 498.2, x 3144 760 / 772.
     // (H: the heads' workgroups and those of the norms are one grid.)
-    if (parts && sparse && group == 1 && H <= 4096 && L <= SELECT_SUMS_MAX_L && G <= (L <= 2048 ? 16 : 8)) {
+    if (parts && sparse && group == 1 && L <= SELECT_SUMS_MAX_L && (L <= 2048 ? G <= 16 && H <= 4096 : G <= 8 && H <= 192)) {
         parts->part = part_a;
         parts->lists = lists;
         parts->k = k;

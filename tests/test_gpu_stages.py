@@ -679,10 +679,11 @@ def test_profile_reads_zero_for_what_is_not_launched(skipped, args):
 
 
 @pytest.mark.parametrize("H,L,summed", [(1, 1024, True), (1, 1025, False), (1, 2048, False), (2, 1088, False), (2, 2048, True), (8, 2048, True),
-                                        (40, 2049, True), (8, 2896, False), (32, 4096, True), (32, 4097, False)])
+                                        (40, 2049, True), (8, 2896, False), (32, 4096, True), (32, 4097, False),
+                                        (192, 2100, True), (193, 2100, False), (256, 2048, True)])
 def test_which_prompts_have_their_chunks_summed_in_the_selection(H, L, summed):
-    """Sixteen chunks at most (1 x 1024, 2 x 2048), past 2048 positions eight (32 x 4096; 8 x 2896 has twelve); 1 x 1025 has seventeen,
-    1 x 2048 thirty-two."""
+    """Sixteen chunks at most (1 x 1024, 2 x 2048), past 2048 positions eight (32 x 4096; 8 x 2896 has twelve) of 192 heads at most; 1 x 1025
+    has seventeen, 1 x 2048 thirty-two."""
     assert (kernel_times(H, L, L // 2, 128, torch.bfloat16)["score_colsum_fold"] == 0.0) == summed
 
 
