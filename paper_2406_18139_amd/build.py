@@ -17,6 +17,7 @@ PKG = Path(__file__).resolve().parent
 CSRC = PKG / "csrc"
 OBJ = PKG / "_build"
 LIB = PKG / "liblookm.so"
+SPLIT_CHECK = OBJ / "libsplit_check.so"
 
 SOURCES = ["api.hip", "score_any.hip", "score_mfma.hip", "select.hip", "nearest_any.hip", "nearest_mfma.hip",
            "merge.hip", "decode.hip", "probe.hip"]
@@ -35,6 +36,17 @@ def _compile(src: str) -> Path:
     if err.strip():
         sys.stderr.write(err + "\n")
     return obj
+
+
+def build_split_check() -> Path:
+    """tests/split_check.hip: the splitting of floats into bf16 parts (csrc/frag.h) by itself, for a GPU test."""
+    OBJ.mkdir(exist_ok=True)
+    tmp = SPLIT_CHECK.with_suffix(f".so.tmp{os.getpid()}")
+    p = subprocess.run([HIPCC, *FLAGS, "-shared", str(PKG.parent / "tests" / "split_check.hip"), "-o", str(tmp)], capture_output=True, text=True)
+    if p.returncode != 0:
+        raise RuntimeError(f"hipcc failed for split_check.hip:\n{p.stderr}")
+    os.replace(tmp, SPLIT_CHECK)
+    return SPLIT_CHECK
 
 
 SAN_FLAGS = ["-Xarch_host", "-fsanitize=address", "-Xarch_host", "-fsanitize=undefined", "-Xarch_host",

@@ -152,8 +152,8 @@ struct frag_split {
 };
 // The remainders come from the dot instruction of bf16 pairs: a pair of parts by (-1, 0) or (0, -1), added to the float, is one
 // instruction where widening the part and subtracting it are two (a whole layer of 16 x 1483 x 128 125 -> 122.5 us, 32 x 2804 x 128
-// 572 -> 554).  Exact like the subtraction, subnormal remainders too (checked
-// bit for bit on 8 million floats of every magnitude); an infinity makes its neighbour in the pair a NaN as well, and so the
+// 572 -> 554).  Exact like the subtraction, subnormal remainders too (the
+// tests hold both bit for bit against the host's on 4 million floats of every magnitude); an infinity makes its neighbour in the pair a NaN as well, and so the
 // products of that row, which it does without that.
 // (The pairs of factors are hidden in registers: from the constant 0x0000bf80 the compiler makes the inline constant
 // -1.0, which the instruction takes for 0xbf800000.)

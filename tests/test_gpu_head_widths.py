@@ -1,12 +1,14 @@
 """The matrix-core kernels for head widths other than bf16 x 128 (score_any.hip, nearest_any.hip) against the oracle:
 widths that fill their operand steps and widths that do not, prompts around the 32-row block and the strip of 16, 32 or
 64 rows, grids on both sides of the size from which a wave holds several groups of stationary rows."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
 
 import oracle
-from paper_2406_18139_amd import lookm
+from paper_2406_18139_amd import build, lookm
 from tests import parity
 
 pytestmark = pytest.mark.gpu
@@ -349,3 +351,31 @@ def test_remainders_by_dots_and_by_subtraction(d, group):
     q, k = torch.randn(8, L, d, generator=g, device="cuda"), torch.randn(8 // group, L, d, generator=g, device="cuda")
     halves = [lookm.lookm_scores_grouped(q[a:a + 4].contiguous(), k[a // group:(a + 4) // group].contiguous()) for a in (0, 4)]
     assert torch.equal(lookm.lookm_scores_grouped(q, k), torch.cat(halves))
+
+
+def test_bf16_parts_bit_for_bit():
+    """The three parts of a float are the nearest bf16 of what the parts before leave, whichever instruction works the remainders out
+    and in either place of a pair: four million floats of every exponent that bf16 holds, both signs, subnormal ones and subnormal
+    remainders among them, next to others of any magnitude.  An odd last step leaves zeros."""
+    lib = ctypes.CDLL(str(build.SPLIT_CHECK if build.SPLIT_CHECK.exists() else build.build_split_check()))
+    n = 1 << 22
+    g = torch.Generator().manual_seed(3)
+    bits = torch.randint(0, 1 << 23, (n,), generator=g, dtype=torch.int32)                # mantissas; a quarter of them short
+    bits &= torch.where(torch.rand(n, generator=g) < 0.25, torch.full((), 0x7f8000), torch.full((), 0x7fffff)).int()
+    bits |= torch.randint(0, 255, (n,), generator=g, dtype=torch.int32) << 23
+    bits = torch.minimum(bits, torch.full((), 0x7f7f7fff, dtype=torch.int32))             # above: rounds to infinity
+    x = torch.where(torch.rand(n, generator=g) < 0.5, -1.0, 1.0) * bits.view(torch.float32)
+    x[:8] = torch.tensor([0.0, -0.0, 2.0 ** -149, -2.0 ** -149, 2.0 ** -126, 3.3895e38, -3.3895e38, 1.0])
+    rest, want = x.clone(), []
+    for _ in range(3):
+        want.append(rest.bfloat16())
+        rest = rest - want[-1].float()
+    want = torch.stack([w.view(torch.int16).view(n // 8, 8) for w in want], 1)            # [groups, part, value]
+    out = torch.empty(3, n // 8, 3, 8, dtype=torch.int16, device="cuda")
+    xg = x.cuda()
+    assert lib.split_check(ctypes.c_void_p(xg.data_ptr()), n // 8, *(ctypes.c_void_p(o.data_ptr()) for o in out),
+                           ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    dots, differences, half = out.cpu()
+    assert torch.equal(differences, want)
+    assert torch.equal(dots, want)
+    assert torch.equal(half[:, :, :4], want[:, :, :4]) and not half[:, :, 4:].any()
