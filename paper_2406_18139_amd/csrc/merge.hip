@@ -385,8 +385,9 @@ k_merge(const T* __restrict__ k, const T* __restrict__ v, const int32_t* __restr
 // memory latencies; this one is a kernel and a round trip shorter (2 heads x 256 x 64 fp32, the whole layer: 27.0 -> 23.4 us; 23.8 when
 // a wave read positions and cosines of its own entries after it had found them).
 // Members are added up by the slot's lane group, up to SHARED of them: one after the other they would make the largest set the
-// time of the kernel.  (8 heads, 1020 members on 256 slots x 128 bf16, us, a slot's own lane group for all / shared: all in one
-// set 176 / 45, half of them 93 / 28, even sets 7.6 / 7.3; with a sort and a lane group per slot 171, 89, 10.6.)
+// time of the kernel.  (8 heads, 256 members on 256 slots x 128 bf16, us, a slot's own lane group for all / shared / the merge whose
+// workgroups scan / sort and merge: all in one set 41.9 / 13.5 / 9.6 / 13.5, half of them 24.2 / 11.1 / 8.7 / 12.1, even sets 5.1 / 5.2 /
+// 5.6 / 8.4; 2 heads, 256 on 154 x 64 fp32 34.0 / 7.7 / 9.2 / 13.1, 20.9 / 7.9 / 8.9 / 12.2, 4.8 / 4.9 / 5.4 / 8.0.)
 constexpr int DIRECT_MAX = 256, SHARED = 32;
 template <typename T, int NB>
 __global__ void __launch_bounds__(256)
@@ -510,7 +511,8 @@ k_merge_direct(const T* __restrict__ k, const T* __restrict__ v, const int32_t* 
 namespace lookm_host {
 
 // Segments per head: as many as make no more workgroups than there are compute units (40 heads x 2765 entries in seven segments,
-// 280 workgroups, 8.0 us, in six 6.7), and no more than BK_MAX_SEG slots in one segment.
+// 280 workgroups, 8.0 us, in six 6.7; whole layers of 24, 40, 64, 96, 128, 160, 200 and 255 heads with one segment more: the same
+// within 0.4 %), and no more than BK_MAX_SEG slots in one segment.
 static void bucket_segments(int H, int B, int& S, int& NS)
 {
     int ns = std::max(1, 256 / H);
@@ -565,11 +567,11 @@ int launch_merge(const void* k, const void* v, const int32_t* kept, const int32_
     const LaunchCheck check;
     if (Le == 0) mode = LOOKM_MERGE_NONE;
     const int G = 1 << merge_lanes(d);
-    // The shortest lists: a wave collects the members of its slots by itself.  The whole layer in us against the merge whose
-    // workgroups scan (below) and against sort and merge: 2 heads, 102 entries in 154 slots x 64 fp32 23.8 / 24.6 / 27.2; 2, 173 in 119
-    // x 64 25.5 / 25.9 / 28.4; 8, 389 in 143 x 128 fp32 43.7 / 43.0 / 45.8; 8, 518 in 158 x 64 bf16 30.1 / 29.5 / 32.5, x 128
-    // 48.8 / 47.6 / 50.8.  Sets of four on average: 8 heads, 1020 in 180 slots 12.2 us sorted and merged, 12.5 this way, in 80
-    // slots 15.1 and 20.5.  A lane group has eight lanes and more, so that a wave has at most eight slots.
+    // The shortest lists: a wave collects the members of its slots by itself.  The merge alone, even sets, us, this way / by the merge whose
+    // workgroups scan (below) / sorted: 2 heads, 102 entries in 154 slots x 64 fp32 4.6 / 5.0 / 7.7; 8, 128 in 143 x 128 fp32 4.7 / 5.3 /
+    // 8.0; 8, 256 in 64 x 128 bf16 5.9 / 6.6 / 9.4; 32, 256 in 64 x 64 bf16 6.0 / 6.8 / 9.6.  Whole layers beyond 256 entries, this way in
+    // two and four times the registers / scan: 1 head, 346 in 386 x 80 28.3 / 27.8; 2, 500 in 200 x 64 fp32 34.2 / 33.1; 8, 500 in 200 x 128
+    // 46.5 / 45.3.  A lane group has eight lanes and more, so that a wave has at most eight slots.
     if (mode != LOOKM_MERGE_NONE && Le <= lookm::DIRECT_MAX && Le <= 4 * (long)B && G >= 8 && (size_t)H * B * G / 64 <= 2048) {
         const int spb = 4 * (64 / G);
         auto go = [&](auto type) {

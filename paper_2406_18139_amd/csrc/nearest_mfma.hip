@@ -437,8 +437,9 @@ constexpr int NF_LDS_CHUNKS = 4;  // chunks whose block masks the fold keeps in 
 // below COS_MIN, takes every slot.
 // (Four waves a SIMD at 126 registers: at six, 80 of them, fourteen values and more went through scratch memory, which cost more than
 // the 1312 workgroups of 32 heads x 12644 gained from being resident all at once.  us: 32 x 2896 10.1 -> 8.1, 40 x 5904 15.2 -> 10.1,
-// 32 x 12644 21.7 -> 16.9, 32 x 7613 with 2123 conserved keys 12.8 -> 8.7; with rows fetched an eighth ahead at 94 registers 8.8,
-// 10.9, 16.9, 9.4.)
+// 32 x 12644 21.7 -> 16.9, 32 x 7613 with 2123 conserved keys 12.8 -> 8.7.  Step by step, timed with events, one after the other: six waves
+// 12.7, 17.0, 25.5, 14.1; four 11.8, 14.3, 20.8, 12.6; the round's lists cleared ahead of the partials 11.9, 14.4, 21.1, 12.7 (no
+// difference); groups counted from the marks 11.5, 13.6, 20.1, 12.4; rows by quarters instead of an eighth ahead 11.0, 12.7, 20.5, 11.5.)
 template <int cbits>   // counter width of the mark words (near_counter_bits of the chunk length)
 __global__ void __launch_bounds__(NF_THREADS, 4)
 k_nearest_fold(const bf16_t* __restrict__ k, const float* __restrict__ rnorm, const int32_t* __restrict__ kept,

@@ -15,9 +15,10 @@
 //
 // What bounds it: bf16 - the vector ALU, busy 80 % of the time in pass 1 and 75 % in pass 2 at 64 dims with an exponential and its
 // two companions per logit.  fp32 - the splitting of every streamed row into bf16 parts for every strip (three and
-// a half instructions a float, two of them dots): at 64 dims and four waves a SIMD the vector ALU is busy 86 % (pass 1); at 128, two waves, 62 % and the
-// matrix pipe 35 %, 86 % of the time one or both, and the longest strips run alone for the last fifth.  Both passes, traced:
-// 16 heads x 1483 x 128 fp32 87 us (82 timed with events; 126 on the fp32 matrix instruction, beside which the vector ALU stands
+// a half instructions a float, two of them dots): at 64 dims and four waves a SIMD the vector
+// ALU is busy 66 % (pass 1) and the matrix pipe 44 %, one or both all the time; at 128, two waves, 50 % and 36 %, one or both
+// 81 % (dots leave the matrix pipe less company: both at once 13 % of its time, with subtractions 31 %), and the longest strips run alone for the last fifth.  Both passes, traced:
+// 16 heads x 1483 x 128 fp32 84 us (126 on the fp32 matrix instruction, beside which the vector ALU stands
 // still; 685 on the vector ALU, with 64 x 64 tiles in LDS), 32 x 2781 x 64 bf16 60 us (790), x 80 74 us, 2 x 256 x 64 fp32
 // 10 us (64).  Stationary rows through LDS, blocks through a buffer descriptor, log-sum-exps straight to LDS and the first block
 // of a wave without a sum against a reference that it has not got, all timed with events: 121 -> 105 us for the first (on the
